@@ -289,6 +289,8 @@ rtl_status rtl_diag_pack_sweep(const void* X, int64_t M, int64_t K, int64_t ldx,
 /* rtl_diag_tile_plan - diagnostic (host arithmetic only, nothing is launched): how the linears cut an
  * [M, N] output into workgroup tiles. plan (HOST pointer, int64[4]) receives {body tile width (256 or
  * 192), rows covered by 256-row body tiles, number of body tiles, number of 256 x 128 tail tiles}.
+ * Problems that would leave the chip idle with 256-row tiles (few tokens, narrow layers; the choice also
+ * depends on K) run on smaller tiles instead, which this plan does not describe.
  * dense != 0 asks for the plan of rtl_dense_linear, else of the sparse linears. */
 rtl_status rtl_diag_tile_plan(int64_t M, int64_t N, int dense, int64_t* plan);
 

@@ -107,19 +107,25 @@ __device__ __forceinline__ void wait_vmcnt_lgkm0() {   // vmcnt <= N, all LDS re
 // dense k, or 32 dense k); rows of the B tile hold 128 bytes (sparse) or 64 bytes (dense).
 // D64 (dense only): stages of 64 dense k, 128-byte rows on both sides, so that every L2 request
 // of the row-major operands is a whole line; a sub-step is then two matrix instructions deep.
+// WAVES_K > 1: a stage holds one k block per K group (see gemm_tile), kGroup bytes each.
 template <bool SPARSE, int BM, int BN, int STAGES, int WAVES_M = 1, int WAVES_N = 1, bool FP8 = false,
-          bool D64 = false>
+          bool D64 = false, int WAVES_K = 1>
 struct Smem {
     static constexpr int kABytes = BM * (D64 ? 128 : 64);
     static constexpr int kMetaRec = FP8 ? 16 : 8;   // metadata bytes per row and stage
     static constexpr int kMetaBytes = SPARSE ? BM * kMetaRec : 0;
     static constexpr int kBBytes = (SPARSE || D64) ? BN * 128 : BN * 64;
-    static constexpr int kStage = kABytes + kMetaBytes + kBBytes;
+    static constexpr int kGroup = kABytes + kMetaBytes + kBBytes;
+    static constexpr int kStage = WAVES_K * kGroup;
     static constexpr int kRing = STAGES * kStage;
     // epilogue staging: every wave owns (BM / WAVES_M) rows of (BN / WAVES_N) bf16 plus 16 bytes
     // of padding per row (keeps rows 4 apart, written together, in different banks)
     static constexpr int kEpiRowBytes = (BN / WAVES_N) * 2 + 16;
-    static constexpr int kEpi = WAVES_M * WAVES_N * (BM / WAVES_M) * kEpiRowBytes;
+    // K groups: one fp32 plane of the tile per group instead; 8 floats of row padding put rows 4 apart
+    // (written together by the two lane halves) 32 banks apart
+    static constexpr int kPitch = BN + 8;
+    static constexpr int kPlane = BM * kPitch * 4;
+    static constexpr int kEpi = WAVES_K > 1 ? WAVES_K * kPlane : WAVES_M * WAVES_N * (BM / WAVES_M) * kEpiRowBytes;
     static constexpr int kTotal = kRing > kEpi ? kRing : kEpi;
     static_assert(kTotal <= 160 * 1024, "LDS budget of a CU");
 };
@@ -144,13 +150,13 @@ __device__ __forceinline__ void unswz4(int p, int& row, int& c) {
 
 // Tile order: consecutive workgroup ids land on different XCDs (round robin), so ids are first
 // regrouped per XCD (XCD x works through a contiguous share of the tile list), and the list walks
-// the tile grid in groups of 8 tile-rows so that the ~32 tiles an XCD runs at a time share few
+// the tile grid in groups of GM tile-rows so that the ~32 tiles an XCD runs at a time share few
 // activation and weight panels in its L2.
 __device__ __forceinline__ int xcd_share_start(int n, int xcd) {   // first list index of XCD xcd's share of n tiles
     return xcd * (n / 8) + min(xcd, n % 8);
 }
+template <int GM>
 __device__ __forceinline__ void tile_walk(int t, int tiles_m, int tiles_n, int& pm, int& pn) {
-    constexpr int GM = 8;
     const int per_group = GM * tiles_n;
     const int group = t / per_group;
     const int first_m = group * GM;
@@ -159,20 +165,31 @@ __device__ __forceinline__ void tile_walk(int t, int tiles_m, int tiles_n, int& 
     pn = (t % per_group) / gsize;
 }
 
+// a * b and x + y rounded one by one: the LoRA form (sum of residual and bias as `add`) and the plain form
+// (bias alone) then agree bit for bit when the residual is zero.
+__device__ __forceinline__ float mul_add_rn(float a, float b, float add) {
+#pragma clang fp contract(off)
+    const float p = a * b;
+    return p + add;
+}
+
 // MODE 0: plain linear. MODE 1 (sparse only): LoRA tail, the accumulators also receive T L_A^T before
 // the epilogue.
 // `tile`: index of this workgroup's output tile in the walk of the (M / BM) x (N / BN) tile grid.
+// WAVES_K > 1: the waves divide the contraction too. K group g of the WAVES_K groups of WAVES_M x WAVES_N
+// waves takes the k blocks g, g + WAVES_K, ... with operands and accumulators of its own, and the groups'
+// tiles are added up in LDS, in the order of g, when the loop is done.
 template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false,
-          bool D64 = false>
+          bool D64 = false, int WAVES_K = 1>
 __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
     static_assert(!D64 || (!SPARSE && MODE != 1), "64-k stages: dense kernels only");
     static_assert(MODE == 0 || (MODE == 1 && SPARSE), "mode/operand combination");
     static_assert(!FP8 || SPARSE, "FP8 operands: sparse kernels only");
-    constexpr int NW = WAVES_M * WAVES_N;
+    constexpr int NW = WAVES_M * WAVES_N;             // waves that share a block of operands
     constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
     constexpr int TM = WTM / 32, TN = WTN / 32;
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be made of 32x32 blocks");
-    using L = Smem<SPARSE, BM, BN, STAGES, WAVES_M, WAVES_N, FP8, D64>;
+    using L = Smem<SPARSE, BM, BN, STAGES, WAVES_M, WAVES_N, FP8, D64, WAVES_K>;
     constexpr int ESZ = FP8 ? 1 : 2;                  // bytes per operand element
     constexpr int KSTAGE = SPARSE ? 128 / ESZ : (D64 ? 64 : 32);   // dense k per stage
     constexpr int A_ELEMS = D64 ? 64 : 64 / ESZ;      // elements of an A row per stage: 64 bytes (D64: 128)
@@ -196,14 +213,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
     extern __shared__ __align__(16) uint8_t smem[];
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, lives in an SGPR
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);    // wave-uniform, lives in an SGPR
+    const int wk = WAVES_K > 1 ? wid / NW : 0, wave = WAVES_K > 1 ? wid % NW : wid;   // K group, wave inside it
+    uint8_t* const ring = smem + wk * L::kGroup;                 // the group's part of the first stage
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)ring;
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
     int pm, pn;
-    tile_walk(tile, tiles_m, tiles_n, pm, pn);
+    tile_walk<(BM >= 256 ? 8 : 16)>(tile, tiles_m, tiles_n, pm, pn);
     const int64_t m0 = (int64_t)pm * BM, n0 = (int64_t)pn * BN;
-    const int KT = (int)(a.K / KSTAGE);
+    const int blocks = (int)(a.K / KSTAGE);
+    const int KT = WAVES_K > 1 ? (blocks - wk + WAVES_K - 1) / WAVES_K : blocks;   // stages in which this wave's group has a block
 
     // ---- global -> LDS: every lane owns fixed chunks; rows past the edge are clamped to the last
     //      valid row (their products only reach outputs that are never stored) -----------------
@@ -255,18 +275,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
         constexpr int n = decltype(n_tag)::value;
         const uint32_t base = lds0 + stage * L::kStage;
         if constexpr (n < A_PER_W) {
-            lds_dma16_so(base_a + (int64_t)kt * a_stride, oa[n], base + (wave * A_PER_W + n) * 1024);
+            lds_dma16_so(base_a + (int64_t)(kt * WAVES_K + wk) * a_stride, oa[n], base + (wave * A_PER_W + n) * 1024);
         } else if constexpr (n < A_PER_W + B_PER_W) {
             constexpr int s = n - A_PER_W;
             const uint32_t dst = base + L::kABytes + L::kMetaBytes + (wave * B_CH + s * 64) * 16;
             if constexpr (B_HALF && s == B_PER_W - 1) {
-                if (lane < 32) lds_dma16_so(base_b + (int64_t)kt * (KSTAGE * ESZ), ob[s], dst);
+                if (lane < 32) lds_dma16_so(base_b + (int64_t)(kt * WAVES_K + wk) * (KSTAGE * ESZ), ob[s], dst);
             } else {
-                lds_dma16_so(base_b + (int64_t)kt * (KSTAGE * ESZ), ob[s], dst);
+                lds_dma16_so(base_b + (int64_t)(kt * WAVES_K + wk) * (KSTAGE * ESZ), ob[s], dst);
             }
         } else if constexpr (SPARSE && n < A_PER_W + B_PER_W + M_PER_W) {
             constexpr int s = n - A_PER_W - B_PER_W;
-            lds_dma4_so(base_m + (int64_t)kt * meta_stride + s * 256, om,
+            lds_dma4_so(base_m + (int64_t)(kt * WAVES_K + wk) * meta_stride + s * 256, om,
                         base + L::kABytes + (wave * M_PER_W + s) * 256);
         }
     };
@@ -289,7 +309,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
         gload_one(kt, stage, std::integral_constant<int, 15>{});
     };
     constexpr int LOADS_PER_STAGE = A_PER_W + B_PER_W + (SPARSE ? M_PER_W : 0);
-    static_assert(LOADS_PER_STAGE <= 16 && (LOADS_PER_STAGE + 1) / 2 <= NMMA, "loads are paired with matrix instructions");
+    static_assert(LOADS_PER_STAGE <= 16, "unrolled by hand up to 16 loads");
 
     // ---- accumulators -------------------------------------------------------------------------
     f32x16 acc[TM][TN];
@@ -313,7 +333,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
     int ix_cur[TM * IXW], ix_nxt[TM * IXW];
 
     auto read_frags = [&](int stage, int sub, Frags& f) {
-        const uint8_t* base = smem + stage * L::kStage;
+        const uint8_t* base = ring + stage * L::kStage;
         const uint8_t* bB = base + L::kABytes + L::kMetaBytes;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -340,7 +360,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
     };
     auto read_idx = [&](int stage, int (&ix)[TM * IXW]) {
         if constexpr (SPARSE) {
-            const uint8_t* bM = smem + stage * L::kStage + L::kABytes;
+            const uint8_t* bM = ring + stage * L::kStage + L::kABytes;
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 if constexpr (FP8) {
@@ -358,7 +378,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
     auto read_one = [&](int stage, auto sub_tag, Frags& f, int (&ix)[TM * IXW], auto n_tag) {
         constexpr int SUB = decltype(sub_tag)::value, n = decltype(n_tag)::value;
         constexpr int NI = (SPARSE && SUB == 0) ? TM : 0;     // metadata reads first
-        const uint8_t* base = smem + stage * L::kStage;
+        const uint8_t* base = ring + stage * L::kStage;
         const uint8_t* bB = base + L::kABytes + L::kMetaBytes;
         if constexpr (n < NI) {
             if constexpr (FP8) {
@@ -424,7 +444,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
                    int rstage, Frags& rf, int (&rix)[TM * IXW], auto lo_tag, auto hi_tag, int kt_load, int buf) {
         constexpr int LO = decltype(lo_tag)::value, HI = decltype(hi_tag)::value;
         constexpr bool READ = decltype(read_tag)::value;
-        static_assert(NMMA <= 16 && HI - LO <= NMMA, "unrolled by hand up to 16 matrix instructions");
+        static_assert(NMMA <= 16, "unrolled by hand up to 16 matrix instructions");
+        constexpr int LPM = (HI - LO + NMMA - 1) / NMMA;      // requests behind each matrix instruction (one, but for small wave tiles)
         static_assert(((SPARSE || D64) ? 2 * TM + 2 * TN : TM + TN) <= 2 * NMMA + 2, "two reads per matrix instruction must cover a fragment set");
 #define RTL_MMA_STEP(N)                                                                       \
         mma_one(f, ix, sub_tag, std::integral_constant<int, N>{});                            \
@@ -437,7 +458,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
                     read_one(rstage, rsub_tag, rf, rix, std::integral_constant<int, 2 * N + 3>{}); \
                 }                                                                             \
             }                                                                                 \
-            if constexpr (LO + N < HI) gload_one(kt_load, buf, std::integral_constant<int, LO + N>{}); \
+            if constexpr (LPM >= 1 && LO + N * LPM < HI) gload_one(kt_load, buf, std::integral_constant<int, LO + N * LPM>{}); \
+            if constexpr (LPM >= 2 && LO + N * LPM + 1 < HI) gload_one(kt_load, buf, std::integral_constant<int, LO + N * LPM + 1>{}); \
+            if constexpr (LPM >= 3 && LO + N * LPM + 2 < HI) gload_one(kt_load, buf, std::integral_constant<int, LO + N * LPM + 2>{}); \
+            if constexpr (LPM >= 4 && LO + N * LPM + 3 < HI) gload_one(kt_load, buf, std::integral_constant<int, LO + N * LPM + 3>{}); \
             __builtin_amdgcn_sched_barrier(0);                                                \
         }
         RTL_MMA_STEP(0) RTL_MMA_STEP(1) RTL_MMA_STEP(2) RTL_MMA_STEP(3)
@@ -447,17 +471,27 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
 #undef RTL_MMA_STEP
     };
 
+    // The barrier of a stage. A group of one wave shares its ring with nobody: its own waits are enough.
+    auto stage_barrier = [&]() {
+        if constexpr (NW > 1) __builtin_amdgcn_s_barrier();
+        else asm volatile("" ::: "memory");
+    };
+    constexpr int kMaxLpm = 4;
+    static_assert((LOADS_PER_STAGE + 1) / 2 <= kMaxLpm * NMMA && (STAGES > 2 || LOADS_PER_STAGE <= kMaxLpm * NMMA), "every request has a slot behind a matrix instruction");
+
     // ---- prologue: the whole ring in flight, stage 0 visible ----------------------------------
 #pragma unroll
     for (int s = 0; s < STAGES; ++s)
         if (s < KT) gload(s, s);
     if (KT >= STAGES) wait_vmcnt_lgkm0<(STAGES - 1) * LOADS_PER_STAGE>();
     else wait_vmcnt_lgkm0<0>();
-    __builtin_amdgcn_s_barrier();
+    stage_barrier();
 
     Frags f0, f1;
-    read_frags(0, 0, f0);
-    read_idx(0, ix_cur);
+    if (WAVES_K == 1 || KT > 0) {
+        read_frags(0, 0, f0);
+        read_idx(0, ix_cur);
+    }
     wait_vmcnt_lgkm0<63>();            // fragments of sub-step 0 are in registers
 
     // One stage of the main loop. Schedule inside a stage kt:
@@ -491,7 +525,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
         if constexpr (LOAD_A) mma(f0, ix_cur, s0{}, T{}, s1{}, cur, f1, ix_nxt, cS{}, cL{}, kt + STAGES - 1, prv);
         else mma(f0, ix_cur, s0{}, T{}, s1{}, cur, f1, ix_nxt, c0{}, c0{}, 0, 0);
         wait_vmcnt_lgkm0<PENDING * LOADS_PER_STAGE>();
-        __builtin_amdgcn_s_barrier();
+        stage_barrier();
         // sub-step 1 runs while the first fragments (and metadata) of stage kt+1 are fetched
         if constexpr (LOAD_B) mma(f1, ix_cur, s1{}, std::integral_constant<bool, HAS_NEXT>{}, s0{}, nxt, f0, ix_nxt, c0{}, cS{}, kt + STAGES, cur);
         else mma(f1, ix_cur, s1{}, std::integral_constant<bool, HAS_NEXT>{}, s0{}, nxt, f0, ix_nxt, c0{}, c0{}, 0, 0);
@@ -504,27 +538,158 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
     static_assert(STAGES == 2 || STAGES == 3 || STAGES == 4, "ring depth");
     using P = std::integral_constant<int, STAGES - 2>;
     int kt = 0;
-    if (KT > STAGES) {
-        // stage 0 has no half-requested predecessor; from then on both halves carry requests
-        stage_step(kt, F{}, T{}, T{}, P{});
-        for (kt = 1; kt < KT - STAGES; ++kt) stage_step(kt, T{}, T{}, T{}, P{});
-        // second part of the last stage; nothing new afterwards
-        stage_step(kt, T{}, F{}, T{}, P{});
-        ++kt;
+    if (WAVES_K == 1 || KT > 0) {
+        if (KT > STAGES) {
+            // stage 0 has no half-requested predecessor; from then on both halves carry requests
+            stage_step(kt, F{}, T{}, T{}, P{});
+            for (kt = 1; kt < KT - STAGES; ++kt) stage_step(kt, T{}, T{}, T{}, P{});
+            // second part of the last stage; nothing new afterwards
+            stage_step(kt, T{}, F{}, T{}, P{});
+            ++kt;
+        }
+        // drain (and short K): stages kt+1 .. KT-1 are all requested; fewer remain in flight each step
+        if constexpr (STAGES >= 4) {
+            if (kt == KT - 4) { stage_step(kt, F{}, F{}, T{}, std::integral_constant<int, 2>{}); ++kt; }
+        }
+        if constexpr (STAGES >= 3) {
+            if (kt == KT - 3) { stage_step(kt, F{}, F{}, T{}, std::integral_constant<int, 1>{}); ++kt; }
+        }
+        if (kt == KT - 2) { stage_step(kt, F{}, F{}, T{}, std::integral_constant<int, 0>{}); ++kt; }
+        stage_step(kt, F{}, F{}, F{}, std::integral_constant<int, 0>{});
     }
-    // drain (and short K): stages kt+1 .. KT-1 are all requested; fewer remain in flight each step
-    if constexpr (STAGES >= 4) {
-        if (kt == KT - 4) { stage_step(kt, F{}, F{}, T{}, std::integral_constant<int, 2>{}); ++kt; }
+    if constexpr (WAVES_K > 1 && NW > 1) {
+        if (KT < (blocks + WAVES_K - 1) / WAVES_K) stage_barrier();   // no block in the last stage: the barrier only
     }
-    if constexpr (STAGES >= 3) {
-        if (kt == KT - 3) { stage_step(kt, F{}, F{}, T{}, std::integral_constant<int, 1>{}); ++kt; }
+
+    if constexpr (WAVES_K > 1) {
+        // ---- add the K groups up in LDS, factors, residual, bias, bf16, store --------------------------------
+        wait_vmcnt_lgkm0<0>();
+        __syncthreads();                         // the ring is free
+        float* const planes = reinterpret_cast<float*>(smem);
+        auto put_plane = [&](const f32x16 (&v)[TM][TN]) {    // this wave's block of its group's plane
+            float* p = planes + wk * (L::kPlane / 4);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)             // register r is row 8 (r / 4) + 4 kb + r % 4 of column li
+                        p[(wm * WTM + i * 32 + 8 * (r / 4) + 4 * kb + (r % 4)) * L::kPitch + wn * WTN + j * 32 + li] = v[i][j][r];
+        };
+        constexpr int THREADS = NW * WAVES_K * 64;
+        constexpr int CPR = BN / 8, CHUNKS = BM * CPR;       // a thread finishes runs of 8 columns
+        constexpr int PER = (CHUNKS + THREADS - 1) / THREADS;
+        float sum[PER][8];
+        auto add_planes = [&](float (&out)[8], int row, int c) {
+            const float* p = planes + row * L::kPitch + c * 8;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) out[e] = p[e];
+#pragma unroll
+            for (int g = 1; g < WAVES_K; ++g)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) out[e] += p[g * (L::kPlane / 4) + e];
+        };
+        put_plane(acc);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int q = u * THREADS + (int)threadIdx.x;
+            if (q < CHUNKS) add_planes(sum[u], q / CPR, q % CPR);
+        }
+        float res[MODE == 1 ? PER : 1][8];
+        if constexpr (MODE == 1) {
+            // Residual Y_r = T L_A^T (T = X L_B^T as two bf16 planes hi + lo, rank 64): eight steps of 16 ranks
+            // (four per plane) dealt over the K groups, operands straight from memory (a few KB that sit in L2),
+            // added up through the same planes. The factors belong to the sparse product only.
+            f32x16 t[TM][TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) t[i][j][r] = 0.f;
+            for (int s = wk; s < 8; s += WAVES_K) {
+                const uint16_t* tp = a.T + (s & 1 ? 0 : a.t_plane);      // lo plane first
+                const int col = (s >> 1) * 16 + 8 * kb;
+                Frag8 fa[TM], fb[TN];
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    fa[i].u = *reinterpret_cast<const uint4*>(tp + min(m0 + arow0 + i * 32, a.M - 1) * kLoraRank + col);
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    fb[j].u = *reinterpret_cast<const uint4*>(a.LA + min(n0 + brow0 + j * 32, a.N - 1) * a.ldla + col);
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+                        t[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i].v, fb[j].v, t[i][j], 0, 0, 0);
+            }
+            __syncthreads();                                 // the sparse planes have been read
+            put_plane(t);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int q = u * THREADS + (int)threadIdx.x;
+                if (q < CHUNKS) add_planes(res[u], q / CPR, q % CPR);
+            }
+        }
+        // the runs of a thread share their eight columns
+        static_assert(THREADS % CPR == 0, "a thread keeps its columns");
+        const int64_t col = n0 + ((int)threadIdx.x % CPR) * 8;
+        const int valid = (int)min((int64_t)8, a.N - col);   // columns of the run inside Y
+        if (valid <= 0) return;
+        float bv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bv[e] = 0.f;
+        if (a.bias) {
+            uint16_t b16[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) b16[e] = a.bias[col + min(e, valid - 1)];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) bv[e] = __uint_as_float((uint32_t)b16[e] << 16);
+        }
+        float f[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int64_t row = m0 + (u * THREADS + (int)threadIdx.x) / CPR;
+            f[u] = a.row_scale ? a.row_scale[min(row, a.M - 1)] : 1.0f;
+        }
+        const float ts = a.tensor_scale ? a.tensor_scale[0] : 1.0f;
+        const bool wide_ok = ((reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) && (a.ldy % 8 == 0) && valid == 8;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int q = u * THREADS + (int)threadIdx.x;
+            const int64_t row = m0 + q / CPR;
+            if (q >= CHUNKS || row >= a.M) continue;
+            typedef float f32x2 __attribute__((ext_vector_type(2)));
+            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+            uint32_t out[4];
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                f32x2 y;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float add = bv[e + h];
+                    if constexpr (MODE == 1) add += res[u][e + h];
+                    y[h] = mul_add_rn(sum[u][e + h], f[u] * ts, add);
+                }
+                out[e / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(y, bf16x2));   // RNE
+            }
+            uint16_t* dst = a.Y + row * a.ldy + col;
+            if (wide_ok) {
+                *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2], out[3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (e < valid) dst[e] = (uint16_t)(out[e >> 1] >> (16 * (e & 1)));
+            }
+        }
+        return;
     }
-    if (kt == KT - 2) { stage_step(kt, F{}, F{}, T{}, std::integral_constant<int, 0>{}); ++kt; }
-    stage_step(kt, F{}, F{}, F{}, std::integral_constant<int, 0>{});
 
     const float ts = a.tensor_scale ? a.tensor_scale[0] : 1.0f;
 
-    if constexpr (MODE == 1) {
+    if constexpr (MODE == 1 && WAVES_K == 1) {
         // ---- LoRA tail (Alg. 1: Y <- Y_s + Y_r, accumulated on chip) --------------------------
         // The ROW / TENSOR factors belong to the sparse product only, so they are applied to the
         // accumulators first. Then Y_r = T L_A^T, T = X L_B^T (bf16 [M,64]), is added by four dense
@@ -767,6 +932,38 @@ struct Mixed {
     }
 };
 
+// One tile shape per launch, for problems that leave the chip idle with the 256-row tiles above: few tokens
+// (the text stream, short prompts, small images) or narrow layers. Those are bound by the chain of stages:
+// a compute unit pulls about 95 GB/s of operands that miss its L2 (64 KB in flight over the 0.7 us a stage
+// takes to arrive), whatever its waves do, so a call ends sooner the more units pull and the fewer bytes each
+// of them has to. Small tiles give more units a part, and inside a tile the waves split the contraction
+// (WAVES_K groups, a block each per stage), which keeps all of LDS in flight without more waves per block.
+// Whole calls, [M, N, K], 256-row tiles -> these (us, GROUP scope with bias, graph replay):
+//   sparse  [37, 3072, 12288] 73 -> 22, [256, 512, 512] 11.0 -> 7.3, [512, 3072, 3072] 26.9 -> 18.2,
+//           [512, 3072, 12288] 77 -> 46, [1024, 3072, 3072] 29.8 -> 25.5
+//   dense   [37, 3072, 12288] 129 -> 20, [333, 3072, 12288] 142 -> 52, [1024, 3072, 3072] 42 -> 24
+template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES, int MODE = 0, bool FP8 = false>
+__global__ __launch_bounds__(WAVES_M * WAVES_N * WAVES_K * 64) void gemm_split_kernel(const GemmArgs a) {
+    const int total = (int)(((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN));
+    const int xcd = (int)blockIdx.x % 8, local = (int)blockIdx.x / 8;
+    gemm_tile<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, !SPARSE, WAVES_K>(a, xcd_share_start(total, xcd) + local);
+}
+
+template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES, int MODE = 0, bool FP8 = false>
+struct Split {
+    using L = Smem<SPARSE, BM, BN, STAGES, WAVES_M, WAVES_N, FP8, !SPARSE, WAVES_K>;
+    static hipError_t prepare() {
+        auto kern = gemm_split_kernel<SPARSE, BM, BN, WAVES_M, WAVES_N, WAVES_K, STAGES, MODE, FP8>;
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, L::kTotal);
+    }
+    static hipError_t launch(const GemmArgs& a, hipStream_t stream) {
+        auto kern = gemm_split_kernel<SPARSE, BM, BN, WAVES_M, WAVES_N, WAVES_K, STAGES, MODE, FP8>;
+        const int64_t tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+        hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(WAVES_M * WAVES_N * WAVES_K * 64), L::kTotal, stream, a);
+        return hipGetLastError();
+    }
+};
+
 }  // namespace
 
 size_t gemm_workspace_bytes(bool, int64_t, int64_t, int64_t) { return 0; }
@@ -782,6 +979,7 @@ struct TilePlan {
     bool use_192;
     int64_t m_split;     // rows covered by body tiles (a multiple of 256, or M when there is no tail)
     int body_tiles, tail_tiles;
+    double cost;         // end of the simulated schedule (KB per stage, as c256 etc. in make_plan)
 };
 
 static double simulate_schedule(int64_t nb, int64_t nt, double cb, double ct) {
@@ -809,10 +1007,10 @@ static TilePlan make_plan(int64_t M, int64_t N, bool dense) {
         // very large grids: many rounds, the last one no longer matters; pick the cheaper uniform shape
         // by rounds x bytes per stage and skip the simulation (it is linear in the number of tiles)
         const double r256 = (double)((tm * n256 + 255) / 256) * c256, r192 = (double)((tm * n192 + 255) / 256) * c192;
-        return r192 < r256 ? TilePlan{true, M, (int)(tm * n192), 0} : TilePlan{false, M, (int)(tm * n256), 0};
+        return r192 < r256 ? TilePlan{true, M, (int)(tm * n192), 0, r192} : TilePlan{false, M, (int)(tm * n256), 0, r256};
     }
-    TilePlan best{false, M, (int)(tm * n256), 0};
     double best_cost = simulate_schedule(tm * n256, 0, c256, c128);
+    TilePlan best{false, M, (int)(tm * n256), 0, best_cost};
     auto consider = [&](bool use_192, int64_t p) {
         if (p < 0 || p > tm) return;
         const int64_t nb = p * (use_192 ? n192 : n256), nt = (tm - p) * n128;
@@ -820,7 +1018,7 @@ static TilePlan make_plan(int64_t M, int64_t N, bool dense) {
         if (nt > 0) cost *= 1.03;          // a tail has to pay for itself
         if (cost < best_cost - 1e-9) {
             best_cost = cost;
-            best = TilePlan{use_192, p == tm ? M : p * 256, (int)nb, (int)nt};
+            best = TilePlan{use_192, p == tm ? M : p * 256, (int)nb, (int)nt, cost};
         }
     };
     consider(true, tm);
@@ -855,6 +1053,78 @@ void tile_plan(int64_t M, int64_t N, bool dense, int64_t out[4]) {
     out[3] = p.tail_tiles;
 }
 
+// ---- small tiles -------------------------------------------------------------------------------
+// Shapes of gemm_split_kernel with what one workgroup takes alone on its compute unit: `fixed` us (prologue,
+// reduction of the K groups, epilogue) plus `block` us per k block, both measured ([1..4096, 3072 | 12288,
+// 3072 | 12288], 250 points per operand kind); `resident` workgroups fit a unit's LDS at a time.
+struct SplitShape {
+    int bm, bn, resident;
+    double fixed, block;
+};
+constexpr SplitShape kSparseShapes[] = {
+    {32, 32, 1, 1.2, 0.087}, {64, 32, 1, 1.9, 0.108}, {64, 64, 2, 2.4, 0.153}, {128, 64, 1, 2.3, 0.19}, {128, 128, 2, 2.8, 0.30}};
+constexpr SplitShape kDenseShapes[] = {
+    {32, 32, 1, 1.2, 0.10}, {64, 32, 1, 1.8, 0.135}, {64, 64, 1, 1.0, 0.18}, {128, 64, 1, 2.5, 0.24}, {128, 128, 1, 3.8, 0.36},
+    {256, 128, 1, 4.0, 0.48}};
+
+// Index of the small shape that should serve the problem, or -1 for the 256-row plan. Times are estimated
+// from the measured constants: a small shape needs ceil(tiles / 256) passes over the 256 compute units (two
+// resident workgroups overlap a little: 0.92; dense passes slow each other down: 1.1). The 256-row plan is its simulated schedule times the time per
+// KB of a stage, which grows from 10.7 ns (dense 15.5: both operands row-major) while at most 96 units work
+// to 17.2 (21) when all do and share the L2s and the power budget. Against the best of all variants, measured,
+// the choice was within 3 % at 98 of 110 random shapes ([1..6000, 64..21504, 128..15360]) and within 8 % at all but one.
+static int pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_t blocks, bool dense) {
+    const double busy = (double)(plan.body_tiles + plan.tail_tiles < 256 ? plan.body_tiles + plan.tail_tiles : 256);
+    const double load = busy > 96 ? (busy - 96) / 160 : 0.0;
+    const double per_kb = dense ? 0.0155 + 0.0055 * load : 0.0107 + 0.0065 * load;
+    double best = 3.4 + (double)blocks * plan.cost * per_kb;
+    int pick = -1;
+    const SplitShape* shapes = dense ? kDenseShapes : kSparseShapes;
+    const int count = dense ? (int)(sizeof(kDenseShapes) / sizeof(SplitShape)) : (int)(sizeof(kSparseShapes) / sizeof(SplitShape));
+    for (int i = 0; i < count; ++i) {
+        const SplitShape& s = shapes[i];
+        const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn);
+        if (tiles > 4096) continue;                        // far more than a few passes: never the better one
+        double block = s.block;
+        if (s.bm == 256) {                                 // 256 x 128 with a ring of three: one pass only, slower as the chip fills
+            if (tiles > 256) continue;
+            if (tiles > 96) block += 0.0026 * (double)(tiles - 96);
+        }
+        const int64_t passes = (tiles + 255) / 256;
+        const double several = s.resident > 1 ? 0.92 : (dense ? 1.1 : 1.0);
+        const double t = (double)passes * (s.fixed + (double)blocks * block) * (passes > 1 ? several : 1.0);
+        if (t < best) {
+            best = t;
+            pick = i;
+        }
+    }
+    return pick;
+}
+
+// Runs `op` (launch or prepare) of small shape `i`. Ring depths: as many stages as LDS holds, two workgroups
+// per unit for 64 x 64 and 128 x 128 (sparse).
+template <bool SPARSE, int MODE, bool FP8, class Op>
+static hipError_t with_split(int i, Op op) {
+    if constexpr (SPARSE) {
+        switch (i) {
+            case 0: return op(Split<true, 32, 32, 1, 1, 4, 4, MODE, FP8>{});
+            case 1: return op(Split<true, 64, 32, 1, 1, 4, 4, MODE, FP8>{});
+            case 2: return op(Split<true, 64, 64, 1, 2, 2, 3, MODE, FP8>{});
+            case 3: return op(Split<true, 128, 64, 2, 2, 2, 3, MODE, FP8>{});
+            default: return op(Split<true, 128, 128, 2, 2, 1, 3, MODE, FP8>{});
+        }
+    } else {
+        switch (i) {
+            case 0: return op(Split<false, 32, 32, 1, 1, 4, 4>{});
+            case 1: return op(Split<false, 64, 32, 1, 1, 4, 3>{});
+            case 2: return op(Split<false, 64, 64, 1, 2, 2, 4>{});
+            case 3: return op(Split<false, 128, 64, 2, 2, 2, 3>{});
+            case 4: return op(Split<false, 128, 128, 2, 2, 1, 3>{});
+            default: return op(Split<false, 256, 128, 2, 4, 1, 3>{});
+        }
+    }
+}
+
 // Every configuration launch_gemm can pick.
 hipError_t prepare_gemm_kernels() {
     hipError_t e = hipSuccess;
@@ -869,6 +1139,14 @@ hipError_t prepare_gemm_kernels() {
     run(Mixed<true, 256, 2, 4, 3>::prepare());
     run(Mixed<false, 192, 4, 2, 2, 0, false, true>::prepare());
     run(Mixed<false, 256, 2, 4, 2, 0, false, true>::prepare());
+    auto prep = [](auto k) { return decltype(k)::prepare(); };
+    for (int i = 0; i < 5; ++i) {
+        run(with_split<true, 0, false>(i, prep));
+        run(with_split<true, 1, false>(i, prep));
+        run(with_split<true, 0, true>(i, prep));
+        run(with_split<true, 1, true>(i, prep));
+    }
+    for (int i = 0; i < 6; ++i) run(with_split<false, 0, false>(i, prep));
     return e;
 }
 
@@ -880,6 +1158,13 @@ hipError_t launch_gemm(bool sparse, const GemmArgs& a_in, hipStream_t stream) {
     a.tail_tiles = plan.tail_tiles;
     a.rows_pad = kmajor_rows(a.M);
     a.t_plane = a.M * kLoraRank;
+    const int split = pick_split(plan, a.M, a.N, a.K / (a.fp8 ? 128 : 64), !sparse);
+    if (split >= 0) {
+        auto go = [&](auto k) { return decltype(k)::launch(a, stream); };
+        if (!sparse) return with_split<false, 0, false>(split, go);
+        if (a.fp8) return a.T ? with_split<true, 1, true>(split, go) : with_split<true, 0, true>(split, go);
+        return a.T ? with_split<true, 1, false>(split, go) : with_split<true, 0, false>(split, go);
+    }
     if (sparse && a.fp8) {
         if (a.T != nullptr) {          // LoRA tail in bf16 on top of the FP8 product
             if (plan.use_192) return Mixed<true, 192, 4, 2, 3, 1, true>::launch(a, stream);

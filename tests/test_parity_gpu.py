@@ -1086,3 +1086,50 @@ def test_randomized_linear_cases():
                                                    bias=bb, scope=comp)
         y8l = y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=bias, comp=comp))
         assert rel_max_err(y8l, r8l["Y"]) <= Y_TOL
+
+
+# One output per tile shape of the small-tile loop (32x32, 64x32, 64x64, 128x64, 128x128, dense 256x128 as the sizes
+# grow), ragged in M and N, with block counts that are short of, equal to and not a multiple of the K groups.
+@pytest.mark.parametrize("M,N,K", [(1, 1, 64), (31, 33, 128), (33, 31, 192), (37, 1000, 4672), (65, 3071, 1088), (97, 3072, 3136),
+                                   (129, 1553, 832), (201, 3009, 1344), (393, 3041, 1600), (700, 3000, 704), (777, 3072, 3072),
+                                   (1301, 3065, 576)])
+@pytest.mark.parametrize("comp", [rtl.COMP_GROUP, rtl.COMP_ROW])
+def test_small_tiles_sparse_dense_and_lora(M, N, K, comp):
+    """Sampled rows against the oracle, guard bytes around Y, and every form that shares the tile loop: sparse,
+    dense, LoRA (a zero L_A must reproduce the plain call bit for bit), packed (bit for bit)."""
+    X = synth.activations("laplace_outlier", M, K, seed=M + N, device=DEV)
+    W = synth.weights(N, K, seed=K + 1, device=DEV, std=0.5)
+    b = synth.bias(N, seed=4, device=DEV, std=1.0)
+    LA, LB = synth.lora(N, K, 64, seed=5, device=DEV, std_a=0.3, std_b=0.3)
+    rows = sampled_rows(M, min(M, 12), seed=6)
+    sel = torch.from_numpy(rows).to(DEV)
+    Xs, Wb, bb = synth.bits(X[sel]), synth.bits(W), synth.bits(b)
+    Y, guard_ok = guarded((M, N), torch.bfloat16, 7.0)
+    rtl.sparse_linear(X, W, bias=b, comp=comp, out=Y)
+    check_y(Y[sel], oracle.sparse_linear_oracle(Xs, Wb, bias=bb, scope=comp)["Y"])
+    guard_ok()
+    vals, meta, scale = rtl.sparsify_pack(X, comp=comp)
+    assert torch.equal(rtl.packed_linear(vals, meta, W, bias=b, row_scale=scale), Y)
+    assert torch.equal(rtl.sparse_lora_linear(X, W, torch.zeros_like(LA), LB, bias=b, comp=rtl.COMP_GROUP),
+                       rtl.sparse_linear(X, W, bias=b, comp=rtl.COMP_GROUP))
+    ref = oracle.sparse_lora_linear_oracle(Xs, Wb, synth.bits(LA), synth.bits(LB), bias=bb, scope=comp)["Y"]
+    check_y(rtl.sparse_lora_linear(X, W, LA, LB, bias=b, comp=comp)[sel], ref)
+    check_y(rtl.dense_linear(X, W, bias=b)[sel], oracle.dense_linear_oracle(Xs, Wb, bias=bb))
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 128), (33, 31, 384), (37, 1000, 4736), (97, 3072, 3200), (201, 3009, 1408),
+                                   (393, 3041, 1664), (700, 3000, 640)])
+def test_small_tiles_fp8(M, N, K):
+    X = synth.activations("laplace", M, K, seed=M + N, device=DEV)
+    W = synth.weights(N, K, seed=K, device=DEV)
+    xs, Wq = fp8_scale(X), rtl.quantize_fp8(W)
+    LA, LB = synth.lora(N, K, 64, seed=5, device=DEV, std_a=0.05, std_b=0.05)
+    rows = sampled_rows(M, min(M, 8), seed=6)
+    sel = torch.from_numpy(rows).to(DEV)
+    for comp in (rtl.COMP_GROUP, rtl.COMP_ROW):
+        r = oracle.sparse_linear_fp8_oracle(synth.bits(X[sel]), Wq.cpu().numpy(), float(xs.item()), scope=comp)
+        f = np.float32(xs.item()) * (r["s"][:, None] if comp == rtl.COMP_ROW else np.float32(1.0))
+        check_y_fp8(rtl.sparse_linear_fp8(X, Wq, xs, comp=comp)[sel], r, Wq.cpu().numpy(), f)
+        rl = oracle.sparse_lora_linear_fp8_oracle(synth.bits(X[sel]), Wq.cpu().numpy(), float(xs.item()), synth.bits(LA),
+                                                  synth.bits(LB), scope=comp)
+        assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, comp=comp)[sel]), rl["Y"]) <= Y_TOL
