@@ -4,7 +4,7 @@
 // kept values + 2-bit positions (App. A operand format). One sweep over X; HBM-bandwidth bound:
 // 2 bytes read + 1.125 bytes written per input element.
 //
-// Mapping: one wavefront per row (two for long rows, each taking a run of whole steps); a lane
+// Mapping: one wavefront per row (several for long rows, each taking a run of whole steps); a lane
 // takes 8 consecutive bf16 (one 16-byte load = two groups) per step and the wave walks the row in
 // steps of 512 elements, so every load, the
 // 8-byte value stores and the 4-byte metadata stores (four lanes' bytes gathered with DPP
@@ -43,14 +43,17 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void sparsify_pack_kernel(
     uint8_t* __restrict__ meta_km, int64_t Mpad, float* __restrict__ scale,
     float* __restrict__ rowsums, const float* __restrict__ x_scale, int parts) {
     const int lane = threadIdx.x & 63;
-    // `parts` waves share a row (NONE / GROUP only: nothing is summed along the row), each taking a
-    // run of whole 512-element steps; short rows then still give every SIMD enough waves in flight.
+    // `parts` waves share a row, each taking a run of whole 512-element steps: few rows then still give
+    // every SIMD enough waves in flight. ROW / TENSOR add the waves' sums up in LDS, so there the waves of a
+    // row sit in one workgroup (parts divides kWavesPerBlock).
+    constexpr bool SUMS = COMP == RTL_COMP_ROW || COMP == RTL_COMP_TENSOR;
     const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     const int64_t row = gw / parts;
-    if (row >= M) return;  // whole wave leaves together
+    const int part = (int)(gw % parts);
+    if (row >= M && (!SUMS || parts == 1)) return;   // whole wave leaves together (it has no barrier to meet)
     const int span = ((K + parts - 1) / parts + 511) / 512 * 512;
-    const int kbeg = (int)(gw % parts) * span;
-    const int kend = min(K, kbeg + span);
+    const int kbeg = part * span;
+    const int kend = row < M ? min(K, kbeg + span) : 0;
     const uint16_t* xr = X + row * ldx;
     // canonical value row (only dereferenced when vals != null): bf16 form / FP8 form
     uint16_t* vr = static_cast<uint16_t*>(vals) + row * (int64_t)(K / 2);
@@ -117,9 +120,23 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void sparsify_pack_kernel(
             }
         }
     }
-    if constexpr (COMP == RTL_COMP_ROW || COMP == RTL_COMP_TENSOR) {
+    if constexpr (SUMS) {
         num = wave_sum(num);
         den = wave_sum(den);
+        if (parts > 1) {
+            __shared__ float part_num[kWavesPerBlock], part_den[kWavesPerBlock];
+            const int wave = threadIdx.x >> 6;
+            if (lane == 0) {
+                part_num[wave] = num;
+                part_den[wave] = den;
+            }
+            __syncthreads();
+            if (part != 0 || row >= M) return;
+            for (int i = 1; i < parts; ++i) {        // in the order of the row
+                num += part_num[wave + i];
+                den += part_den[wave + i];
+            }
+        }
         if (lane == 0) {
             if constexpr (COMP == RTL_COMP_ROW) {
                 scale[row] = sqrtf(num / (den + eps));
@@ -314,11 +331,21 @@ static hipError_t launch_pack_any(const uint16_t* X, int64_t M, int64_t K, int64
             }
         }
     }
-    // Waves per row: two once each still has a full unrolled trip of work (measured: 34 -> 31 us at
-    // [4096,12288], 141 -> 131 us at [16896,12288], no change at K = 3072; four or more waves per row
-    // lose on the short rows). ROW / TENSOR sum along the row inside one wave.
-    int parts = 1;
-    if ((comp == RTL_COMP_NONE || comp == RTL_COMP_GROUP) && K >= 2 * 512 * kUnroll) parts = 2;
+    // Waves per row: one per unrolled trip of work (1536 elements) while the rows alone do not fill the chip,
+    // fewer once they do. Measured [M, 12288], us with 1 / 2 / 4 / 8 waves per row: FP8 GROUP M = 37 18.9 / 10.7 /
+    // 6.5 / 4.4, 512 19.6 / 11.3 / 7.3 / 6.5, 1029 21.2 / 16.4 / 12.8 / 11.1, 2048 22.4 / 19.0 / 17.1 / 18.1,
+    // 4608 41.9 / 34.5 / 31.7 / 32.1, 9728 67 / 64 / 62 / 64. ROW and TENSOR pay for the sum over the waves:
+    // ROW M = 37 12.7 / 7.9 / 5.4 / 4.5, 512 14.2 / 8.7 / 6.6 / 7.0, 2048 17.0 / 16.2 / 18.5 / 19.1. At K = 3072 two waves
+    // win or tie for GROUP (4608: 13.0 -> 11.6) and lose for ROW from M = 1500 on (5.8 -> 5.9, 9728 17.9 -> 19.3).
+    int parts = (int)(K / (512 * kUnroll));
+    if (comp == RTL_COMP_NONE || comp == RTL_COMP_GROUP) {
+        const int most = M <= 1024 ? 8 : 4;
+        parts = parts < 1 ? 1 : (parts > most ? most : parts);
+    } else {
+        const int most = M <= 256 ? 8 : (M <= 1536 ? 4 : (K >= 4 * 512 * kUnroll ? 2 : 1));
+        parts = parts >= 8 ? 8 : (parts >= 4 ? 4 : (parts >= 2 ? 2 : 1));     // divides kWavesPerBlock
+        parts = parts > most ? most : parts;
+    }
     const dim3 grid((unsigned)((M * parts + kWavesPerBlock - 1) / kWavesPerBlock));
     const dim3 block(kWavesPerBlock * 64);
     switch (comp) {

@@ -1133,3 +1133,13 @@ def test_small_tiles_fp8(M, N, K):
         rl = oracle.sparse_lora_linear_fp8_oracle(synth.bits(X[sel]), Wq.cpu().numpy(), float(xs.item()), synth.bits(LA),
                                                   synth.bits(LB), scope=comp)
         assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, comp=comp)[sel]), rl["Y"]) <= Y_TOL
+
+
+@pytest.mark.parametrize("M,K", [(3, 12296), (257, 12288), (259, 6152), (1031, 3080), (1025, 15360), (1537, 6144), (2049, 4616)])
+@pytest.mark.parametrize("comp", COMPS)
+def test_pack_several_waves_per_row(M, K, comp):
+    """Row counts on both sides of the limits of the waves-per-row rule and K that leaves the last wave of a
+    row a short or empty run; a workgroup's last row group lies past M for odd M."""
+    X = synth.activations("laplace_outlier", M, K, seed=M + K, device=DEV)
+    check_pack(X, comp)
+    check_pack_fp8(X, comp, fp8_scale(X))
