@@ -269,7 +269,7 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
         return RTL_ERR_ALIGN;
     const SparseWs ws = sparse_ws(M, N, K, comp);
     const size_t t_off = ws.total, p_off = t_off + round_up((size_t)M * rtl::kLoraRank * 4, 256);
-    const size_t need = p_off + round_up(rtl::pack_down_scratch_bytes(M, K), 256);
+    const size_t need = p_off + round_up(rtl::pack_down_scratch_min(M, K), 256);   // the query asks for the preferred size
     if (!workspace || workspace_bytes < need) return RTL_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return RTL_ERR_ALIGN;
     RTL_REQUIRE_DEVICE();
@@ -280,7 +280,7 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
     // one pass over X: the sweep that compresses the activation also forms T = X L_B^T
     hipError_t e = rtl::launch_pack_down(static_cast<const uint16_t*>(X), M, K, ldx, comp, eps,
                                          static_cast<const uint16_t*>(LB), ldlb, base + ws.vals, base + ws.meta,
-                                         reinterpret_cast<float*>(base + p_off), T, scale,
+                                         reinterpret_cast<float*>(base + p_off), workspace_bytes - p_off, T, scale,
                                          reinterpret_cast<float*>(base + ws.pack), s);
     if (e != hipSuccess) return RTL_ERR_HIP;
     rtl::GemmArgs g{};
@@ -403,7 +403,7 @@ rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float
         return RTL_ERR_ALIGN;
     const SparseWs ws = sparse_ws(M, N, K, comp, 1);
     const size_t t_off = ws.total, p_off = t_off + round_up((size_t)M * rtl::kLoraRank * 4, 256);
-    const size_t need = p_off + round_up(rtl::pack_down_scratch_bytes(M, K), 256);
+    const size_t need = p_off + round_up(rtl::pack_down_scratch_min(M, K), 256);   // the query asks for the preferred size
     if (!workspace || workspace_bytes < need) return RTL_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return RTL_ERR_ALIGN;
     RTL_REQUIRE_DEVICE();
@@ -414,7 +414,7 @@ rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = rtl::launch_pack_down(static_cast<const uint16_t*>(X), M, K, ldx, comp, eps,
                                          static_cast<const uint16_t*>(LB), ldlb, base + ws.vals, base + ws.meta,
-                                         reinterpret_cast<float*>(base + p_off), T, scale,
+                                         reinterpret_cast<float*>(base + p_off), workspace_bytes - p_off, T, scale,
                                          reinterpret_cast<float*>(base + ws.pack), s, x_scale, fused);
     if (e != hipSuccess) return RTL_ERR_HIP;
     rtl::GemmArgs g{};

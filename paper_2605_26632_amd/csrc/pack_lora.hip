@@ -188,39 +188,83 @@ __global__ __launch_bounds__(256) void pack_down_kernel(const uint16_t* __restri
     }
 }
 
-// Ordered sum of the partial planes, T stored as two bf16 planes [2][M][64]: hi = bf16(T), lo =
-// bf16(T - hi) (the matrix unit takes bf16 operands; the pair keeps 16 significant bits). ROW / TENSOR:
-// the first M threads also add the row sums of the K ranges in order and emit the row's factor
-// s = sqrt(|X|^2 / (|X~|^2 + eps)) (ROW) or the row's two sums for the tensor-wide factor (TENSOR).
-__global__ __launch_bounds__(256) void lora_reduce_kernel(const float* __restrict__ partials, int splits, int64_t M,
-                                                          uint16_t* __restrict__ T, const float* __restrict__ sums,
-                                                          int comp, float eps, float* __restrict__ scale,
-                                                          float* __restrict__ rowsums) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= M * kLoraRank) return;
-    float acc = 0.f;
-    for (int sp0 = 0; sp0 < splits; sp0 += 8) {          // the loads of up to eight ranges in flight together
-        float p[8];
+// Fixed-order sum of the partial planes, T stored as two bf16 planes [2][M][64]: hi = bf16(T), lo =
+// bf16(T - hi) (the matrix unit takes bf16 operands; the pair keeps 16 significant bits). A workgroup of
+// kReduceWaves waves finishes four rows: a lane takes four consecutive ranks (16 bytes), wave w the planes w,
+// w + kReduceWaves, ..., all of a wave's loads in flight together, and the waves' sums are added in LDS in
+// order of w. It is bound by latency: one trip over the planes. ROW / TENSOR: wave 0 also adds the row sums of
+// the K ranges in order (16 lanes per row hold them) and emits the row's factor s = sqrt(|X|^2 / (|X~|^2 + eps)) (ROW) or the
+// row's two sums for the tensor-wide factor (TENSOR).
+constexpr int kReduceWaves = 4;
+constexpr int kMaxRanges = 64;
+__global__ __launch_bounds__(kReduceWaves * 64) void lora_reduce_kernel(
+    const float* __restrict__ partials, int splits, int64_t M, uint16_t* __restrict__ T, const float* __restrict__ sums,
+    int comp, float eps, float* __restrict__ scale, float* __restrict__ rowsums) {
+    __shared__ float4 part[kReduceWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t row = (int64_t)blockIdx.x * 4 + (lane >> 4);
+    const int64_t e = min(row, M - 1) * kLoraRank + (lane & 15) * 4;
+    const bool with_sums = comp == RTL_COMP_ROW || comp == RTL_COMP_TENSOR;
+    float2 range_sums[kMaxRanges / 16];
+    if (with_sums && wave == 0) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) p[u] = sp0 + u < splits ? partials[(int64_t)(sp0 + u) * M * kLoraRank + e] : 0.f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (sp0 + u < splits) acc += p[u];
-    }
-    const uint32_t hi = f32_to_bf16_rne(acc);
-    T[e] = (uint16_t)hi;
-    T[M * kLoraRank + e] = (uint16_t)f32_to_bf16_rne(acc - __uint_as_float(hi << 16));
-    if ((comp == RTL_COMP_ROW || comp == RTL_COMP_TENSOR) && e < M) {
-        float n = 0.f, d = 0.f;
-        for (int sp = 0; sp < splits; ++sp) {
-            n += sums[((int64_t)sp * M + e) * 2];
-            d += sums[((int64_t)sp * M + e) * 2 + 1];
+        for (int j = 0; j < kMaxRanges / 16; ++j) {
+            const int sp = 16 * j + (lane & 15);
+            range_sums[j] = make_float2(0.f, 0.f);
+            if (sp < splits) range_sums[j] = *reinterpret_cast<const float2*>(sums + ((int64_t)sp * M + min(row, M - 1)) * 2);
         }
-        if (comp == RTL_COMP_ROW) {
-            scale[e] = sqrtf(n / (d + eps));
-        } else {
-            rowsums[2 * e] = n;
-            rowsums[2 * e + 1] = d;
+    }
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int sp0 = wave; sp0 < splits; sp0 += 8 * kReduceWaves) {     // up to eight planes in flight
+        float4 p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int sp = sp0 + u * kReduceWaves;
+            p[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (sp < splits) p[u] = *reinterpret_cast<const float4*>(partials + (int64_t)sp * M * kLoraRank + e);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            acc.x += p[u].x; acc.y += p[u].y; acc.z += p[u].z; acc.w += p[u].w;
+        }
+    }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int w = 1; w < kReduceWaves; ++w) {
+        const float4 p = part[w][lane];
+        acc.x += p.x; acc.y += p.y; acc.z += p.z; acc.w += p.w;
+    }
+    const float v[4] = {acc.x, acc.y, acc.z, acc.w};
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        hi[i] = f32_to_bf16_rne(v[i]);
+        lo[i] = f32_to_bf16_rne(v[i] - __uint_as_float(hi[i] << 16));
+    }
+    if (row < M) {
+        *reinterpret_cast<uint2*>(T + e) = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
+        *reinterpret_cast<uint2*>(T + M * kLoraRank + e) = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+    }
+    if (with_sums) {
+        float n = 0.f, d = 0.f;
+#pragma unroll
+        for (int j = 0; j < kMaxRanges / 16; ++j)
+            if (16 * j < splits) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {           // in range order (absent ranges hold zeros)
+                    n += __shfl(range_sums[j].x, (lane & 48) + i, 64);
+                    d += __shfl(range_sums[j].y, (lane & 48) + i, 64);
+                }
+            }
+        if ((lane & 15) == 0 && row < M) {
+            if (comp == RTL_COMP_ROW) {
+                scale[row] = sqrtf(n / (d + eps));
+            } else {
+                rowsums[2 * row] = n;
+                rowsums[2 * row + 1] = d;
+            }
         }
     }
 }
@@ -243,31 +287,43 @@ hipError_t prepare_pack_lora_kernels() {
     return e;
 }
 
-// K ranges of the fused sweep: enough workgroups (128 rows each) to give every compute unit two, at
-// least 8 ranges (workgroups that walk different parts of K touch different memory channels at any
-// moment), at most 16 (partial-plane traffic), every range at least one 64-k block.
-static int pack_down_ranges(int64_t M, int64_t K, int* per_out) {
+// K ranges of the fused sweep, every range at least one 64-k block. Many rows: enough workgroups (128 rows
+// each) to give every compute unit two, at least 8 ranges (workgroups that walk different parts of K touch
+// different memory channels at any moment), at most 16 (partial-plane traffic). Few rows (up to 2048): one
+// workgroup per compute unit, up to 64 ranges: a stage takes about 0.9 us whatever else runs, so the walk of a
+// range is what the sweep takes, and the planes are small. Sweep + reduction + rest of a narrow call [M, 12288],
+// 16 ranges -> these: M = 37 37.3 -> 26.1 us, 512 40.2 -> 30.9, 1029 41.9 -> 37; more workgroups than compute units
+// lose again (M = 1029 with 32 ranges 39.9). `room`: most ranges the scratch holds (>= 8 and <= 16 always fit,
+// see pack_down_scratch_min).
+static int pack_down_ranges(int64_t M, int64_t K, int* per_out, int room) {
     const int64_t tiles = (M + kRows - 1) / kRows;
     const int KT = (int)(K / 64);
     int want = (int)((512 + tiles - 1) / tiles);
     want = want < 8 ? 8 : (want > 16 ? 16 : want);
+    if (tiles <= 16) {
+        const int spread = (int)(256 / tiles);
+        want = spread > kMaxRanges ? kMaxRanges : spread;
+    }
+    if (want > room) want = room;
     if (want > KT) want = KT;
     const int per = (KT + want - 1) / want;
     if (per_out) *per_out = per;
     return (KT + per - 1) / per;
 }
-int pack_down_splits(int64_t M, int64_t K) { return pack_down_ranges(M, K, nullptr); }
 
-size_t pack_down_scratch_bytes(int64_t M, int64_t K) {     // partial planes, then the row sums of the K ranges
-    return (size_t)pack_down_splits(M, K) * (size_t)M * (kLoraRank + 2) * sizeof(float);
+static size_t pack_down_bytes(int64_t M, int splits) {     // partial planes, then the row sums of the K ranges
+    return (size_t)splits * (size_t)M * (kLoraRank + 2) * sizeof(float);
 }
+size_t pack_down_scratch_bytes(int64_t M, int64_t K) { return pack_down_bytes(M, pack_down_ranges(M, K, nullptr, kMaxRanges)); }
+size_t pack_down_scratch_min(int64_t M, int64_t K) { return pack_down_bytes(M, pack_down_ranges(M, K, nullptr, 16)); }
 
 hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps,
                             const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, float* scratch,
-                            uint16_t* T, float* scale, float* rowsums, hipStream_t stream, const float* x_scale,
+                            size_t scratch_bytes, uint16_t* T, float* scale, float* rowsums, hipStream_t stream, const float* x_scale,
                             float* fused_scale) {
     int per = 1;
-    const int splits = pack_down_ranges(M, K, &per);
+    const size_t fit = scratch_bytes / pack_down_bytes(M, 1);
+    const int splits = pack_down_ranges(M, K, &per, fit > kMaxRanges ? kMaxRanges : (int)fit);
     const dim3 grid((unsigned)((M + kRows - 1) / kRows), (unsigned)splits);
     const int64_t Mpad = kmajor_rows(M);
     float* partials = scratch;
@@ -291,9 +347,8 @@ hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx
 #undef RTL_PACK_DOWN
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t n = M * kLoraRank;
-    hipLaunchKernelGGL(lora_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, partials, splits,
-                       M, T, sums, (int)comp, eps, scale, rowsums);
+    hipLaunchKernelGGL(lora_reduce_kernel, dim3((unsigned)((M + 3) / 4)), dim3(kReduceWaves * 64), 0, stream, partials,
+                       splits, M, T, sums, (int)comp, eps, scale, rowsums);
     e = hipGetLastError();
     if (e != hipSuccess || comp != RTL_COMP_TENSOR) return e;
     return launch_tensor_scale(rowsums, M, eps, scale, stream, x_scale, fused_scale);

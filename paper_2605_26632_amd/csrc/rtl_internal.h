@@ -88,14 +88,16 @@ constexpr int kLoraRank = 64;
 
 // One pass over X for the LoRA branch (pack_lora.hip): the sweep writes the k-major compressed operand (as
 // launch_sparsify_pack does) and, per K range, an fp32 partial plane of T = X L_B^T and (ROW / TENSOR) the
-// row sums of squares, into `scratch` (pack_down_scratch_bytes(M, K) bytes); a second small kernel adds the
-// ranges up in order into the two bf16 planes of T ([2][M][64]: hi, lo), the ROW factors `scale` [M] or
+// row sums of squares, into `scratch` (scratch_bytes >= pack_down_scratch_min(M, K); the number of ranges is
+// the preferred one with pack_down_scratch_bytes(M, K)); a second small kernel adds the ranges up in a fixed
+// order into the two bf16 planes of T ([2][M][64]: hi, lo), the ROW factors `scale` [M] or
 // the TENSOR row sums `rowsums` [M][2], from which launch_tensor_scale then forms scale[0].
 size_t pack_down_scratch_bytes(int64_t M, int64_t K);
+size_t pack_down_scratch_min(int64_t M, int64_t K);
 hipError_t prepare_pack_lora_kernels();
 hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps,
                             const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, float* scratch,
-                            uint16_t* T, float* scale, float* rowsums, hipStream_t stream,
+                            size_t scratch_bytes, uint16_t* T, float* scale, float* rowsums, hipStream_t stream,
                             const float* x_scale = nullptr, float* fused_scale = nullptr);
 // (x_scale set: FP8 form: kept values as E4M3 codes of (s x) / x_scale[0] in the FP8 k-major layout, K % 128 == 0;
 //  fused_scale [1] then receives x_scale[0] times the TENSOR factor, TENSOR scope only.)

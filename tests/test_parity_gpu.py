@@ -1143,3 +1143,28 @@ def test_pack_several_waves_per_row(M, K, comp):
     X = synth.activations("laplace_outlier", M, K, seed=M + K, device=DEV)
     check_pack(X, comp)
     check_pack_fp8(X, comp, fp8_scale(X))
+
+
+@pytest.mark.parametrize("M,K", [(1, 64), (130, 4160), (513, 12288), (1029, 3072), (2049, 1088)])
+@pytest.mark.parametrize("comp", [rtl.COMP_ROW, rtl.COMP_TENSOR])
+def test_lora_sweep_ranges_and_smaller_workspace(M, K, comp):
+    """One to 64 K ranges (block counts that do not divide over them), sums over the ranges, and the smallest
+    workspace the call accepts: 16 ranges at most, same result up to the grouping of the fp32 sums over K."""
+    N = 40
+    X = synth.activations("laplace_outlier", M, K, seed=M, device=DEV)
+    W = synth.weights(N, K, seed=K, device=DEV)
+    LA, LB = synth.lora(N, K, 64, seed=5, device=DEV, std_a=0.1, std_b=0.1)
+    rows = sampled_rows(M, min(M, 12), seed=6) if comp == rtl.COMP_ROW else np.arange(M)
+    ref = oracle.sparse_lora_linear_oracle(synth.bits(X[torch.from_numpy(rows).to(DEV)]), synth.bits(W), synth.bits(LA),
+                                           synth.bits(LB), scope=comp)["Y"]
+    n = rtl.sparse_lora_linear_workspace(M, N, K, 64, comp)
+    Y = rtl.sparse_lora_linear(X, W, LA, LB, comp=comp)
+    check_y(Y[torch.from_numpy(rows).to(DEV)], ref)
+    for cut in range(0, n, 1 << 18):                 # shrink until refused: every accepted size must give the same Y
+        ws = torch.full((max(n - cut, 256),), 0x5A, dtype=torch.uint8, device=DEV)
+        try:
+            Yc = rtl.sparse_lora_linear(X, W, LA, LB, comp=comp, ws=ws)
+        except rtl.RtlError as e:
+            assert e.status == 4
+            break
+        check_y(Yc[torch.from_numpy(rows).to(DEV)], ref)
