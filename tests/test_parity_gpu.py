@@ -1168,3 +1168,38 @@ def test_lora_sweep_ranges_and_smaller_workspace(M, K, comp):
             assert e.status == 4
             break
         check_y(Yc[torch.from_numpy(rows).to(DEV)], ref)
+
+
+def test_pack_every_order_and_tie_of_a_group():
+    """All 6^4 groups over six magnitudes (zero, a denormal, equal neighbours, the largest finite value, infinity),
+    signs alternating differently per row: positions and kept values bit for bit."""
+    mags = np.array([0x0000, 0x0001, 0x3F80, 0x3F81, 0x7F7F, 0x7F80], dtype=np.uint16)
+    g = np.stack(np.meshgrid(*[np.arange(6)] * 4, indexing="ij"), axis=-1).reshape(-1, 4)
+    rows = []
+    for s in range(16):
+        signs = np.array([(s >> i) & 1 for i in range(4)], dtype=np.uint16) << 15
+        rows.append((mags[g] | signs).reshape(-1))
+    X = synth.from_bits(np.stack(rows), DEV)
+    for comp in (rtl.COMP_NONE, rtl.COMP_ROW):
+        vals, meta, _ = rtl.sparsify_pack(X, comp=comp)
+        ref = oracle.sparsify_pack_oracle(synth.bits(X), scope=comp)
+        assert np.array_equal(meta.cpu().numpy(), ref["meta"]) and np.array_equal(synth.bits(vals), ref["vals"])
+    vals, meta, _ = rtl.sparsify_pack(X, comp=rtl.COMP_GROUP)
+    ref = oracle.sparsify_pack_oracle(synth.bits(X), scope=oracle.GROUP)
+    assert np.array_equal(meta.cpu().numpy(), ref["meta"])
+    assert np.array_equal(canon_nan(synth.bits(vals)), canon_nan(ref["vals"]))
+
+
+@pytest.mark.parametrize("spread", [0, 2, 8, 24])
+def test_pack_group_factor_over_exponent_spreads(spread):
+    """Four million groups whose magnitudes differ by up to 2^spread: the fast factor (dot products, hardware
+    reciprocal and root) must round like the exact one everywhere, in bf16 and in FP8, with and without an eps
+    of the size of the squares."""
+    rng = np.random.default_rng(spread)
+    shape = (1024, 16384)
+    e = rng.integers(127 - spread // 2 - 1, 127 + spread // 2 + 1, size=shape)
+    bits = ((rng.integers(0, 2, size=shape) << 15) | (e << 7) | rng.integers(0, 128, size=shape)).astype(np.uint16)
+    X = synth.from_bits(bits, DEV)
+    for eps in (1e-8, 0.7):
+        check_pack(X, rtl.COMP_GROUP, eps=eps)
+    check_pack_fp8(X, rtl.COMP_GROUP, fp8_scale(X))
