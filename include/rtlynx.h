@@ -27,6 +27,10 @@
  *      RTL_ERR_ARCH       the current device is not a gfx950 GPU (checked once per device, after
  *                         the argument checks and before anything is launched)
  *  - M == 0 or N == 0 is RTL_OK with no launch.
+ *  - The *_workspace queries of the linears include room that lets a call spread a long contraction over more
+ *    compute units (fp32 partial sums; few rows only). That part is optional: a smaller workspace is accepted as long
+ *    as it holds the rest (RTL_ERR_WORKSPACE otherwise), the call is then slower and its fp32 sums are grouped
+ *    differently. A given call on a given workspace size is deterministic.
  *  - Arithmetic: bf16 operands, fp32 accumulation, fp32 -> bf16 round-to-nearest-even on store.
  */
 #ifndef RTLYNX_H
@@ -183,7 +187,8 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
  * rtl_dense_linear - Eq. (linear_layer), Y = X W^T (+ b), on the dense matrix instructions.
  * The denominator of every speedup the paper reports ("GEMM" column of its kernel tables).
  * Same layouts and alignment rules as rtl_sparse_linear; K % 64 == 0.
- *   workspace  rtl_dense_linear_workspace(M, N, K) bytes, 256-byte aligned (may be 0).
+ *   workspace  rtl_dense_linear_workspace(M, N, K) bytes, 256-byte aligned (may be 0). All of it is optional: NULL is
+ *   accepted too.
  * ------------------------------------------------------------------------------------------- */
 size_t rtl_dense_linear_workspace(int64_t M, int64_t N, int64_t K);
 rtl_status rtl_dense_linear(const void* X, const void* W, const void* bias, void* Y,

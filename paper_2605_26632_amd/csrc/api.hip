@@ -62,21 +62,36 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline bool comp_ok(rtl_comp c) { return c >= RTL_COMP_NONE && c <= RTL_COMP_TENSOR; }
 inline bool eps_ok(float e) { return std::isfinite(e) && e >= 0.0f; }
 
-// Layout of the rtl_sparse_linear workspace:
-// [vals | k-major meta | scale | pack scratch | gemm scratch]
+// Layout of the rtl_sparse_linear workspace: [vals | k-major meta | scale | pack scratch], and behind it, as in every
+// linear's workspace, the optional partial planes of the tile loop. The queries ask for the planes too; a
+// workspace without room for them is accepted and the contraction then stays in one workgroup per tile.
 struct SparseWs {
-    size_t vals, meta, scale, pack, gemm, total;
+    size_t vals, meta, scale, pack, total;
 };
-SparseWs sparse_ws(int64_t M, int64_t N, int64_t K, rtl_comp comp, size_t val_bytes = 2) {
+SparseWs sparse_ws(int64_t M, int64_t K, rtl_comp comp, size_t val_bytes = 2) {
     SparseWs w{};
     size_t off = 0;
     w.vals = off; off += round_up(rtl::kmajor_val_bytes(M, K, val_bytes), 256);
     w.meta = off; off += round_up(rtl::kmajor_bytes(M, K), 256);
     w.scale = off; off += round_up((size_t)((M > 0 ? M : 1) + 1) * sizeof(float), 256);   // + one fused scalar
     w.pack = off; off += round_up(rtl_sparsify_pack_workspace(M, K, comp), 256);
-    w.gemm = off; off += round_up(rtl::gemm_workspace_bytes(true, M, N, K), 256);
     w.total = off;
     return w;
+}
+
+// Hands what lies behind the first `used` bytes of a workspace to the tile loop. Never more than the fixed
+// scratch of rtl_sparse_linear_static would leave, so that every entry point splits a contraction alike.
+void give_partials(rtl::GemmArgs& g, uint8_t* base, size_t used, size_t bytes) {
+    used = round_up(used, 256);
+    const size_t end = bytes < (size_t)RTL_STATIC_SCRATCH_BYTES ? bytes : (size_t)RTL_STATIC_SCRATCH_BYTES;
+    if (!base || !aligned(base, 16) || end <= used) return;
+    g.partials = reinterpret_cast<float*>(base + used);
+    g.partial_bytes = end - used;
+}
+// Size of a workspace whose mandatory part is `used` bytes.
+size_t with_partials(size_t used, bool sparse, bool fp8, int64_t M, int64_t N, int64_t K) {
+    const size_t planes = rtl::gemm_partial_bytes(sparse, fp8, M, N, K), at = round_up(used, 256);
+    return planes && at + planes <= (size_t)RTL_STATIC_SCRATCH_BYTES ? at + planes : used;
 }
 
 }  // namespace
@@ -147,11 +162,13 @@ static rtl_status check_linear(const void* A, const void* W, const void* Y, int6
     return RTL_OK;
 }
 
-// rtl_packed_linear workspace: [k-major copy of the values | k-major copy of the metadata | gemm scratch]
+// rtl_packed_linear workspace: [k-major copy of the values | k-major copy of the metadata | partial planes]
+static size_t packed_ws(int64_t M, int64_t K) {
+    return round_up(rtl::kmajor_val_bytes(M, K, 2), 256) + round_up(rtl::kmajor_bytes(M, K), 256);
+}
 size_t rtl_packed_linear_workspace(int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    return round_up(rtl::kmajor_val_bytes(M, K, 2), 256) + round_up(rtl::kmajor_bytes(M, K), 256) +
-           rtl::gemm_workspace_bytes(true, M, N, K);
+    return with_partials(packed_ws(M, K), true, false, M, N, K);
 }
 
 rtl_status rtl_packed_linear(const void* vals, const void* meta, const float* row_scale,
@@ -162,7 +179,7 @@ rtl_status rtl_packed_linear(const void* vals, const void* meta, const float* ro
     if (st != RTL_OK || M == 0 || N == 0) return st;
     if (!meta) return RTL_ERR_NULL;
     if (!aligned(meta, 8) || (bias && !aligned(bias, 2))) return RTL_ERR_ALIGN;
-    const size_t need = rtl_packed_linear_workspace(M, N, K);
+    const size_t need = packed_ws(M, K);
     if (need && (!workspace || workspace_bytes < need)) return RTL_ERR_WORKSPACE;
     if (need && !aligned(workspace, 256)) return RTL_ERR_ALIGN;
     RTL_REQUIRE_DEVICE();
@@ -181,19 +198,20 @@ rtl_status rtl_packed_linear(const void* vals, const void* meta, const float* ro
     g.tensor_scale = tensor_scale;
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
+    give_partials(g, static_cast<uint8_t*>(workspace), need, workspace_bytes);
     e = rtl::launch_gemm(true, g, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
 
 size_t rtl_sparse_linear_workspace(int64_t M, int64_t N, int64_t K, rtl_comp comp) {
     if (M <= 0 || N <= 0 || K <= 0 || !comp_ok(comp)) return 0;
-    return sparse_ws(M, N, K, comp).total;
+    return with_partials(sparse_ws(M, K, comp).total, true, false, M, N, K);
 }
 
 // Pack sweep + tile loop of rtl_sparse_linear on an already validated problem, with `base` the
-// 256-byte aligned scratch of sparse_ws(M, N, K, comp).total bytes (caller's workspace, or the
-// static array of rtl_sparse_linear_static).
-static rtl_status sparse_linear_on(uint8_t* base, const SparseWs& ws, const void* X, const void* W,
+// 256-byte aligned scratch of `bytes` >= ws.total bytes (caller's workspace, or the static array of
+// rtl_sparse_linear_static).
+static rtl_status sparse_linear_on(uint8_t* base, size_t bytes, const SparseWs& ws, const void* X, const void* W,
                                    const void* bias, void* Y, int64_t M, int64_t N, int64_t K, int64_t ldx,
                                    int64_t ldw, int64_t ldy, rtl_comp comp, float eps, hipStream_t s) {
     float* scale = reinterpret_cast<float*>(base + ws.scale);
@@ -210,6 +228,7 @@ static rtl_status sparse_linear_on(uint8_t* base, const SparseWs& ws, const void
     g.tensor_scale = comp == RTL_COMP_TENSOR ? scale : nullptr;
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
+    give_partials(g, base, ws.total, bytes);
     e = rtl::launch_gemm(true, g, s);
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
@@ -222,11 +241,11 @@ rtl_status rtl_sparse_linear(const void* X, const void* W, const void* bias, voi
     rtl_status st = check_linear(X, W, Y, M, N, K, ldx, ldw, ldy, K);
     if (st != RTL_OK || M == 0 || N == 0) return st;
     if (bias && !aligned(bias, 2)) return RTL_ERR_ALIGN;
-    const SparseWs ws = sparse_ws(M, N, K, comp);
+    const SparseWs ws = sparse_ws(M, K, comp);
     if (!workspace || workspace_bytes < ws.total) return RTL_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return RTL_ERR_ALIGN;
     RTL_REQUIRE_DEVICE();
-    return sparse_linear_on(static_cast<uint8_t*>(workspace), ws, X, W, bias, Y, M, N, K, ldx, ldw, ldy, comp,
+    return sparse_linear_on(static_cast<uint8_t*>(workspace), workspace_bytes, ws, X, W, bias, Y, M, N, K, ldx, ldw, ldy, comp,
                             eps, static_cast<hipStream_t>(stream));
 }
 
@@ -237,12 +256,12 @@ rtl_status rtl_sparse_linear_static(const void* X, const void* W, const void* bi
     rtl_status st = check_linear(X, W, Y, M, N, K, ldx, ldw, ldy, K);
     if (st != RTL_OK || M == 0 || N == 0) return st;
     if (bias && !aligned(bias, 2)) return RTL_ERR_ALIGN;
-    const SparseWs ws = sparse_ws(M, N, K, comp);
+    const SparseWs ws = sparse_ws(M, K, comp);
     if (ws.total > (size_t)RTL_STATIC_SCRATCH_BYTES) return RTL_ERR_WORKSPACE;   // problem too large for the fixed scratch
     void* base = nullptr;
     const rtl_status ready = device_ready(&base);    // first call on a device: looks up this device's array
     if (ready != RTL_OK) return ready;
-    return sparse_linear_on(static_cast<uint8_t*>(base), ws, X, W, bias, Y, M, N, K, ldx, ldw, ldy, comp, eps,
+    return sparse_linear_on(static_cast<uint8_t*>(base), RTL_STATIC_SCRATCH_BYTES, ws, X, W, bias, Y, M, N, K, ldx, ldw, ldy, comp, eps,
                             static_cast<hipStream_t>(stream));
 }
 
@@ -250,8 +269,8 @@ rtl_status rtl_sparse_linear_static(const void* X, const void* W, const void* bi
 // per-K-range partial planes and row sums of the one-pass sweep]
 size_t rtl_sparse_lora_linear_workspace(int64_t M, int64_t N, int64_t K, int64_t R, rtl_comp comp) {
     if (M <= 0 || N <= 0 || K <= 0 || R != rtl::kLoraRank || !comp_ok(comp)) return 0;
-    return sparse_ws(M, N, K, comp).total + round_up((size_t)M * rtl::kLoraRank * 4, 256) +
-           round_up(rtl::pack_down_scratch_bytes(M, K), 256);
+    return with_partials(sparse_ws(M, K, comp).total + round_up((size_t)M * rtl::kLoraRank * 4, 256) +
+                             round_up(rtl::pack_down_scratch_bytes(M, K), 256), true, false, M, N, K);
 }
 
 rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, const void* LB,
@@ -267,7 +286,7 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
     if (ldla % 8 != 0 || ldlb % 8 != 0 || !aligned(LA, 16) || !aligned(LB, 16) ||
         (bias && !aligned(bias, 2)))
         return RTL_ERR_ALIGN;
-    const SparseWs ws = sparse_ws(M, N, K, comp);
+    const SparseWs ws = sparse_ws(M, K, comp);
     const size_t t_off = ws.total, p_off = t_off + round_up((size_t)M * rtl::kLoraRank * 4, 256);
     const size_t need = p_off + round_up(rtl::pack_down_scratch_min(M, K), 256);   // the query asks for the preferred size
     if (!workspace || workspace_bytes < need) return RTL_ERR_WORKSPACE;
@@ -295,6 +314,7 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
     g.T = T;
     g.LA = static_cast<const uint16_t*>(LA);
     g.ldla = ldla;
+    give_partials(g, base, p_off + round_up(rtl::pack_down_scratch_bytes(M, K), 256), workspace_bytes);
     e = rtl::launch_gemm(true, g, s);
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
@@ -343,7 +363,7 @@ rtl_status rtl_sparsify_pack_fp8(const void* X, int64_t M, int64_t K, int64_t ld
 
 size_t rtl_sparse_linear_fp8_workspace(int64_t M, int64_t N, int64_t K, rtl_comp comp) {
     if (M <= 0 || N <= 0 || K <= 0 || !comp_ok(comp)) return 0;
-    return sparse_ws(M, N, K, comp, 1).total;
+    return with_partials(sparse_ws(M, K, comp, 1).total, true, true, M, N, K);
 }
 
 rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_scale, const void* bias,
@@ -355,7 +375,7 @@ rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_s
     if (st != RTL_OK || M == 0 || N == 0) return st;
     if (!x_scale) return RTL_ERR_NULL;
     if ((bias && !aligned(bias, 2)) || !aligned(x_scale, 4)) return RTL_ERR_ALIGN;
-    const SparseWs ws = sparse_ws(M, N, K, comp, 1);
+    const SparseWs ws = sparse_ws(M, K, comp, 1);
     if (!workspace || workspace_bytes < ws.total) return RTL_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return RTL_ERR_ALIGN;
     RTL_REQUIRE_DEVICE();
@@ -377,6 +397,7 @@ rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_s
     g.tensor_scale = comp == RTL_COMP_TENSOR ? fused : x_scale;   // dequantisation rides on the epilogue
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
+    give_partials(g, base, ws.total, workspace_bytes);
     e = rtl::launch_gemm(true, g, s);
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
@@ -384,8 +405,8 @@ rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_s
 // rtl_sparse_lora_linear_fp8 workspace: [rtl_sparse_linear_fp8 workspace | T as two bf16 planes | sweep scratch]
 size_t rtl_sparse_lora_linear_fp8_workspace(int64_t M, int64_t N, int64_t K, int64_t R, rtl_comp comp) {
     if (M <= 0 || N <= 0 || K <= 0 || R != rtl::kLoraRank || !comp_ok(comp)) return 0;
-    return sparse_ws(M, N, K, comp, 1).total + round_up((size_t)M * rtl::kLoraRank * 4, 256) +
-           round_up(rtl::pack_down_scratch_bytes(M, K), 256);
+    return with_partials(sparse_ws(M, K, comp, 1).total + round_up((size_t)M * rtl::kLoraRank * 4, 256) +
+                             round_up(rtl::pack_down_scratch_bytes(M, K), 256), true, true, M, N, K);
 }
 
 rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float* x_scale, const void* LA,
@@ -401,7 +422,7 @@ rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float
     if (ldla % 8 != 0 || ldlb % 8 != 0 || !aligned(LA, 16) || !aligned(LB, 16) || (bias && !aligned(bias, 2)) ||
         !aligned(x_scale, 4))
         return RTL_ERR_ALIGN;
-    const SparseWs ws = sparse_ws(M, N, K, comp, 1);
+    const SparseWs ws = sparse_ws(M, K, comp, 1);
     const size_t t_off = ws.total, p_off = t_off + round_up((size_t)M * rtl::kLoraRank * 4, 256);
     const size_t need = p_off + round_up(rtl::pack_down_scratch_min(M, K), 256);   // the query asks for the preferred size
     if (!workspace || workspace_bytes < need) return RTL_ERR_WORKSPACE;
@@ -430,6 +451,7 @@ rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float
     g.T = T;
     g.LA = static_cast<const uint16_t*>(LA);
     g.ldla = ldla;
+    give_partials(g, base, p_off + round_up(rtl::pack_down_scratch_bytes(M, K), 256), workspace_bytes);
     e = rtl::launch_gemm(true, g, s);
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
@@ -469,7 +491,7 @@ rtl_status rtl_diag_pack_sweep(const void* X, int64_t M, int64_t K, int64_t ldx,
     if (M == 0) return RTL_OK;
     if (!X) return RTL_ERR_NULL;
     if (ldx % 8 != 0 || !aligned(X, 16)) return RTL_ERR_ALIGN;
-    const SparseWs ws = sparse_ws(M, 1, K, comp);
+    const SparseWs ws = sparse_ws(M, K, comp);
     if (!workspace || workspace_bytes < ws.total) return RTL_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return RTL_ERR_ALIGN;
     RTL_REQUIRE_DEVICE();
@@ -489,7 +511,7 @@ rtl_status rtl_diag_tile_plan(int64_t M, int64_t N, int dense, int64_t* plan) {
 
 size_t rtl_dense_linear_workspace(int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    return rtl::gemm_workspace_bytes(false, M, N, K);
+    return with_partials(0, false, false, M, N, K);
 }
 
 rtl_status rtl_dense_linear(const void* X, const void* W, const void* bias, void* Y, int64_t M,
@@ -498,11 +520,9 @@ rtl_status rtl_dense_linear(const void* X, const void* W, const void* bias, void
     rtl_status st = check_linear(X, W, Y, M, N, K, ldx, ldw, ldy, K);
     if (st != RTL_OK || M == 0 || N == 0) return st;
     if (bias && !aligned(bias, 2)) return RTL_ERR_ALIGN;
-    const size_t need = rtl_dense_linear_workspace(M, N, K);
-    if (need && (!workspace || workspace_bytes < need)) return RTL_ERR_WORKSPACE;
-    if (need && !aligned(workspace, 256)) return RTL_ERR_ALIGN;
     RTL_REQUIRE_DEVICE();
     rtl::GemmArgs g{};
+    give_partials(g, static_cast<uint8_t*>(workspace), 0, workspace_bytes);      // none of it is mandatory
     g.A = X;
     g.W = W;
     g.bias = static_cast<const uint16_t*>(bias);

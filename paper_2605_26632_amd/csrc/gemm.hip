@@ -176,12 +176,16 @@ __device__ __forceinline__ float mul_add_rn(float a, float b, float add) {
 // MODE 0: plain linear. MODE 1 (sparse only): LoRA tail, the accumulators also receive T L_A^T before
 // the epilogue.
 // `tile`: index of this workgroup's output tile in the walk of the (M / BM) x (N / BN) tile grid.
+// PART: the workgroup covers the k blocks [kblk0, kblk0 + kblks) only and leaves its fp32 sums in plane `part` of
+// a.partials; the factors (MODE 0), the bias and the rounding are split_reduce_kernel's.
 // WAVES_K > 1: the waves divide the contraction too. K group g of the WAVES_K groups of WAVES_M x WAVES_N
 // waves takes the k blocks g, g + WAVES_K, ... with operands and accumulators of its own, and the groups'
 // tiles are added up in LDS, in the order of g, when the loop is done.
 template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false,
-          bool D64 = false, int WAVES_K = 1>
-__device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
+          bool D64 = false, int WAVES_K = 1, bool PART = false>
+__device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, const int part = 0, const int kblk0 = 0,
+                                          const int kblks = 0) {
+    static_assert(!PART || WAVES_K == 1, "partial sums leave from the accumulators");
     static_assert(!D64 || (!SPARSE && MODE != 1), "64-k stages: dense kernels only");
     static_assert(MODE == 0 || (MODE == 1 && SPARSE), "mode/operand combination");
     static_assert(!FP8 || SPARSE, "FP8 operands: sparse kernels only");
@@ -215,14 +219,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);    // wave-uniform, lives in an SGPR
     const int wk = WAVES_K > 1 ? wid / NW : 0, wave = WAVES_K > 1 ? wid % NW : wid;   // K group, wave inside it
-    uint8_t* const ring = smem + wk * L::kGroup;                 // the group's part of the first stage
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)ring;
+    uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
+    if constexpr (WAVES_K > 1) lds0 += wk * L::kGroup;           // the group's part of the first stage
+    auto stage_base = [&](int stage) {
+        if constexpr (WAVES_K > 1) return (const uint8_t*)(smem + wk * L::kGroup + stage * L::kStage);
+        else return (const uint8_t*)(smem + stage * L::kStage);
+    };
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
     int pm, pn;
     tile_walk<(BM >= 256 ? 8 : 16)>(tile, tiles_m, tiles_n, pm, pn);
     const int64_t m0 = (int64_t)pm * BM, n0 = (int64_t)pn * BN;
-    const int blocks = (int)(a.K / KSTAGE);
+    const int blocks = PART ? kblks : (int)(a.K / KSTAGE);
     const int KT = WAVES_K > 1 ? (blocks - wk + WAVES_K - 1) / WAVES_K : blocks;   // stages in which this wave's group has a block
 
     // ---- global -> LDS: every lane owns fixed chunks; rows past the edge are clamped to the last
@@ -236,6 +244,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
         ? static_cast<const uint8_t*>(a.A) + m0 * 64
         : static_cast<const uint8_t*>(a.A) + m0 * a.lda * ESZ;
     const uint8_t* base_b = static_cast<const uint8_t*>(a.W) + n0 * a.ldw * ESZ;
+    if constexpr (PART) {
+        base_a += kblk0 * a_stride;
+        base_b += (int64_t)kblk0 * (KSTAGE * ESZ);
+    }
     const int64_t rows_a = a.M - m0, rows_b = a.N - n0;     // valid rows from the tile's first row
     uint32_t oa[A_PER_W];
 #pragma unroll
@@ -263,6 +275,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
         // k-major records: the rows of this tile are one contiguous run per stage (2 KiB, 4 KiB with
         // FP8 operands) and wave w moves M_PER_W 256-byte pieces of it, 4 bytes per lane
         base_m = a.meta + m0 * MREC;
+        if constexpr (PART) base_m += kblk0 * rows_pad * MREC;
         om = (uint32_t)(wave * M_PER_W * 256 + lane * 4);
     }
 
@@ -333,7 +346,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
     int ix_cur[TM * IXW], ix_nxt[TM * IXW];
 
     auto read_frags = [&](int stage, int sub, Frags& f) {
-        const uint8_t* base = ring + stage * L::kStage;
+        const uint8_t* base = stage_base(stage);
         const uint8_t* bB = base + L::kABytes + L::kMetaBytes;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -360,7 +373,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
     };
     auto read_idx = [&](int stage, int (&ix)[TM * IXW]) {
         if constexpr (SPARSE) {
-            const uint8_t* bM = ring + stage * L::kStage + L::kABytes;
+            const uint8_t* bM = stage_base(stage) + L::kABytes;
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 if constexpr (FP8) {
@@ -378,7 +391,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
     auto read_one = [&](int stage, auto sub_tag, Frags& f, int (&ix)[TM * IXW], auto n_tag) {
         constexpr int SUB = decltype(sub_tag)::value, n = decltype(n_tag)::value;
         constexpr int NI = (SPARSE && SUB == 0) ? TM : 0;     // metadata reads first
-        const uint8_t* base = ring + stage * L::kStage;
+        const uint8_t* base = stage_base(stage);
         const uint8_t* bB = base + L::kABytes + L::kMetaBytes;
         if constexpr (n < NI) {
             if constexpr (FP8) {
@@ -705,6 +718,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
                     for (int j = 0; j < TN; ++j) acc[i][j][r] *= f;
                 }
         }
+      if (!PART || part == 0) {                // (of several partial planes the first carries the residual)
         wait_vmcnt_lgkm0<0>();
         __builtin_amdgcn_s_barrier();          // the ring is free: reuse it for the two rank tiles
         constexpr int T_LOADS = BM * 128 / 1024, LA_LOADS = BN * 128 / 1024;   // rows of 64 bf16
@@ -750,6 +764,24 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile) {
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(th[i].v, lb[j].v, acc[i][j], 0, 0, 0);
                 }
         }
+      }
+    }
+
+    if constexpr (PART) {
+        // 32 lanes of a register hold 32 neighbouring columns of one row: whole 128-byte lines
+        float* plane = a.partials + (int64_t)part * a.M * a.part_pitch;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int64_t col = n0 + wn * WTN + j * 32 + li;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int64_t row = m0 + wm * WTM + i * 32 + 8 * (r / 4) + 4 * kb + (r % 4);
+                    if (row < a.M && col < a.N) plane[row * a.part_pitch + col] = acc[i][j][r];
+                }
+        }
+        return;
     }
 
     // ---- epilogue: optional fp32 scales, bias, bf16 RNE, store --------------------------------
@@ -964,9 +996,84 @@ struct Split {
     }
 };
 
-}  // namespace
+// Contraction split over workgroups (PART): a.k_splits workgroups per tile, each with an even share of the k blocks,
+// and split_reduce_kernel over their planes. For problems whose tiles do not reach all compute units and whose
+// contraction is long enough to pay for the planes (M x N x 4 bytes each way per split) and the second launch.
+// Whole calls, best unsplit shape -> split (us): dense [200, 3072, 12288] 36.9 -> 28.7, [333, 3072, 12288] 51.6 -> 37.6,
+// [512, 1024, 12288] 29.7 -> 23.6; sparse [333, 3072, 12288] 44.4 -> 37.3, [700, 3072, 12288] 66.2 -> 55.7; LoRA [512, 3072,
+// 12288] 55.9 -> 51.3.
+template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false>
+__global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void gemm_part_kernel(const GemmArgs a) {
+    const int tiles = (int)(((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN)), total = tiles * a.k_splits;
+    const int xcd = (int)blockIdx.x % 8, local = (int)blockIdx.x / 8;
+    const int idx = xcd_share_start(total, xcd) + local;       // an XCD's share: few parts, neighbouring tiles
+    const int part = idx / tiles, blocks = (int)(a.K / (FP8 ? 128 : 64));
+    const int b0 = (int)((int64_t)blocks * part / a.k_splits), b1 = (int)((int64_t)blocks * (part + 1) / a.k_splits);
+    gemm_tile<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, !SPARSE, 1, true>(a, idx % tiles, part, b0, b1 - b0);
+}
 
-size_t gemm_workspace_bytes(bool, int64_t, int64_t, int64_t) { return 0; }
+// Adds the planes up in order, then factors, bias, bf16. A thread finishes eight columns of a row, the planes'
+// loads in flight together; grid (column chunks / 256, rows).
+constexpr int kMaxKSplits = 8;
+__global__ __launch_bounds__(256) void split_reduce_kernel(const GemmArgs a, const bool factors) {
+    const int64_t row = blockIdx.y, col = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+    if (col >= a.N) return;
+    const float* p = a.partials + row * a.part_pitch + col;
+    float4 v[kMaxKSplits][2];
+#pragma unroll
+    for (int s = 0; s < kMaxKSplits; ++s)
+        if (s < a.k_splits) {
+            v[s][0] = *reinterpret_cast<const float4*>(p + (int64_t)s * a.M * a.part_pitch);
+            v[s][1] = *reinterpret_cast<const float4*>(p + (int64_t)s * a.M * a.part_pitch + 4);
+        }
+    const int valid = (int)min((int64_t)8, a.N - col);
+    float bv[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) bv[e] = a.bias ? __uint_as_float((uint32_t)a.bias[col + min(e, valid - 1)] << 16) : 0.f;
+    const float f = factors ? (a.row_scale ? a.row_scale[row] : 1.0f) * (a.tensor_scale ? a.tensor_scale[0] : 1.0f) : 1.0f;
+    float sum[8] = {v[0][0].x, v[0][0].y, v[0][0].z, v[0][0].w, v[0][1].x, v[0][1].y, v[0][1].z, v[0][1].w};
+#pragma unroll
+    for (int s = 1; s < kMaxKSplits; ++s)
+        if (s < a.k_splits) {
+            sum[0] += v[s][0].x; sum[1] += v[s][0].y; sum[2] += v[s][0].z; sum[3] += v[s][0].w;
+            sum[4] += v[s][1].x; sum[5] += v[s][1].y; sum[6] += v[s][1].z; sum[7] += v[s][1].w;
+        }
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    uint32_t out[4];
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        const f32x2 y = {mul_add_rn(sum[e], f, bv[e]), mul_add_rn(sum[e + 1], f, bv[e + 1])};
+        out[e / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(y, bf16x2));       // RNE
+    }
+    uint16_t* dst = a.Y + row * a.ldy + col;
+    if (((reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) && (a.ldy % 8 == 0) && valid == 8) {
+        *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2], out[3]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (e < valid) dst[e] = (uint16_t)(out[e >> 1] >> (16 * (e & 1)));
+    }
+}
+
+template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false>
+struct Part {
+    using L = Smem<SPARSE, BM, BN, STAGES, WAVES_M, WAVES_N, FP8, !SPARSE>;
+    static hipError_t prepare() {
+        auto kern = gemm_part_kernel<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8>;
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, L::kTotal);
+    }
+    static hipError_t launch(const GemmArgs& a, hipStream_t stream) {
+        auto kern = gemm_part_kernel<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8>;
+        const int64_t tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * a.k_splits)), dim3(WAVES_M * WAVES_N * 64), L::kTotal, stream, a);
+        hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)((a.N + 2047) / 2048), (unsigned)a.M), dim3(256), 0, stream, a,
+                           MODE == 0);
+        return hipGetLastError();
+    }
+};
+
+}  // namespace
 
 // ---- tile plan ---------------------------------------------------------------------------------
 // A launch cuts rows [0, m_split) of the output into 256 x BN body tiles (BN = 256 or 192) and the
@@ -1064,7 +1171,7 @@ struct SplitShape {
 constexpr SplitShape kSparseShapes[] = {
     {32, 32, 1, 1.2, 0.087}, {64, 32, 1, 1.9, 0.108}, {64, 64, 2, 2.4, 0.153}, {128, 64, 1, 2.3, 0.19}, {128, 128, 2, 2.8, 0.30}};
 constexpr SplitShape kDenseShapes[] = {
-    {32, 32, 1, 1.2, 0.10}, {64, 32, 1, 1.8, 0.135}, {64, 64, 1, 1.0, 0.18}, {128, 64, 1, 2.5, 0.24}, {128, 128, 1, 3.8, 0.36},
+    {32, 32, 1, 1.2, 0.10}, {64, 32, 1, 1.8, 0.135}, {64, 64, 1, 1.0, 0.18}, {128, 64, 1, 2.5, 0.262}, {128, 128, 1, 3.8, 0.36},
     {256, 128, 1, 4.0, 0.48}};
 
 // Index of the small shape that should serve the problem, or -1 for the 256-row plan. Times are estimated
@@ -1073,12 +1180,18 @@ constexpr SplitShape kDenseShapes[] = {
 // KB of a stage, which grows from 10.7 ns (dense 15.5: both operands row-major) while at most 96 units work
 // to 17.2 (21) when all do and share the L2s and the power budget. Against the best of all variants, measured,
 // the choice was within 3 % at 98 of 110 random shapes ([1..6000, 64..21504, 128..15360]) and within 8 % at all but one.
-static int pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_t blocks, bool dense) {
+struct SplitChoice {
+    int shape;       // index of the small shape, or -1 for the 256-row plan
+    int k_splits;    // > 1: gemm_part_kernel on the 128 x 128 (part_256 false) or 256 x 128 tile
+    bool part_256;
+};
+static int64_t part_pitch(int64_t N) { return (N + 7) / 8 * 8; }     // columns of a plane: whole eight-column chunks
+static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_t blocks, bool dense, size_t room) {
     const double busy = (double)(plan.body_tiles + plan.tail_tiles < 256 ? plan.body_tiles + plan.tail_tiles : 256);
     const double load = busy > 96 ? (busy - 96) / 160 : 0.0;
     const double per_kb = dense ? 0.0155 + 0.0055 * load : 0.0107 + 0.0065 * load;
     double best = 3.4 + (double)blocks * plan.cost * per_kb;
-    int pick = -1;
+    SplitChoice pick{-1, 1, false};
     const SplitShape* shapes = dense ? kDenseShapes : kSparseShapes;
     const int count = dense ? (int)(sizeof(kDenseShapes) / sizeof(SplitShape)) : (int)(sizeof(kSparseShapes) / sizeof(SplitShape));
     for (int i = 0; i < count; ++i) {
@@ -1095,10 +1208,35 @@ static int pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_t blocks
         const double t = (double)passes * (s.fixed + (double)blocks * block) * (passes > 1 ? several : 1.0);
         if (t < best) {
             best = t;
-            pick = i;
+            pick.shape = i;
+        }
+    }
+    // Contraction split over workgroups: at most one workgroup per compute unit (dense 224: the last ones slow all
+    // others down), at least 16 blocks each, up to six parts (dense eight). Second launch, writing and reading the planes: 8 us + 0.5 us per MB of
+    // planes (dense 4.5 + 0.8), fitted to 150 points at N = 1024 and 3072, K = 6144 and 12288; the estimate has to be
+    // 2 % better than the best unsplit one.
+    for (int big = 0; big < 2; ++big) {
+        const int64_t tiles = ((M + (big ? 255 : 127)) / (big ? 256 : 128)) * ((N + 127) / 128);
+        const double block = big ? (dense ? 0.53 : 0.35) : (dense ? 0.36 : 0.285);
+        for (int s = 2; s <= (dense ? kMaxKSplits : 6) && tiles * s <= (dense ? 224 : 256) && blocks / s >= 16; ++s) {
+            const double planes = (double)s * (double)M * (double)part_pitch(N) * 4.0;
+            if (planes > (double)room) break;
+            const double t = (double)((blocks + s - 1) / s) * block + (dense ? 4.5 + planes * 0.8e-6 : 8.0 + planes * 0.5e-6);
+            if (t < best * (pick.k_splits > 1 ? 1.0 : 0.98)) {
+                best = t;
+                pick = SplitChoice{pick.shape, s, big != 0};
+            }
         }
     }
     return pick;
+}
+
+// Preferred size of the partial planes for an [M, N, K] problem (0 where the contraction is not split over workgroups).
+size_t gemm_partial_bytes(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K) {
+    const int64_t blocks = K / (fp8 ? 128 : 64);
+    if (blocks < 32 || ((M + 255) / 256) * ((N + 127) / 128) > 128) return 0;       // (the bound of the loop above at two splits)
+    const SplitChoice c = pick_split(plan_for(M, N, !sparse), M, N, blocks, !sparse, ~(size_t)0);
+    return c.k_splits > 1 ? (size_t)c.k_splits * (size_t)M * (size_t)part_pitch(N) * 4 : 0;
 }
 
 // Runs `op` (launch or prepare) of small shape `i`. Ring depths: as many stages as LDS holds, two workgroups
@@ -1125,6 +1263,12 @@ static hipError_t with_split(int i, Op op) {
     }
 }
 
+template <bool SPARSE, int MODE, bool FP8, class Op>
+static hipError_t with_part(bool big, Op op) {
+    if (big) return op(Part<SPARSE, 256, 128, 2, 4, 3, MODE, FP8>{});
+    return op(Part<SPARSE, 128, 128, 2, 2, 3, MODE, FP8>{});
+}
+
 // Every configuration launch_gemm can pick.
 hipError_t prepare_gemm_kernels() {
     hipError_t e = hipSuccess;
@@ -1147,6 +1291,13 @@ hipError_t prepare_gemm_kernels() {
         run(with_split<true, 1, true>(i, prep));
     }
     for (int i = 0; i < 6; ++i) run(with_split<false, 0, false>(i, prep));
+    for (int i = 0; i < 2; ++i) {
+        run(with_part<false, 0, false>(i != 0, prep));
+        run(with_part<true, 0, false>(i != 0, prep));
+        run(with_part<true, 1, false>(i != 0, prep));
+        run(with_part<true, 0, true>(i != 0, prep));
+        run(with_part<true, 1, true>(i != 0, prep));
+    }
     return e;
 }
 
@@ -1158,9 +1309,18 @@ hipError_t launch_gemm(bool sparse, const GemmArgs& a_in, hipStream_t stream) {
     a.tail_tiles = plan.tail_tiles;
     a.rows_pad = kmajor_rows(a.M);
     a.t_plane = a.M * kLoraRank;
-    const int split = pick_split(plan, a.M, a.N, a.K / (a.fp8 ? 128 : 64), !sparse);
+    const SplitChoice choice = pick_split(plan, a.M, a.N, a.K / (a.fp8 ? 128 : 64), !sparse, a.partials ? a.partial_bytes : 0);
+    auto go = [&](auto k) { return decltype(k)::launch(a, stream); };
+    if (choice.k_splits > 1) {
+        a.k_splits = choice.k_splits;
+        a.part_pitch = part_pitch(a.N);
+        const bool big = choice.part_256;
+        if (!sparse) return with_part<false, 0, false>(big, go);
+        if (a.fp8) return a.T ? with_part<true, 1, true>(big, go) : with_part<true, 0, true>(big, go);
+        return a.T ? with_part<true, 1, false>(big, go) : with_part<true, 0, false>(big, go);
+    }
+    const int split = choice.shape;
     if (split >= 0) {
-        auto go = [&](auto k) { return decltype(k)::launch(a, stream); };
         if (!sparse) return with_split<false, 0, false>(split, go);
         if (a.fp8) return a.T ? with_split<true, 1, true>(split, go) : with_split<true, 0, true>(split, go);
         return a.T ? with_split<true, 1, false>(split, go) : with_split<true, 0, false>(split, go);

@@ -1203,3 +1203,52 @@ def test_pack_group_factor_over_exponent_spreads(spread):
     for eps in (1e-8, 0.7):
         check_pack(X, rtl.COMP_GROUP, eps=eps)
     check_pack_fp8(X, rtl.COMP_GROUP, fp8_scale(X))
+
+
+@pytest.mark.parametrize("M,N,K", [(129, 3001, 12352), (200, 3072, 12288), (260, 2100, 9280), (700, 3071, 12352), (200, 3072, 24576)])
+def test_contraction_split_over_workgroups(M, N, K):
+    """Shapes on which the contraction is spread over workgroups (ragged M, N and block counts): dense, sparse with
+    per-row factor and bias, LoRA, FP8, FP8 + LoRA on sampled rows, the entry point on the fixed scratch bit for bit,
+    and every call again on a workspace without room for the partial planes."""
+    X = synth.activations("gelu", M, K, seed=M, device=DEV)
+    W = synth.weights(N, K, seed=N, device=DEV)
+    b = synth.bias(N, seed=4, device=DEV, std=0.5)
+    LA, LB = synth.lora(N, K, 64, seed=5, device=DEV, std_a=0.05, std_b=0.05)
+    rows = sampled_rows(M, 8, seed=6)
+    sel = torch.from_numpy(rows).to(DEV)
+    Xs, Wb, bb = synth.bits(X[sel]), synth.bits(W), synth.bits(b)
+    L = rtl.lib()
+
+    def both(call, planned, ref):
+        assert planned > 0
+        check_y(call(None)[sel], ref)
+        planes = 2 * M * ((N + 7) // 8 * 8) * 4                    # the least a split needs
+        ws = torch.empty(max(planned - planes, 256), dtype=torch.uint8, device=DEV)
+        try:
+            check_y(call(ws)[sel], ref)
+        except rtl.RtlError as e:
+            assert e.status == 4                                   # cut into the mandatory part
+    ref = oracle.dense_linear_oracle(Xs, Wb, bias=bb)
+    both(lambda ws: rtl.dense_linear(X, W, bias=b, ws=ws), int(L.rtl_dense_linear_workspace(M, N, K)), ref)
+    check_y(rtl.dense_linear(X, W, bias=b, ws=torch.empty(0, dtype=torch.uint8, device=DEV))[sel], ref)
+    for comp in (rtl.COMP_GROUP, rtl.COMP_ROW):
+        ref = oracle.sparse_linear_oracle(Xs, Wb, bias=bb, scope=comp)["Y"]
+        Y, guard_ok = guarded((M, N), torch.bfloat16, 7.0)
+        rtl.sparse_linear(X, W, bias=b, comp=comp, out=Y)
+        check_y(Y[sel], ref)
+        guard_ok()
+        both(lambda ws: rtl.sparse_linear(X, W, bias=b, comp=comp, ws=ws), rtl.sparse_linear_workspace(M, N, K, comp), ref)
+        Z = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+        assert torch.equal(rtl.sparse_linear_static(X, W, Z, bias=b, comp=comp), Y)
+        ref = oracle.sparse_lora_linear_oracle(Xs, Wb, synth.bits(LA), synth.bits(LB), bias=bb, scope=comp)["Y"]
+        both(lambda ws: rtl.sparse_lora_linear(X, W, LA, LB, bias=b, comp=comp, ws=ws),
+             rtl.sparse_lora_linear_workspace(M, N, K, 64, comp), ref)
+    vals, meta, _ = rtl.sparsify_pack(X, comp=rtl.COMP_GROUP)
+    assert torch.equal(rtl.packed_linear(vals, meta, W, bias=b), rtl.sparse_linear(X, W, bias=b, comp=rtl.COMP_GROUP))
+    if K % 128 == 0:
+        xs, Wq = fp8_scale(X), rtl.quantize_fp8(W)
+        Wn, f = Wq.cpu().numpy(), float(xs.item())
+        r = oracle.sparse_linear_fp8_oracle(Xs, Wn, f, bias=bb, scope=oracle.GROUP)
+        check_y_fp8(rtl.sparse_linear_fp8(X, Wq, xs, bias=b)[sel], r, Wn, f, bias=bb)
+        r = oracle.sparse_lora_linear_fp8_oracle(Xs, Wn, f, synth.bits(LA), synth.bits(LB), bias=bb, scope=oracle.GROUP)
+        assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b)[sel]), r["Y"]) <= Y_TOL
