@@ -103,8 +103,8 @@ __device__ __forceinline__ GroupOut select_group(uint32_t d0, uint32_t d1, float
         // exact sequence: 3 in num, 2 in den, 1 for the quotient, 3 after the root, 1 and 1: 5. The two differ by
         // at most 13; the exact sequence only runs when a fast product lies within 16 units of a bf16 rounding
         // boundary, i.e. whenever they could round differently. The result is bit-identical.
-        // Against selection on 17-bit keys with fused multiply-adds for the norms (14 vector instructions more of
-        // 51 per group): sweep of rtl_sparse_linear [4096, 12288] 31.1 -> 28.1 us (5.6 TB/s), [4608, 3072] 10.8 ->
+        // Against selection on 17-bit keys with fused multiply-adds for the norms (fast path of the whole sweep 67
+        // vector instructions per group, 51 now): sweep of rtl_sparse_linear [4096, 12288] 31.1 -> 28.1 us (5.6 TB/s), [4608, 3072] 10.8 ->
         // 9.9, NONE 7.7 -> 7.3, FP8 GROUP [4608, 12288] 31.5 -> 29.6.
         const float num = dot2_bf16(d1, dot2_bf16(d0, 0.f));
         const float d = dot2_bf16(pair, eps);
