@@ -88,6 +88,16 @@ void give_partials(rtl::GemmArgs& g, uint8_t* base, size_t used, size_t bytes) {
     g.partials = reinterpret_cast<float*>(base + used);
     g.partial_bytes = end - used;
 }
+// TENSOR scope: leaves the factor of the sums at `rowsums` to the tile loop, which puts it in scale[0] (and, with an
+// FP8 activation scale, their product in fused[0]).
+void give_factor(rtl::GemmArgs& g, const float* rowsums, int64_t M, float eps, float* scale, const float* x_scale, float* fused) {
+    g.rowsums = rowsums;
+    g.factor_rows = M;
+    g.factor_eps = eps;
+    g.factor_out = scale;
+    g.factor_mul = x_scale;
+    g.factor_fused = fused;
+}
 // Size of a workspace whose mandatory part is `used` bytes.
 size_t with_partials(size_t used, bool sparse, bool fp8, int64_t M, int64_t N, int64_t K) {
     const size_t planes = rtl::gemm_partial_bytes(sparse, fp8, M, N, K), at = round_up(used, 256);
@@ -217,7 +227,7 @@ static rtl_status sparse_linear_on(uint8_t* base, size_t bytes, const SparseWs& 
     float* scale = reinterpret_cast<float*>(base + ws.scale);
     hipError_t e = rtl::launch_sparsify_pack(
         static_cast<const uint16_t*>(X), M, K, ldx, comp, eps, nullptr, nullptr, base + ws.vals,
-        base + ws.meta, scale, reinterpret_cast<float*>(base + ws.pack), s);
+        base + ws.meta, comp == RTL_COMP_TENSOR ? nullptr : scale, reinterpret_cast<float*>(base + ws.pack), s);
     if (e != hipSuccess) return RTL_ERR_HIP;
     rtl::GemmArgs g{};
     g.A = base + ws.vals;
@@ -225,7 +235,7 @@ static rtl_status sparse_linear_on(uint8_t* base, size_t bytes, const SparseWs& 
     g.W = W;
     g.bias = static_cast<const uint16_t*>(bias);
     g.row_scale = comp == RTL_COMP_ROW ? scale : nullptr;
-    g.tensor_scale = comp == RTL_COMP_TENSOR ? scale : nullptr;
+    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), M, eps, scale, nullptr, nullptr);
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
     give_partials(g, base, ws.total, bytes);
@@ -299,7 +309,8 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
     // one pass over X: the sweep that compresses the activation also forms T = X L_B^T
     hipError_t e = rtl::launch_pack_down(static_cast<const uint16_t*>(X), M, K, ldx, comp, eps,
                                          static_cast<const uint16_t*>(LB), ldlb, base + ws.vals, base + ws.meta,
-                                         reinterpret_cast<float*>(base + p_off), workspace_bytes - p_off, T, scale,
+                                         reinterpret_cast<float*>(base + p_off), workspace_bytes - p_off, T,
+                                         comp == RTL_COMP_TENSOR ? nullptr : scale,
                                          reinterpret_cast<float*>(base + ws.pack), s);
     if (e != hipSuccess) return RTL_ERR_HIP;
     rtl::GemmArgs g{};
@@ -308,7 +319,7 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
     g.W = W;
     g.bias = static_cast<const uint16_t*>(bias);
     g.row_scale = comp == RTL_COMP_ROW ? scale : nullptr;
-    g.tensor_scale = comp == RTL_COMP_TENSOR ? scale : nullptr;
+    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), M, eps, scale, nullptr, nullptr);
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
     g.T = T;
@@ -356,7 +367,7 @@ rtl_status rtl_sparsify_pack_fp8(const void* X, int64_t M, int64_t K, int64_t ld
     RTL_REQUIRE_DEVICE();
     hipError_t e = rtl::launch_sparsify_pack_fp8(
         static_cast<const uint16_t*>(X), M, K, ldx, comp, eps, x_scale, static_cast<uint8_t*>(vals),
-        static_cast<uint8_t*>(meta), nullptr, nullptr, scale, static_cast<float*>(workspace), nullptr,
+        static_cast<uint8_t*>(meta), nullptr, nullptr, scale, static_cast<float*>(workspace),
         static_cast<hipStream_t>(stream));
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
@@ -385,7 +396,7 @@ rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_s
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = rtl::launch_sparsify_pack_fp8(
         static_cast<const uint16_t*>(X), M, K, ldx, comp, eps, x_scale, nullptr, nullptr, base + ws.vals,
-        base + ws.meta, scale, reinterpret_cast<float*>(base + ws.pack), fused, s);
+        base + ws.meta, comp == RTL_COMP_TENSOR ? nullptr : scale, reinterpret_cast<float*>(base + ws.pack), s);
     if (e != hipSuccess) return RTL_ERR_HIP;
     rtl::GemmArgs g{};
     g.fp8 = true;
@@ -394,7 +405,8 @@ rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_s
     g.W = Wq;
     g.bias = static_cast<const uint16_t*>(bias);
     g.row_scale = comp == RTL_COMP_ROW ? scale : nullptr;
-    g.tensor_scale = comp == RTL_COMP_TENSOR ? fused : x_scale;   // dequantisation rides on the epilogue
+    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), M, eps, scale, x_scale, fused);
+    else g.tensor_scale = x_scale;                       // dequantisation rides on the epilogue
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
     give_partials(g, base, ws.total, workspace_bytes);
@@ -435,8 +447,9 @@ rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = rtl::launch_pack_down(static_cast<const uint16_t*>(X), M, K, ldx, comp, eps,
                                          static_cast<const uint16_t*>(LB), ldlb, base + ws.vals, base + ws.meta,
-                                         reinterpret_cast<float*>(base + p_off), workspace_bytes - p_off, T, scale,
-                                         reinterpret_cast<float*>(base + ws.pack), s, x_scale, fused);
+                                         reinterpret_cast<float*>(base + p_off), workspace_bytes - p_off, T,
+                                         comp == RTL_COMP_TENSOR ? nullptr : scale,
+                                         reinterpret_cast<float*>(base + ws.pack), s, x_scale);
     if (e != hipSuccess) return RTL_ERR_HIP;
     rtl::GemmArgs g{};
     g.fp8 = true;
@@ -445,7 +458,8 @@ rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float
     g.W = Wq;
     g.bias = static_cast<const uint16_t*>(bias);
     g.row_scale = comp == RTL_COMP_ROW ? scale : nullptr;
-    g.tensor_scale = comp == RTL_COMP_TENSOR ? fused : x_scale;   // dequantisation of the sparse product only
+    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), M, eps, scale, x_scale, fused);
+    else g.tensor_scale = x_scale;                       // dequantisation of the sparse product only
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
     g.T = T;

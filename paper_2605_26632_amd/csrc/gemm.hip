@@ -41,6 +41,7 @@
 #include <type_traits>
 #include <vector>
 #include "rtl_internal.h"
+#include "tensor_factor.h"
 
 namespace rtl {
 namespace {
@@ -178,11 +179,12 @@ __device__ __forceinline__ float mul_add_rn(float a, float b, float add) {
 // `tile`: index of this workgroup's output tile in the walk of the (M / BM) x (N / BN) tile grid.
 // PART: the workgroup covers the k blocks [kblk0, kblk0 + kblks) only and leaves its fp32 sums in plane `part` of
 // a.partials; the factors (MODE 0), the bias and the rounding are split_reduce_kernel's.
+// FOLDED: with a.rowsums set the TENSOR factor is a.folded.
 // WAVES_K > 1: the waves divide the contraction too. K group g of the WAVES_K groups of WAVES_M x WAVES_N
 // waves takes the k blocks g, g + WAVES_K, ... with operands and accumulators of its own, and the groups'
 // tiles are added up in LDS, in the order of g, when the loop is done.
 template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false,
-          bool D64 = false, int WAVES_K = 1, bool PART = false>
+          bool D64 = false, int WAVES_K = 1, bool PART = false, bool FOLDED = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, const int part = 0, const int kblk0 = 0,
                                           const int kblks = 0) {
     static_assert(!PART || WAVES_K == 1, "partial sums leave from the accumulators");
@@ -574,6 +576,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
         if (KT < (blocks + WAVES_K - 1) / WAVES_K) stage_barrier();   // no block in the last stage: the barrier only
     }
 
+    const bool own_factor = FOLDED && a.rowsums;
+    const bool has_tensor_scale = own_factor || a.tensor_scale;
+    auto tensor_scale = [&]() { return own_factor ? a.folded : (a.tensor_scale ? a.tensor_scale[0] : 1.0f); };
+
     if constexpr (WAVES_K > 1) {
         // ---- add the K groups up in LDS, factors, residual, bias, bf16, store --------------------------------
         wait_vmcnt_lgkm0<0>();
@@ -667,7 +673,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
             const int64_t row = m0 + (u * THREADS + (int)threadIdx.x) / CPR;
             f[u] = a.row_scale ? a.row_scale[min(row, a.M - 1)] : 1.0f;
         }
-        const float ts = a.tensor_scale ? a.tensor_scale[0] : 1.0f;
+        const float ts = tensor_scale();
         const bool wide_ok = ((reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) && (a.ldy % 8 == 0) && valid == 8;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
@@ -700,14 +706,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
         return;
     }
 
-    const float ts = a.tensor_scale ? a.tensor_scale[0] : 1.0f;
+    const float ts = tensor_scale();
 
     if constexpr (MODE == 1 && WAVES_K == 1) {
         // ---- LoRA tail (Alg. 1: Y <- Y_s + Y_r, accumulated on chip) --------------------------
         // The ROW / TENSOR factors belong to the sparse product only, so they are applied to the
         // accumulators first. Then Y_r = T L_A^T, T = X L_B^T (bf16 [M,64]), is added by four dense
         // matrix-instruction steps over the rank; SMFMAC and MFMA 32x32 share one accumulator layout.
-        if (a.row_scale || a.tensor_scale) {
+        if (a.row_scale || has_tensor_scale) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -788,7 +794,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
     auto finish = [&](float v, int64_t row, float bv) {
         if constexpr (MODE != 1) {
             if (a.row_scale) v *= a.row_scale[row];
-            if (a.tensor_scale) v *= ts;
+            if (has_tensor_scale) v *= ts;
         }
         if (a.bias) v += bv;
         return (uint16_t)f32_to_bf16_rne(v);
@@ -824,7 +830,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
             const uint32_t w = __builtin_amdgcn_perm(partner, own, sel);
             *reinterpret_cast<uint32_t*>(ep + rl * ROWB + rsel + (cl & ~1) * 2) = w;
         };
-        const bool scaled = MODE != 1 && (a.row_scale || a.tensor_scale);
+        const bool scaled = MODE != 1 && (a.row_scale || has_tensor_scale);
         if (!scaled && !a.bias) {
 #pragma unroll
             for (int j = 0; j < TN; ++j)
@@ -978,7 +984,20 @@ template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int WAVES_K, in
 __global__ __launch_bounds__(WAVES_M * WAVES_N * WAVES_K * 64) void gemm_split_kernel(const GemmArgs a) {
     const int total = (int)(((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN));
     const int xcd = (int)blockIdx.x % 8, local = (int)blockIdx.x / 8;
-    gemm_tile<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, !SPARSE, WAVES_K>(a, xcd_share_start(total, xcd) + local);
+    GemmArgs b = a;
+    if constexpr (SPARSE) {
+        if (a.rowsums) {
+            // TENSOR scope: every workgroup adds the rows' sums up for itself (a few KB from L2, 1 to 2 us), which
+            // spares the launch that would do only this (4.7 us and the gap before it)
+            const float sc = tensor_factor(a.rowsums, a.factor_rows, a.factor_eps);
+            b.folded = a.factor_mul ? a.factor_mul[0] * sc : sc;
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                a.factor_out[0] = sc;
+                if (a.factor_fused) a.factor_fused[0] = b.folded;
+            }
+        }
+    }
+    gemm_tile<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, !SPARSE, WAVES_K, false, SPARSE>(b, xcd_share_start(total, xcd) + local);
 }
 
 template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES, int MODE = 0, bool FP8 = false>
@@ -1309,7 +1328,24 @@ hipError_t launch_gemm(bool sparse, const GemmArgs& a_in, hipStream_t stream) {
     a.tail_tiles = plan.tail_tiles;
     a.rows_pad = kmajor_rows(a.M);
     a.t_plane = a.M * kLoraRank;
+    // The TENSOR factor: formed by the small-tile kernels themselves while that is cheaper than a launch (each of their
+    // workgroups reads all rows' sums: up to two passes of workgroups and 2048 rows), else by its own kernel. Whole call
+    // [M, 3072, 3072], own kernel -> folded, us: M = 37 12.2 -> 11.1, 512 21.9 -> 20.4, 1024 28.6 -> 27.6; [2000, 512, 1024] 15.4 -> 13.8; 4000 rows lost 0.2.
     const SplitChoice choice = pick_split(plan, a.M, a.N, a.K / (a.fp8 ? 128 : 64), !sparse, a.partials ? a.partial_bytes : 0);
+    if (a.rowsums) {
+        bool fold = sparse && choice.k_splits == 1 && choice.shape >= 0 && a.M <= 2048;
+        if (fold) {
+            const SplitShape& s = kSparseShapes[choice.shape];
+            fold = ((a.M + s.bm - 1) / s.bm) * ((a.N + s.bn - 1) / s.bn) <= 512;
+        }
+        if (!fold) {
+            const hipError_t e = launch_tensor_scale(a.rowsums, a.factor_rows, a.factor_eps, a.factor_out, stream, a.factor_mul,
+                                                     a.factor_fused);
+            if (e != hipSuccess) return e;
+            a.rowsums = nullptr;
+            a.tensor_scale = a.factor_fused ? a.factor_fused : a.factor_out;
+        }
+    }
     auto go = [&](auto k) { return decltype(k)::launch(a, stream); };
     if (choice.k_splits > 1) {
         a.k_splits = choice.k_splits;

@@ -17,6 +17,7 @@
 // the row mapping: with its heavier per-group arithmetic the block mapping measured the same.)
 #include "rtl_internal.h"
 #include "select.h"
+#include "tensor_factor.h"
 
 namespace rtl {
 namespace {
@@ -206,41 +207,14 @@ __global__ __launch_bounds__(kBlockWaves * 64) void sparsify_pack_block_kernel(
     }
 }
 
-// TENSOR scope: fold the per-row sums in a fixed order (fp64) and emit the single factor.
-// `fused` (nullable) receives the factor times mul[0] (the FP8 activation scale).
-__global__ __launch_bounds__(256) void tensor_scale_kernel(const float* __restrict__ rowsums,
-                                                           int64_t M, float eps,
-                                                           float* __restrict__ scale,
-                                                           const float* __restrict__ mul,
-                                                           float* __restrict__ fused) {
-    __shared__ double sn[256], sd[256];
-    double n = 0.0, d = 0.0;
-    const float2* rs = reinterpret_cast<const float2*>(rowsums);
-    int64_t r = threadIdx.x;
-    for (; r + 3 * 256 < M; r += 4 * 256) {     // four loads in flight; the additions keep the row order of a thread
-        const float2 v0 = rs[r], v1 = rs[r + 256], v2 = rs[r + 512], v3 = rs[r + 768];
-        n += (double)v0.x; d += (double)v0.y;
-        n += (double)v1.x; d += (double)v1.y;
-        n += (double)v2.x; d += (double)v2.y;
-        n += (double)v3.x; d += (double)v3.y;
-    }
-    for (; r < M; r += 256) {
-        const float2 v = rs[r];
-        n += (double)v.x;
-        d += (double)v.y;
-    }
-    sn[threadIdx.x] = n;
-    sd[threadIdx.x] = d;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            sn[threadIdx.x] += sn[threadIdx.x + s];
-            sd[threadIdx.x] += sd[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
+// TENSOR scope: fold the per-row sums and emit the single factor. `fused` (nullable) receives the factor times
+// mul[0] (the FP8 activation scale).
+__global__ __launch_bounds__(kFactorThreads) void tensor_scale_kernel(const float* __restrict__ rowsums, int64_t M,
+                                                                      float eps, float* __restrict__ scale,
+                                                                      const float* __restrict__ mul,
+                                                                      float* __restrict__ fused) {
+    const float sc = tensor_factor(rowsums, M, eps);
     if (threadIdx.x == 0) {
-        const float sc = (float)sqrt(sn[0] / (sd[0] + (double)eps));
         scale[0] = sc;
         if (fused) fused[0] = mul[0] * sc;
     }
@@ -305,8 +279,7 @@ hipError_t launch_operand_to_kmajor(const uint16_t* vals, const uint8_t* meta, i
 template <bool FP8>
 static hipError_t launch_pack_any(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp,
                                   float eps, void* vals, uint8_t* meta, uint8_t* vals_km, uint8_t* meta_km,
-                                  float* scale, float* rowsums, const float* x_scale, float* fused_scale,
-                                  hipStream_t stream) {
+                                  float* scale, float* rowsums, const float* x_scale, hipStream_t stream) {
     const int64_t Mpad = kmajor_rows(M);
     if constexpr (!FP8) {
         // only the k-major outputs, nothing summed along a row: the block mapping (see its kernel)
@@ -364,8 +337,7 @@ static hipError_t launch_pack_any(const uint16_t* X, int64_t M, int64_t K, int64
         case RTL_COMP_TENSOR:
             hipLaunchKernelGGL((sparsify_pack_kernel<RTL_COMP_TENSOR, FP8>), grid, block, 0, stream, X, M,
                                (int)K, ldx, eps, vals, meta, vals_km, meta_km, Mpad, scale, rowsums, x_scale, parts);
-            hipLaunchKernelGGL(tensor_scale_kernel, dim3(1), dim3(256), 0, stream, rowsums, M, eps,
-                               scale, x_scale, fused_scale);
+            if (scale) return launch_tensor_scale(rowsums, M, eps, scale, stream);
             break;
     }
     return hipGetLastError();
@@ -375,20 +347,20 @@ hipError_t launch_sparsify_pack(const uint16_t* X, int64_t M, int64_t K, int64_t
                                 float eps, uint16_t* vals, uint8_t* meta, uint8_t* vals_km,
                                 uint8_t* meta_km, float* scale, float* rowsums, hipStream_t stream) {
     return launch_pack_any<false>(X, M, K, ldx, comp, eps, vals, meta, vals_km, meta_km, scale, rowsums,
-                                  nullptr, nullptr, stream);
+                                  nullptr, stream);
 }
 
 hipError_t launch_sparsify_pack_fp8(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp,
                                     float eps, const float* x_scale, uint8_t* vals8, uint8_t* meta,
                                     uint8_t* vals_km, uint8_t* meta_km, float* scale, float* rowsums,
-                                    float* fused_scale, hipStream_t stream) {
+                                    hipStream_t stream) {
     return launch_pack_any<true>(X, M, K, ldx, comp, eps, vals8, meta, vals_km, meta_km, scale, rowsums,
-                                 x_scale, fused_scale, stream);
+                                 x_scale, stream);
 }
 
 hipError_t launch_tensor_scale(const float* rowsums, int64_t M, float eps, float* scale, hipStream_t stream,
                                const float* mul, float* fused) {
-    hipLaunchKernelGGL(tensor_scale_kernel, dim3(1), dim3(256), 0, stream, rowsums, M, eps, scale, mul, fused);
+    hipLaunchKernelGGL(tensor_scale_kernel, dim3(1), dim3(kFactorThreads), 0, stream, rowsums, M, eps, scale, mul, fused);
     return hipGetLastError();
 }
 

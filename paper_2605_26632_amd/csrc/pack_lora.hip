@@ -319,8 +319,7 @@ size_t pack_down_scratch_min(int64_t M, int64_t K) { return pack_down_bytes(M, p
 
 hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps,
                             const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, float* scratch,
-                            size_t scratch_bytes, uint16_t* T, float* scale, float* rowsums, hipStream_t stream, const float* x_scale,
-                            float* fused_scale) {
+                            size_t scratch_bytes, uint16_t* T, float* scale, float* rowsums, hipStream_t stream, const float* x_scale) {
     int per = 1;
     const size_t fit = scratch_bytes / pack_down_bytes(M, 1);
     const int splits = pack_down_ranges(M, K, &per, fit > kMaxRanges ? kMaxRanges : (int)fit);
@@ -349,9 +348,7 @@ hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(lora_reduce_kernel, dim3((unsigned)((M + 3) / 4)), dim3(kReduceWaves * 64), 0, stream, partials,
                        splits, M, T, sums, (int)comp, eps, scale, rowsums);
-    e = hipGetLastError();
-    if (e != hipSuccess || comp != RTL_COMP_TENSOR) return e;
-    return launch_tensor_scale(rowsums, M, eps, scale, stream, x_scale, fused_scale);
+    return hipGetLastError();
 }
 
 }  // namespace rtl

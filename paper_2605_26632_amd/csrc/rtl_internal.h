@@ -30,19 +30,18 @@ inline size_t kmajor_val_bytes(int64_t M, int64_t K, size_t val_bytes) {
 // ---- sparsify + pack (pack.hip) -------------------------------------------------------------
 // Launches the select/compensate/compress sweep. The canonical outputs (`vals`, `meta`) and the
 // k-major ones (`vals_km`, `meta_km`, need K % 64 == 0) are each optional; `rowsums` ([M][2] fp32)
-// is only touched for RTL_COMP_TENSOR. Returns the HIP launch status.
+// is only touched for RTL_COMP_TENSOR; with `scale` NULL that scope stops there and the factor is left to
+// launch_gemm (GemmArgs::rowsums). Returns the HIP launch status.
 hipError_t launch_sparsify_pack(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp,
                                 float eps, uint16_t* vals, uint8_t* meta, uint8_t* vals_km,
                                 uint8_t* meta_km, float* scale, float* rowsums, hipStream_t stream);
 // FP8 form (implementation details, "orthogonal validation with FP8 quantization"): kept values
 // leave as E4M3 codes of (s * x) / x_scale[0] (vals8 [M,K/2] bytes); `meta_km` then uses the 16-byte
-// records and `vals_km` 128-k blocks (need K % 128 == 0). `fused_scale` (nullable, [1]) receives
-// x_scale[0] times the TENSOR factor (TENSOR scope only), the single multiplier the GEMM epilogue
-// then needs.
+// records and `vals_km` 128-k blocks (need K % 128 == 0).
 hipError_t launch_sparsify_pack_fp8(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp,
                                     float eps, const float* x_scale, uint8_t* vals8, uint8_t* meta,
                                     uint8_t* vals_km, uint8_t* meta_km, float* scale, float* rowsums,
-                                    float* fused_scale, hipStream_t stream);
+                                    hipStream_t stream);
 // Direct cast of a bf16 matrix to E4M3 codes (round to nearest even, saturating), cols % 8 == 0.
 hipError_t launch_quantize_fp8(const uint16_t* W, int64_t rows, int64_t cols, int64_t ld, uint8_t* Wq,
                                int64_t ldq, hipStream_t stream);
@@ -74,6 +73,15 @@ struct GemmArgs {
     bool fp8;               // sparse only: E4M3 operands, K % 128 == 0, 16-byte metadata records
     // optional scratch for fp32 partial planes (16-byte aligned): with at least gemm_partial_bytes launch_gemm may
     // split the contraction over workgroups, with less it splits less or not at all
+    // TENSOR scope whose factor is still to be formed: the rows' sums [factor_rows][2]; the factor goes to
+    // factor_out[0], times factor_mul[0] (nullable) to factor_fused[0], and is used in place of tensor_scale
+    const float* rowsums;
+    int64_t factor_rows;
+    float factor_eps;
+    float* factor_out;
+    const float* factor_mul;
+    float* factor_fused;
+    float folded;           // filled in by the kernels that form the factor themselves
     float* partials;
     size_t partial_bytes;
     int64_t part_pitch;     // filled in by launch_gemm
@@ -97,16 +105,15 @@ constexpr int kLoraRank = 64;
 // row sums of squares, into `scratch` (scratch_bytes >= pack_down_scratch_min(M, K); the number of ranges is
 // the preferred one with pack_down_scratch_bytes(M, K)); a second small kernel adds the ranges up in a fixed
 // order into the two bf16 planes of T ([2][M][64]: hi, lo), the ROW factors `scale` [M] or
-// the TENSOR row sums `rowsums` [M][2], from which launch_tensor_scale then forms scale[0].
+// the TENSOR row sums `rowsums` [M][2], from which launch_gemm forms the factor (GemmArgs::rowsums).
 size_t pack_down_scratch_bytes(int64_t M, int64_t K);
 size_t pack_down_scratch_min(int64_t M, int64_t K);
 hipError_t prepare_pack_lora_kernels();
 hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps,
                             const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, float* scratch,
                             size_t scratch_bytes, uint16_t* T, float* scale, float* rowsums, hipStream_t stream,
-                            const float* x_scale = nullptr, float* fused_scale = nullptr);
-// (x_scale set: FP8 form: kept values as E4M3 codes of (s x) / x_scale[0] in the FP8 k-major layout, K % 128 == 0;
-//  fused_scale [1] then receives x_scale[0] times the TENSOR factor, TENSOR scope only.)
+                            const float* x_scale = nullptr);
+// (x_scale set: FP8 form: kept values as E4M3 codes of (s x) / x_scale[0] in the FP8 k-major layout, K % 128 == 0.)
 // TENSOR scope: the single factor from the per-row sums [M][2] (fixed order, fp64), into scale[0]; `fused`
 // (nullable) receives scale[0] * mul[0].
 hipError_t launch_tensor_scale(const float* rowsums, int64_t M, float eps, float* scale, hipStream_t stream,

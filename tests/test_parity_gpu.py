@@ -1252,3 +1252,22 @@ def test_contraction_split_over_workgroups(M, N, K):
         check_y_fp8(rtl.sparse_linear_fp8(X, Wq, xs, bias=b)[sel], r, Wn, f, bias=bb)
         r = oracle.sparse_lora_linear_fp8_oracle(Xs, Wn, f, synth.bits(LA), synth.bits(LB), bias=bb, scope=oracle.GROUP)
         assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b)[sel]), r["Y"]) <= Y_TOL
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 8, 128), (257, 1000, 512), (300, 3072, 3072), (1029, 640, 1152), (4097, 96, 256), (200, 3072, 12288)])
+def test_tensor_factor_formed_by_the_tile_loop(M, N, K):
+    """TENSOR scope: the factor is formed inside the small-tile kernels, by its own kernel elsewhere; either way the
+    call must equal, bit for bit, the product with the factor rtl_sparsify_pack hands out."""
+    X = synth.activations("laplace_outlier", M, K, seed=M, device=DEV)
+    W = synth.weights(N, K, seed=N, device=DEV)
+    vals, meta, scale = rtl.sparsify_pack(X, comp=rtl.COMP_TENSOR)
+    assert torch.equal(rtl.packed_linear(vals, meta, W, tensor_scale=scale), rtl.sparse_linear(X, W, comp=rtl.COMP_TENSOR))
+    LA, LB = synth.lora(N, K, 64, seed=5, device=DEV, std_a=0.1, std_b=0.1)
+    xs, Wq = fp8_scale(X), rtl.quantize_fp8(W)
+    Xb, Wb, Wn, f = synth.bits(X), synth.bits(W), Wq.cpu().numpy(), float(xs.item())
+    ref = oracle.sparse_lora_linear_oracle(Xb, Wb, synth.bits(LA), synth.bits(LB), scope=oracle.TENSOR)["Y"]
+    check_y(rtl.sparse_lora_linear(X, W, LA, LB, comp=rtl.COMP_TENSOR), ref)
+    r = oracle.sparse_linear_fp8_oracle(Xb, Wn, f, scope=oracle.TENSOR)
+    assert rel_max_err(y_to_np(rtl.sparse_linear_fp8(X, Wq, xs, comp=rtl.COMP_TENSOR)), r["Y"]) <= Y_TOL
+    r = oracle.sparse_lora_linear_fp8_oracle(Xb, Wn, f, synth.bits(LA), synth.bits(LB), scope=oracle.TENSOR)
+    assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, comp=rtl.COMP_TENSOR)), r["Y"]) <= Y_TOL
