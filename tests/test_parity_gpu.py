@@ -1271,3 +1271,36 @@ def test_tensor_factor_formed_by_the_tile_loop(M, N, K):
     assert rel_max_err(y_to_np(rtl.sparse_linear_fp8(X, Wq, xs, comp=rtl.COMP_TENSOR)), r["Y"]) <= Y_TOL
     r = oracle.sparse_lora_linear_fp8_oracle(Xb, Wn, f, synth.bits(LA), synth.bits(LB), scope=oracle.TENSOR)
     assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, comp=rtl.COMP_TENSOR)), r["Y"]) <= Y_TOL
+
+
+def test_split_contraction_in_a_captured_graph():
+    """The partial planes are written and added up anew by every replay (inputs changed between replays)."""
+    M, N, K = 200, 3072, 12288
+    X = synth.activations("gelu", M, K, seed=1, device=DEV)
+    W = synth.weights(N, K, seed=2, device=DEV)
+    Y1, Y2 = torch.empty((M, N), dtype=torch.bfloat16, device=DEV), torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    ws1 = torch.empty(rtl.sparse_linear_workspace(M, N, K, rtl.COMP_TENSOR) + 256, dtype=torch.uint8, device=DEV)
+    ws2 = torch.empty(int(rtl.lib().rtl_dense_linear_workspace(M, N, K)), dtype=torch.uint8, device=DEV)
+
+    def run():
+        rtl.sparse_linear(X, W, comp=rtl.COMP_TENSOR, out=Y1, ws=ws1)
+        rtl.dense_linear(X, W, out=Y2, ws=ws2)
+
+    rtl.init()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        run()
+    for seed in (5, 6, 7):
+        X.copy_(synth.activations("gelu", M, K, seed=seed, device=DEV))
+        Y1.zero_()
+        Y2.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        got = Y1.clone(), Y2.clone()
+        run()
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], Y1) and torch.equal(got[1], Y2)
+        rows = sampled_rows(M, 6, seed=seed)
+        sel = torch.from_numpy(rows).to(DEV)
+        check_y(got[1][sel], oracle.dense_linear_oracle(synth.bits(X[sel]), synth.bits(W)))
