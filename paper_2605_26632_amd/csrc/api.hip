@@ -79,14 +79,20 @@ SparseWs sparse_ws(int64_t M, int64_t K, rtl_comp comp, size_t val_bytes = 2) {
     return w;
 }
 
-// Hands what lies behind the first `used` bytes of a workspace to the tile loop. Never more than the fixed
-// scratch of rtl_sparse_linear_static would leave, so that every entry point splits a contraction alike.
-void give_partials(rtl::GemmArgs& g, uint8_t* base, size_t used, size_t bytes) {
+// Most bytes of partial planes a call on an [M, K] activation may take: what rtl_sparse_linear_static has left of its
+// fixed scratch, counted for the scope with the largest mandatory part. The queries and the calls of every sparse entry
+// point choose the split with this room, whatever else their own workspace holds, so that on a workspace of the queried
+// size all of them split a contraction alike (same bits) and alike for every scope.
+size_t planes_room(int64_t M, int64_t K, size_t val_bytes = 2) {
+    const size_t used = sparse_ws(M, K, RTL_COMP_TENSOR, val_bytes).total;
+    return used < (size_t)RTL_STATIC_SCRATCH_BYTES ? (size_t)RTL_STATIC_SCRATCH_BYTES - used : 0;
+}
+// Hands what lies behind the first `used` bytes of a workspace, `room` bytes at most, to the tile loop.
+void give_partials(rtl::GemmArgs& g, uint8_t* base, size_t used, size_t bytes, size_t room) {
     used = round_up(used, 256);
-    const size_t end = bytes < (size_t)RTL_STATIC_SCRATCH_BYTES ? bytes : (size_t)RTL_STATIC_SCRATCH_BYTES;
-    if (!base || !aligned(base, 16) || end <= used) return;
+    if (!base || !aligned(base, 16) || bytes <= used) return;
     g.partials = reinterpret_cast<float*>(base + used);
-    g.partial_bytes = end - used;
+    g.partial_bytes = bytes - used < room ? bytes - used : room;
 }
 // TENSOR scope: leaves the factor of the sums at `rowsums` to the tile loop, which puts it in scale[0] (and, with an
 // FP8 activation scale, their product in fused[0]).
@@ -99,9 +105,9 @@ void give_factor(rtl::GemmArgs& g, const float* rowsums, int64_t M, float eps, f
     g.factor_fused = fused;
 }
 // Size of a workspace whose mandatory part is `used` bytes.
-size_t with_partials(size_t used, bool sparse, bool fp8, int64_t M, int64_t N, int64_t K) {
-    const size_t planes = rtl::gemm_partial_bytes(sparse, fp8, M, N, K), at = round_up(used, 256);
-    return planes && at + planes <= (size_t)RTL_STATIC_SCRATCH_BYTES ? at + planes : used;
+size_t with_partials(size_t used, size_t room, bool sparse, bool fp8, int64_t M, int64_t N, int64_t K) {
+    const size_t planes = rtl::gemm_partial_bytes(sparse, fp8, M, N, K, room);
+    return planes ? round_up(used, 256) + planes : used;
 }
 
 }  // namespace
@@ -178,7 +184,7 @@ static size_t packed_ws(int64_t M, int64_t K) {
 }
 size_t rtl_packed_linear_workspace(int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    return with_partials(packed_ws(M, K), true, false, M, N, K);
+    return with_partials(packed_ws(M, K), planes_room(M, K), true, false, M, N, K);
 }
 
 rtl_status rtl_packed_linear(const void* vals, const void* meta, const float* row_scale,
@@ -208,14 +214,14 @@ rtl_status rtl_packed_linear(const void* vals, const void* meta, const float* ro
     g.tensor_scale = tensor_scale;
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
-    give_partials(g, static_cast<uint8_t*>(workspace), need, workspace_bytes);
+    give_partials(g, static_cast<uint8_t*>(workspace), need, workspace_bytes, planes_room(M, K));
     e = rtl::launch_gemm(true, g, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
 
 size_t rtl_sparse_linear_workspace(int64_t M, int64_t N, int64_t K, rtl_comp comp) {
     if (M <= 0 || N <= 0 || K <= 0 || !comp_ok(comp)) return 0;
-    return with_partials(sparse_ws(M, K, comp).total, true, false, M, N, K);
+    return with_partials(sparse_ws(M, K, comp).total, planes_room(M, K), true, false, M, N, K);
 }
 
 // Pack sweep + tile loop of rtl_sparse_linear on an already validated problem, with `base` the
@@ -238,7 +244,7 @@ static rtl_status sparse_linear_on(uint8_t* base, size_t bytes, const SparseWs& 
     if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), M, eps, scale, nullptr, nullptr);
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
-    give_partials(g, base, ws.total, bytes);
+    give_partials(g, base, ws.total, bytes, planes_room(M, K));
     e = rtl::launch_gemm(true, g, s);
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
@@ -280,7 +286,8 @@ rtl_status rtl_sparse_linear_static(const void* X, const void* W, const void* bi
 size_t rtl_sparse_lora_linear_workspace(int64_t M, int64_t N, int64_t K, int64_t R, rtl_comp comp) {
     if (M <= 0 || N <= 0 || K <= 0 || R != rtl::kLoraRank || !comp_ok(comp)) return 0;
     return with_partials(sparse_ws(M, K, comp).total + round_up((size_t)M * rtl::kLoraRank * 4, 256) +
-                             round_up(rtl::pack_down_scratch_bytes(M, K), 256), true, false, M, N, K);
+                             round_up(rtl::pack_down_scratch_bytes(M, K), 256),
+                         planes_room(M, K), true, false, M, N, K);
 }
 
 rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, const void* LB,
@@ -325,7 +332,7 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
     g.T = T;
     g.LA = static_cast<const uint16_t*>(LA);
     g.ldla = ldla;
-    give_partials(g, base, p_off + round_up(rtl::pack_down_scratch_bytes(M, K), 256), workspace_bytes);
+    give_partials(g, base, p_off + round_up(rtl::pack_down_scratch_bytes(M, K), 256), workspace_bytes, planes_room(M, K));
     e = rtl::launch_gemm(true, g, s);
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
@@ -374,7 +381,7 @@ rtl_status rtl_sparsify_pack_fp8(const void* X, int64_t M, int64_t K, int64_t ld
 
 size_t rtl_sparse_linear_fp8_workspace(int64_t M, int64_t N, int64_t K, rtl_comp comp) {
     if (M <= 0 || N <= 0 || K <= 0 || !comp_ok(comp)) return 0;
-    return with_partials(sparse_ws(M, K, comp, 1).total, true, true, M, N, K);
+    return with_partials(sparse_ws(M, K, comp, 1).total, planes_room(M, K, 1), true, true, M, N, K);
 }
 
 rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_scale, const void* bias,
@@ -409,7 +416,7 @@ rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_s
     else g.tensor_scale = x_scale;                       // dequantisation rides on the epilogue
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
-    give_partials(g, base, ws.total, workspace_bytes);
+    give_partials(g, base, ws.total, workspace_bytes, planes_room(M, K, 1));
     e = rtl::launch_gemm(true, g, s);
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
@@ -418,7 +425,8 @@ rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_s
 size_t rtl_sparse_lora_linear_fp8_workspace(int64_t M, int64_t N, int64_t K, int64_t R, rtl_comp comp) {
     if (M <= 0 || N <= 0 || K <= 0 || R != rtl::kLoraRank || !comp_ok(comp)) return 0;
     return with_partials(sparse_ws(M, K, comp, 1).total + round_up((size_t)M * rtl::kLoraRank * 4, 256) +
-                             round_up(rtl::pack_down_scratch_bytes(M, K), 256), true, true, M, N, K);
+                             round_up(rtl::pack_down_scratch_bytes(M, K), 256),
+                         planes_room(M, K, 1), true, true, M, N, K);
 }
 
 rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float* x_scale, const void* LA,
@@ -465,7 +473,7 @@ rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float
     g.T = T;
     g.LA = static_cast<const uint16_t*>(LA);
     g.ldla = ldla;
-    give_partials(g, base, p_off + round_up(rtl::pack_down_scratch_bytes(M, K), 256), workspace_bytes);
+    give_partials(g, base, p_off + round_up(rtl::pack_down_scratch_bytes(M, K), 256), workspace_bytes, planes_room(M, K, 1));
     e = rtl::launch_gemm(true, g, s);
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
@@ -525,7 +533,7 @@ rtl_status rtl_diag_tile_plan(int64_t M, int64_t N, int dense, int64_t* plan) {
 
 size_t rtl_dense_linear_workspace(int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    return with_partials(0, false, false, M, N, K);
+    return with_partials(0, (size_t)RTL_STATIC_SCRATCH_BYTES, false, false, M, N, K);
 }
 
 rtl_status rtl_dense_linear(const void* X, const void* W, const void* bias, void* Y, int64_t M,
@@ -536,7 +544,7 @@ rtl_status rtl_dense_linear(const void* X, const void* W, const void* bias, void
     if (bias && !aligned(bias, 2)) return RTL_ERR_ALIGN;
     RTL_REQUIRE_DEVICE();
     rtl::GemmArgs g{};
-    give_partials(g, static_cast<uint8_t*>(workspace), 0, workspace_bytes);      // none of it is mandatory
+    give_partials(g, static_cast<uint8_t*>(workspace), 0, workspace_bytes, (size_t)RTL_STATIC_SCRATCH_BYTES);   // none of it is mandatory
     g.A = X;
     g.W = W;
     g.bias = static_cast<const uint16_t*>(bias);

@@ -1250,11 +1250,12 @@ static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_
     return pick;
 }
 
-// Preferred size of the partial planes for an [M, N, K] problem (0 where the contraction is not split over workgroups).
-size_t gemm_partial_bytes(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K) {
+// Size of the partial planes of the choice made with `room` bytes (0 where the contraction is not split over workgroups).
+// launch_gemm makes the same choice with any room from this size up to `room`.
+size_t gemm_partial_bytes(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K, size_t room) {
     const int64_t blocks = K / (fp8 ? 128 : 64);
     if (blocks < 32 || ((M + 255) / 256) * ((N + 127) / 128) > 128) return 0;       // (the bound of the loop above at two splits)
-    const SplitChoice c = pick_split(plan_for(M, N, !sparse), M, N, blocks, !sparse, ~(size_t)0);
+    const SplitChoice c = pick_split(plan_for(M, N, !sparse), M, N, blocks, !sparse, room);
     return c.k_splits > 1 ? (size_t)c.k_splits * (size_t)M * (size_t)part_pitch(N) * 4 : 0;
 }
 

@@ -71,8 +71,6 @@ struct GemmArgs {
     int64_t m_split;        // rows [0, m_split) are cut into body tiles, rows [m_split, M) into 256 x 128 tail tiles
     int body_tiles, tail_tiles;
     bool fp8;               // sparse only: E4M3 operands, K % 128 == 0, 16-byte metadata records
-    // optional scratch for fp32 partial planes (16-byte aligned): with at least gemm_partial_bytes launch_gemm may
-    // split the contraction over workgroups, with less it splits less or not at all
     // TENSOR scope whose factor is still to be formed: the rows' sums [factor_rows][2]; the factor goes to
     // factor_out[0], times factor_mul[0] (nullable) to factor_fused[0], and is used in place of tensor_scale
     const float* rowsums;
@@ -82,12 +80,15 @@ struct GemmArgs {
     const float* factor_mul;
     float* factor_fused;
     float folded;           // filled in by the kernels that form the factor themselves
+    // optional scratch for fp32 partial planes (16-byte aligned): room in which launch_gemm may split the contraction
+    // over workgroups; with less than gemm_partial_bytes it splits less or not at all
     float* partials;
     size_t partial_bytes;
     int64_t part_pitch;     // filled in by launch_gemm
     int k_splits;
 };
-size_t gemm_partial_bytes(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K);
+// Bytes of partial planes launch_gemm would use of `room` bytes.
+size_t gemm_partial_bytes(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K, size_t room);
 // One-time set-up per device (rtl_init, or the first entry-point call): raises the dynamic-LDS limit
 // of every tile-loop kernel and makes the runtime load both code objects, so that later launches
 // are plain kernel nodes (HIP-graph capture needs no warm-up call).

@@ -174,3 +174,39 @@ def test_tile_plan_covers_the_output_exactly():
     assert rtl.lib().rtl_diag_tile_plan(0, 5, 0, None) == 2 and rtl.lib().rtl_diag_tile_plan(5, 5, 0, None) == 1
     # the headline shape keeps its one-round plan: 256 tiles of 256 x 192, no tail
     assert rtl.diag_tile_plan(4096, 3072) == dict(body_width=192, body_rows=4096, body_tiles=256, tail_tiles=0)
+
+
+def split_planes(query, M, N, K, *rest):
+    """Bytes of partial planes in a linear's queried workspace: at N = 2^20 no contraction is split, so that query
+    is the mandatory part alone."""
+    return int(query(M, N, K, *rest)) - int(query(M, 1 << 20, K, *rest))
+
+
+# The first five only split with fewer parts than the preferred number, because the room ends before: by 64 MiB in all
+# for the entry point on the fixed scratch, whatever the other entry points' own mandatory part leaves.
+SPLIT_SHAPES = [(2304, 1024, 15360), (2816, 512, 12288), (2304, 512, 15360), (1792, 1536, 18432), (2752, 512, 12288),
+                (200, 3072, 12288), (333, 3072, 12288), (700, 3071, 12352), (140, 5504, 15360)]
+
+
+def test_every_entry_point_plans_the_same_contraction_split():
+    """The queries of all sparse entry points of an operand type ask for the same partial planes in every scope, and
+    for planes wherever the entry point on the fixed scratch, which hands over all it has left, would split."""
+    L = rtl.lib()
+    limit = rtl.STATIC_SCRATCH_BYTES
+    grid = [(M, N, K) for M in range(64, 4097, 448) for N in (256, 640, 1024, 2100, 3072, 5504) for K in (4096, 9216, 12288, 15360)]
+    for M, N, K in SPLIT_SHAPES + [(3008, 1024, 12288), (2752, 1280, 12288)] + grid:
+        planes = {split_planes(L.rtl_packed_linear_workspace, M, N, K)}
+        fp8 = set()
+        for comp in range(4):
+            planes.add(split_planes(L.rtl_sparse_linear_workspace, M, N, K, comp))
+            planes.add(split_planes(L.rtl_sparse_lora_linear_workspace, M, N, K, 64, comp))
+            if L.rtl_sparse_linear_workspace(M, 1 << 20, K, comp) <= limit:
+                assert L.rtl_sparse_linear_workspace(M, N, K, comp) <= limit      # what the fixed scratch takes
+            if K % 128 == 0:
+                fp8.add(split_planes(L.rtl_sparse_linear_fp8_workspace, M, N, K, comp))
+                fp8.add(split_planes(L.rtl_sparse_lora_linear_fp8_workspace, M, N, K, 64, comp))
+        assert len(planes) == 1 and len(fp8) <= 1, (M, N, K, planes, fp8)
+        for p in planes | fp8:
+            assert p == 0 or (p >= 2 * M * N * 4 and p % (M * ((N + 7) // 8 * 8) * 4) == 0)
+        if (M, N, K) in SPLIT_SHAPES:
+            assert min(planes) > 0, (M, N, K)

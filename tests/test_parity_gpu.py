@@ -1254,6 +1254,26 @@ def test_contraction_split_over_workgroups(M, N, K):
         assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b)[sel]), r["Y"]) <= Y_TOL
 
 
+@pytest.mark.parametrize("M,N,K", [(2304, 1024, 15360), (2752, 512, 12288), (2752, 1280, 12288), (333, 3071, 12288)])
+def test_split_choice_is_the_same_for_every_entry_point(M, N, K):
+    """Bit for bit: the call on a queried workspace, on a larger one, on the fixed scratch, and the packed operand, in
+    GROUP and TENSOR scope; LoRA with a zero L_A in GROUP scope. Up to the last shape the preferred number of parts does not
+    fit beside the compressed operand (the entry points once gave up or reduced the split there each in its own way)."""
+    X = synth.activations("gelu", M, K, seed=M, device=DEV)
+    W = synth.weights(N, K, seed=N, device=DEV)
+    b = synth.bias(N, seed=4, device=DEV, std=0.5)
+    LA, LB = synth.lora(N, K, 64, seed=5, device=DEV, std_a=0.05, std_b=0.05)
+    for comp in (rtl.COMP_GROUP, rtl.COMP_TENSOR):
+        Y = rtl.sparse_linear(X, W, bias=b, comp=comp)
+        ws = torch.empty(rtl.sparse_linear_workspace(M, N, K, comp) + (96 << 20), dtype=torch.uint8, device=DEV)
+        assert torch.equal(rtl.sparse_linear(X, W, bias=b, comp=comp, ws=ws), Y)
+        assert torch.equal(rtl.sparse_linear_static(X, W, torch.empty_like(Y), bias=b, comp=comp), Y)
+        vals, meta, scale = rtl.sparsify_pack(X, comp=comp)
+        assert torch.equal(rtl.packed_linear(vals, meta, W, bias=b, tensor_scale=scale), Y)
+        if comp == rtl.COMP_GROUP:
+            assert torch.equal(rtl.sparse_lora_linear(X, W, torch.zeros_like(LA), LB, bias=b, comp=comp), Y)
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 8, 128), (257, 1000, 512), (300, 3072, 3072), (1029, 640, 1152), (4097, 96, 256), (200, 3072, 12288)])
 def test_tensor_factor_formed_by_the_tile_loop(M, N, K):
     """TENSOR scope: the factor is formed inside the small-tile kernels, by its own kernel elsewhere; either way the
