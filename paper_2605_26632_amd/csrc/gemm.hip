@@ -1182,23 +1182,29 @@ void tile_plan(int64_t M, int64_t N, bool dense, int64_t out[4]) {
 // ---- small tiles -------------------------------------------------------------------------------
 // Shapes of gemm_split_kernel with what one workgroup takes alone on its compute unit: `fixed` us (prologue,
 // reduction of the K groups, epilogue) plus `block` us per k block, both measured ([1..4096, 3072 | 12288,
-// 3072 | 12288], 250 points per operand kind); `resident` workgroups fit a unit's LDS at a time.
+// 3072 | 12288], 250 points per operand kind).
 struct SplitShape {
-    int bm, bn, resident;
+    int bm, bn;
     double fixed, block;
 };
 constexpr SplitShape kSparseShapes[] = {
-    {32, 32, 1, 1.2, 0.087}, {64, 32, 1, 1.9, 0.108}, {64, 64, 2, 2.4, 0.153}, {128, 64, 1, 2.3, 0.19}, {128, 128, 2, 2.8, 0.30}};
+    {32, 32, 1.2, 0.087}, {64, 32, 1.9, 0.108}, {64, 64, 2.4, 0.153}, {128, 64, 2.3, 0.19}, {128, 128, 2.8, 0.30}};
 constexpr SplitShape kDenseShapes[] = {
-    {32, 32, 1, 1.2, 0.10}, {64, 32, 1, 1.8, 0.135}, {64, 64, 1, 1.0, 0.18}, {128, 64, 1, 2.5, 0.262}, {128, 128, 1, 3.8, 0.36},
-    {256, 128, 1, 4.0, 0.48}};
+    {32, 32, 1.2, 0.10}, {64, 32, 1.8, 0.135}, {64, 64, 1.0, 0.18}, {128, 64, 2.5, 0.262}, {128, 128, 3.8, 0.36},
+    {256, 128, 4.0, 0.48}};
 
-// Index of the small shape that should serve the problem, or -1 for the 256-row plan. Times are estimated
-// from the measured constants: a small shape needs ceil(tiles / 256) passes over the 256 compute units (two
-// resident workgroups overlap a little: 0.92; dense passes slow each other down: 1.1). The 256-row plan is its simulated schedule times the time per
-// KB of a stage, which grows from 10.7 ns (dense 15.5: both operands row-major) while at most 96 units work
-// to 17.2 (21) when all do and share the L2s and the power budget. Against the best of all variants, measured,
-// the choice was within 3 % at 98 of 110 random shapes ([1..6000, 64..21504, 128..15360]) and within 8 % at all but one.
+// How the problem should run. Times are estimated from the measured constants: a small shape needs ceil(tiles / 256)
+// passes over the 256 compute units; with more than one, all units pull operands all the time and slow each other down
+// beyond the constants, which were taken one workgroup to a unit (factor 1.1; dense 128 x 128 1.15 with two passes, 1.3
+// with more). The 256-row plan is its simulated schedule times the time per KB of a stage, which grows from 10.7 ns (dense
+// 15.5: both operands row-major) while at most 96 units work to 17.2 (21) when all do and share the L2s and the power
+// budget. One table serves every operand kind: FP8 and LoRA calls rank the same way (LoRA's residual, 5 us a tile of the
+// 256-row plan, is left out), and LoRA without its residual then sums like the plain call.
+// Against every variant forced one by one on 3130 shapes ([1..6000, 512..21504, 512..15360], all six kinds of call, 1320 of
+// them drawn where several passes compete with the 256-row plan): 1.2 % slower than the best on average, more than 2 %
+// slower than the 256-row plan at 11. With the factors at 0.92 (sparse 64 x 64 and 128 x 128), 1.0 and 1.1 (dense) it was
+// 118, by up to 1.29x (128 x 128 tiles in several passes: sparse [1408, 14368, 11904] 303 -> 392 us, LoRA [639, 10400, 11776]
+// 137 -> 169); above 2048 rows, 128 x 128 tiles in several passes won more than 3 % at 2 of 220.
 struct SplitChoice {
     int shape;       // index of the small shape, or -1 for the 256-row plan
     int k_splits;    // > 1: gemm_part_kernel on the 128 x 128 (part_256 false) or 256 x 128 tile
@@ -1223,7 +1229,8 @@ static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_
             if (tiles > 96) block += 0.0026 * (double)(tiles - 96);
         }
         const int64_t passes = (tiles + 255) / 256;
-        const double several = s.resident > 1 ? 0.92 : (dense ? 1.1 : 1.0);
+        if (passes > 1 && s.bm >= 128 && s.bn >= 128 && M > 2048) continue;
+        const double several = !(dense && s.bm >= 128 && s.bn >= 128) ? 1.1 : (passes > 2 ? 1.3 : 1.15);
         const double t = (double)passes * (s.fixed + (double)blocks * block) * (passes > 1 ? several : 1.0);
         if (t < best) {
             best = t;
@@ -1257,6 +1264,13 @@ size_t gemm_partial_bytes(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K
     if (blocks < 32 || ((M + 255) / 256) * ((N + 127) / 128) > 128) return 0;       // (the bound of the loop above at two splits)
     const SplitChoice c = pick_split(plan_for(M, N, !sparse), M, N, blocks, !sparse, room);
     return c.k_splits > 1 ? (size_t)c.k_splits * (size_t)M * (size_t)part_pitch(N) * 4 : 0;
+}
+
+void gemm_choice(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K, size_t room, int out[3]) {
+    const SplitChoice c = pick_split(plan_for(M, N, !sparse), M, N, K / (fp8 ? 128 : 64), !sparse, room);
+    out[0] = c.k_splits > 1 ? -1 : c.shape;
+    out[1] = c.k_splits;
+    out[2] = c.part_256 ? 256 : 128;
 }
 
 // Runs `op` (launch or prepare) of small shape `i`. Ring depths: as many stages as LDS holds, two workgroups

@@ -89,6 +89,9 @@ struct GemmArgs {
 };
 // Bytes of partial planes launch_gemm would use of `room` bytes.
 size_t gemm_partial_bytes(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K, size_t room);
+// The form launch_gemm picks with `room` bytes of planes (host arithmetic, for the tests): out = {index of the small tile
+// shape or -1, parts of the contraction (1: not split over workgroups), rows of the part tile}.
+void gemm_choice(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K, size_t room, int out[3]);
 // One-time set-up per device (rtl_init, or the first entry-point call): raises the dynamic-LDS limit
 // of every tile-loop kernel and makes the runtime load both code objects, so that later launches
 // are plain kernel nodes (HIP-graph capture needs no warm-up call).

@@ -7,6 +7,7 @@ import re
 import pytest
 
 from paper_2605_26632_amd import binding as rtl
+from util import gemm_choice
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -210,3 +211,28 @@ def test_every_entry_point_plans_the_same_contraction_split():
             assert p == 0 or (p >= 2 * M * N * 4 and p % (M * ((N + 7) // 8 * 8) * 4) == 0)
         if (M, N, K) in SPLIT_SHAPES:
             assert min(planes) > 0, (M, N, K)
+
+
+# Measured GPU time of a call, 256-row plan against the small tiles in several passes (us): the latter is the slower one.
+@pytest.mark.parametrize("sparse,fp8,M,N,K", [
+    (True, False, 1408, 14368, 11904),       # 303 / 392
+    (True, False, 639, 10400, 11776),        # 137 / 169 (LoRA)
+    (True, False, 1297, 5728, 5312),         # 59 / 64
+    (True, False, 831, 17124, 6144),         # 145 / 149
+    (True, False, 4973, 800, 4352),          # 59 / 71 (LoRA)
+    (True, True, 858, 9024, 14592),          # 86 / 91
+    (False, False, 4535, 4320, 13952),       # 481 / 581
+    (False, False, 3960, 2036, 4096),        # 74 / 87
+    (False, False, 884, 17575, 3840),        # 152 / 159
+])
+def test_tile_choice_keeps_the_256_row_plan_where_small_tiles_are_slower(sparse, fp8, M, N, K):
+    assert gemm_choice(sparse, fp8, M, N, K)[:2] == (-1, 1)
+
+
+def test_tile_choice_where_small_tiles_are_faster():
+    """[37, 3072, 12288] 69 us with the 256-row plan, 17 with 32 x 32 tiles in one pass; dense 125 and 20;
+    [10, 16416, 11776] 32 x 32 tiles in three passes (all of W once) 1.27 times as fast as 128 x 128."""
+    assert gemm_choice(True, False, 37, 3072, 12288) == (0, 1, 128)
+    assert gemm_choice(True, False, 10, 16416, 11776)[:2] == (0, 1)
+    assert gemm_choice(False, False, 37, 3072, 12288)[:2] != (-1, 1)
+    assert gemm_choice(False, False, 333, 3072, 12288)[1] > 1

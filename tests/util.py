@@ -22,3 +22,16 @@ def floored_elem_err(y, ref):
 # predicts far less: identical bf16 operands, exact fp32 products, a different summation order
 # (~1e-6) and one bf16 rounding of the stored result (2^-9 = 2e-3 of the element).
 Y_TOL = 1e-2
+
+
+def gemm_choice(sparse, fp8, M, N, K, room=1 << 62):
+    """(index of the small tile shape or -1, parts of the contraction, rows of the part tile) the tile loop picks: an
+    internal host function of the library, not part of its ABI."""
+    import ctypes as C
+    from paper_2605_26632_amd import binding as rtl
+    f = rtl.lib()._ZN3rtl11gemm_choiceEbblllmPi
+    f.argtypes = [C.c_bool, C.c_bool, C.c_int64, C.c_int64, C.c_int64, C.c_size_t, C.POINTER(C.c_int)]
+    f.restype = None
+    out = (C.c_int * 3)()
+    f(bool(sparse), bool(fp8), M, N, K, room, out)
+    return tuple(out)
