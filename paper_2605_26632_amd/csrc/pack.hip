@@ -4,7 +4,7 @@
 // kept values + 2-bit positions (App. A operand format). One sweep over X; HBM-bandwidth bound:
 // 2 bytes read + 1.125 bytes written per input element.
 //
-// Mapping: one wavefront per row (several for long rows, each taking a run of whole steps); a lane
+// Mapping: one wavefront per row (several for long rows, each taking a run of whole trips); a lane
 // takes 8 consecutive bf16 (one 16-byte load = two groups) per step and the wave walks the row in
 // steps of 512 elements, so every load, the
 // 8-byte value stores and the 4-byte metadata stores (four lanes' bytes gathered with DPP
@@ -42,9 +42,9 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void sparsify_pack_kernel(
     const uint16_t* __restrict__ X, int64_t M, int K, int64_t ldx, float eps,
     void* __restrict__ vals, uint8_t* __restrict__ meta, uint8_t* __restrict__ vals_km,
     uint8_t* __restrict__ meta_km, int64_t Mpad, float* __restrict__ scale,
-    float* __restrict__ rowsums, const float* __restrict__ x_scale, int parts) {
+    float* __restrict__ rowsums, const float* __restrict__ x_scale, int parts, int span) {
     const int lane = threadIdx.x & 63;
-    // `parts` waves share a row, each taking a run of whole 512-element steps: few rows then still give
+    // `parts` waves share a row, each taking a run of `span` elements: few rows then still give
     // every SIMD enough waves in flight. ROW / TENSOR add the waves' sums up in LDS, so there the waves of a
     // row sit in one workgroup (parts divides kWavesPerBlock).
     constexpr bool SUMS = COMP == RTL_COMP_ROW || COMP == RTL_COMP_TENSOR;
@@ -52,7 +52,6 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void sparsify_pack_kernel(
     const int64_t row = gw / parts;
     const int part = (int)(gw % parts);
     if (row >= M && (!SUMS || parts == 1)) return;   // whole wave leaves together (it has no barrier to meet)
-    const int span = ((K + parts - 1) / parts + 511) / 512 * 512;
     const int kbeg = part * span;
     const int kend = row < M ? min(K, kbeg + span) : 0;
     const uint16_t* xr = X + row * ldx;
@@ -276,6 +275,33 @@ hipError_t launch_operand_to_kmajor(const uint16_t* vals, const uint8_t* meta, i
     return hipGetLastError();
 }
 
+// Waves per row: one per unrolled trip of work (1536 elements) while the rows alone do not fill the chip,
+// fewer once they do. Measured [M, 12288], us with 1 / 2 / 4 / 8 waves per row: FP8 GROUP M = 37 18.9 / 10.7 /
+// 6.5 / 4.4, 512 19.6 / 11.3 / 7.3 / 6.5, 1029 21.2 / 16.4 / 12.8 / 11.1, 2048 22.4 / 19.0 / 17.1 / 18.1,
+// 4608 41.9 / 34.5 / 31.7 / 32.1, 9728 67 / 64 / 62 / 64. ROW and TENSOR pay for the sum over the waves:
+// ROW M = 37 12.7 / 7.9 / 5.4 / 4.5, 512 14.2 / 8.7 / 6.6 / 7.0, 2048 17.0 / 16.2 / 18.5 / 19.1. At K = 3072 two waves
+// win or tie for GROUP (4608: 13.0 -> 11.6) and lose for ROW from M = 1500 on (5.8 -> 5.9, 9728 17.9 -> 19.3).
+// Between those K, FP8 GROUP at [16000, 5120 / 6656 / 9216]: 1 wave 45.6 / 56.2 / 84.1, this rule 45.4 / 56.7 / 76.9; runs cut at
+// 512 elements 53.3 / 70.7 / 80.8. ROW [37 / 300 / 700, 7680], five trips: 4 waves 5.6 / 5.9 / 8.2, 8 waves 4.7 / 5.4 / 6.9
+// (eight trips, [1000, 12288]: 9.3 and 9.8).
+// Runs are whole trips: a trip costs its three steps of arithmetic however much of it lies past the run's end, and runs
+// of whole 512-element steps made up to 7 trips out of the 5 of K = 6656.
+void row_split(int comp, int64_t M, int64_t K, int out[2]) {
+    const int trips = (int)((K + 512 * kUnroll - 1) / (512 * kUnroll));
+    int parts;
+    if (comp == RTL_COMP_NONE || comp == RTL_COMP_GROUP) {
+        const int most = M <= 1024 ? 8 : (K >= 2 * 512 * kUnroll ? 4 : 1);
+        const int per = (trips + most - 1) / most;                            // trips of a wave
+        parts = (trips + per - 1) / per;                                      // no wave without one
+    } else {
+        const int most = M <= 256 || (M <= 1024 && trips % 4 != 0) ? 8 : (M <= 1536 ? 4 : (K >= 4 * 512 * kUnroll ? 2 : 1));
+        parts = trips > 4 ? 8 : (trips > 2 ? 4 : trips);                      // divides kWavesPerBlock
+        parts = parts > most ? most : parts;
+    }
+    out[0] = parts;
+    out[1] = (trips + parts - 1) / parts * (512 * kUnroll);
+}
+
 template <bool FP8>
 static hipError_t launch_pack_any(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp,
                                   float eps, void* vals, uint8_t* meta, uint8_t* vals_km, uint8_t* meta_km,
@@ -304,39 +330,27 @@ static hipError_t launch_pack_any(const uint16_t* X, int64_t M, int64_t K, int64
             }
         }
     }
-    // Waves per row: one per unrolled trip of work (1536 elements) while the rows alone do not fill the chip,
-    // fewer once they do. Measured [M, 12288], us with 1 / 2 / 4 / 8 waves per row: FP8 GROUP M = 37 18.9 / 10.7 /
-    // 6.5 / 4.4, 512 19.6 / 11.3 / 7.3 / 6.5, 1029 21.2 / 16.4 / 12.8 / 11.1, 2048 22.4 / 19.0 / 17.1 / 18.1,
-    // 4608 41.9 / 34.5 / 31.7 / 32.1, 9728 67 / 64 / 62 / 64. ROW and TENSOR pay for the sum over the waves:
-    // ROW M = 37 12.7 / 7.9 / 5.4 / 4.5, 512 14.2 / 8.7 / 6.6 / 7.0, 2048 17.0 / 16.2 / 18.5 / 19.1. At K = 3072 two waves
-    // win or tie for GROUP (4608: 13.0 -> 11.6) and lose for ROW from M = 1500 on (5.8 -> 5.9, 9728 17.9 -> 19.3).
-    int parts = (int)(K / (512 * kUnroll));
-    if (comp == RTL_COMP_NONE || comp == RTL_COMP_GROUP) {
-        const int most = M <= 1024 ? 8 : 4;
-        parts = parts < 1 ? 1 : (parts > most ? most : parts);
-    } else {
-        const int most = M <= 256 ? 8 : (M <= 1536 ? 4 : (K >= 4 * 512 * kUnroll ? 2 : 1));
-        parts = parts >= 8 ? 8 : (parts >= 4 ? 4 : (parts >= 2 ? 2 : 1));     // divides kWavesPerBlock
-        parts = parts > most ? most : parts;
-    }
+    int split[2];
+    row_split((int)comp, M, K, split);
+    const int parts = split[0], span = split[1];
     const dim3 grid((unsigned)((M * parts + kWavesPerBlock - 1) / kWavesPerBlock));
     const dim3 block(kWavesPerBlock * 64);
     switch (comp) {
         case RTL_COMP_NONE:
             hipLaunchKernelGGL((sparsify_pack_kernel<RTL_COMP_NONE, FP8>), grid, block, 0, stream, X, M,
-                               (int)K, ldx, eps, vals, meta, vals_km, meta_km, Mpad, scale, rowsums, x_scale, parts);
+                               (int)K, ldx, eps, vals, meta, vals_km, meta_km, Mpad, scale, rowsums, x_scale, parts, span);
             break;
         case RTL_COMP_GROUP:
             hipLaunchKernelGGL((sparsify_pack_kernel<RTL_COMP_GROUP, FP8>), grid, block, 0, stream, X, M,
-                               (int)K, ldx, eps, vals, meta, vals_km, meta_km, Mpad, scale, rowsums, x_scale, parts);
+                               (int)K, ldx, eps, vals, meta, vals_km, meta_km, Mpad, scale, rowsums, x_scale, parts, span);
             break;
         case RTL_COMP_ROW:
             hipLaunchKernelGGL((sparsify_pack_kernel<RTL_COMP_ROW, FP8>), grid, block, 0, stream, X, M,
-                               (int)K, ldx, eps, vals, meta, vals_km, meta_km, Mpad, scale, rowsums, x_scale, parts);
+                               (int)K, ldx, eps, vals, meta, vals_km, meta_km, Mpad, scale, rowsums, x_scale, parts, span);
             break;
         case RTL_COMP_TENSOR:
             hipLaunchKernelGGL((sparsify_pack_kernel<RTL_COMP_TENSOR, FP8>), grid, block, 0, stream, X, M,
-                               (int)K, ldx, eps, vals, meta, vals_km, meta_km, Mpad, scale, rowsums, x_scale, parts);
+                               (int)K, ldx, eps, vals, meta, vals_km, meta_km, Mpad, scale, rowsums, x_scale, parts, span);
             if (scale) return launch_tensor_scale(rowsums, M, eps, scale, stream);
             break;
     }

@@ -35,6 +35,8 @@ inline size_t kmajor_val_bytes(int64_t M, int64_t K, size_t val_bytes) {
 hipError_t launch_sparsify_pack(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp,
                                 float eps, uint16_t* vals, uint8_t* meta, uint8_t* vals_km,
                                 uint8_t* meta_km, float* scale, float* rowsums, hipStream_t stream);
+// How the row mapping divides a row (host arithmetic): out = {waves per row, elements of a wave's run}.
+void row_split(int comp, int64_t M, int64_t K, int out[2]);
 // FP8 form (implementation details, "orthogonal validation with FP8 quantization"): kept values
 // leave as E4M3 codes of (s * x) / x_scale[0] (vals8 [M,K/2] bytes); `meta_km` then uses the 16-byte
 // records and `vals_km` 128-k blocks (need K % 128 == 0).

@@ -7,7 +7,7 @@ import re
 import pytest
 
 from paper_2605_26632_amd import binding as rtl
-from util import gemm_choice
+from util import gemm_choice, row_split
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -236,3 +236,19 @@ def test_tile_choice_where_small_tiles_are_faster():
     assert gemm_choice(True, False, 10, 16416, 11776)[:2] == (0, 1)
     assert gemm_choice(False, False, 37, 3072, 12288)[:2] != (-1, 1)
     assert gemm_choice(False, False, 333, 3072, 12288)[1] > 1
+
+
+def test_waves_of_a_row_make_no_extra_trips():
+    """The runs of a row's waves cover it once, in whole 512-element steps, and cost no more unrolled trips (1536 elements,
+    paid in full when part of one lies past the run) than one wave alone; where the waves' sums meet in LDS their number
+    divides the eight waves of a workgroup."""
+    for comp in range(4):
+        for M in (1, 37, 256, 300, 1024, 1025, 1500, 1537, 4608, 16896):
+            for K in [8, 512, 1536, 1544] + list(range(2048, 20000, 520)) + [12288, 15360, 1 << 20]:
+                parts, span = row_split(comp, M, K)
+                assert 1 <= parts <= 8 and span % 512 == 0 and parts * span >= K
+                runs = [max(0, min(K, (i + 1) * span) - i * span) for i in range(parts)]
+                assert sum(runs) == K
+                assert sum((r + 1535) // 1536 for r in runs) == (K + 1535) // 1536, (comp, M, K, parts, span)
+                if comp >= 2:
+                    assert 8 % parts == 0

@@ -1145,6 +1145,16 @@ def test_pack_several_waves_per_row(M, K, comp):
     check_pack_fp8(X, comp, fp8_scale(X))
 
 
+@pytest.mark.parametrize("M,K", [(5, 1544), (301, 7688), (1030, 6664), (2049, 5128), (1025, 15368)])
+@pytest.mark.parametrize("comp", COMPS)
+def test_pack_runs_of_whole_trips(M, K, comp):
+    """Trip counts that do not divide over the waves of a row (2, 4, 5, 6 and 11 trips: a short last run, ROW / TENSOR waves
+    without any) and a last trip of eight elements."""
+    X = synth.activations("laplace_outlier", M, K, seed=M + K, device=DEV)
+    check_pack(X, comp)
+    check_pack_fp8(X, comp, fp8_scale(X))
+
+
 @pytest.mark.parametrize("M,K", [(1, 64), (130, 4160), (513, 12288), (1029, 3072), (2049, 1088)])
 @pytest.mark.parametrize("comp", [rtl.COMP_ROW, rtl.COMP_TENSOR])
 def test_lora_sweep_ranges_and_smaller_workspace(M, K, comp):

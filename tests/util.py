@@ -35,3 +35,15 @@ def gemm_choice(sparse, fp8, M, N, K, room=1 << 62):
     out = (C.c_int * 3)()
     f(bool(sparse), bool(fp8), M, N, K, room, out)
     return tuple(out)
+
+
+def row_split(comp, M, K):
+    """(waves per row, elements of a wave's run) of the row-mapped sweep: an internal host function, not part of the ABI."""
+    import ctypes as C
+    from paper_2605_26632_amd import binding as rtl
+    f = rtl.lib()._ZN3rtl9row_splitEillPi
+    f.argtypes = [C.c_int, C.c_int64, C.c_int64, C.POINTER(C.c_int)]
+    f.restype = None
+    out = (C.c_int * 2)()
+    f(comp, M, K, out)
+    return tuple(out)
