@@ -10,7 +10,7 @@ import torch
 import oracle
 from paper_2605_26632_amd import binding as rtl
 from paper_2605_26632_amd import synth
-from util import Y_TOL, floored_elem_err, rel_max_err
+from util import Y_TOL, floored_elem_err, gemm_choice, rel_max_err
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -705,7 +705,7 @@ def bf16_ulp(x):
 
 def check_y_fp8(Y, r, Wq_np, factor, bias=None, max_rows=64):
     """Output check of the FP8 linear, three ways:
-    1. the north-star bound against the exact oracle: max error 1e-2 of max|Y|;
+    1. the output bound against the exact oracle: max error 1e-2 of max|Y|;
     2. elementwise against the exact oracle with the allowance the arithmetic predicts: one bf16
        rounding of the result, the worst case of the instruction's cut (fp8_truncation_bound, computed
        from the very operands of every run, no fitted constant), and fp32 summation noise;
@@ -1089,10 +1089,11 @@ def test_randomized_linear_cases():
 
 
 # One output per tile shape of the small-tile loop (32x32, 64x32, 64x64, 128x64, 128x128, dense 256x128 as the sizes
-# grow), ragged in M and N, with block counts that are short of, equal to and not a multiple of the K groups.
+# grow), ragged in M and N, with block counts that are short of, equal to and not a multiple of the K groups; the last two
+# take several passes over the compute units (sparse 32x32, dense 128x128).
 @pytest.mark.parametrize("M,N,K", [(1, 1, 64), (31, 33, 128), (33, 31, 192), (37, 1000, 4672), (65, 3071, 1088), (97, 3072, 3136),
                                    (129, 1553, 832), (201, 3009, 1344), (393, 3041, 1600), (700, 3000, 704), (777, 3072, 3072),
-                                   (1301, 3065, 576)])
+                                   (1301, 3065, 576), (1, 16421, 6144), (259, 16976, 2048)])
 @pytest.mark.parametrize("comp", [rtl.COMP_GROUP, rtl.COMP_ROW])
 def test_small_tiles_sparse_dense_and_lora(M, N, K, comp):
     """Sampled rows against the oracle, guard bytes around Y, and every form that shares the tile loop: sparse,
@@ -1219,7 +1220,9 @@ def test_pack_group_factor_over_exponent_spreads(spread):
 def test_contraction_split_over_workgroups(M, N, K):
     """Shapes on which the contraction is spread over workgroups (ragged M, N and block counts): dense, sparse with
     per-row factor and bias, LoRA, FP8, FP8 + LoRA on sampled rows, the entry point on the fixed scratch bit for bit,
-    and every call again on a workspace without room for the partial planes."""
+    and every bf16 call again on a workspace of its mandatory size, where nothing is split. (FP8 takes half as many
+    blocks and splits at the last shape only; see the test below.)"""
+    assert gemm_choice(True, False, M, N, K)[1] > 1 and gemm_choice(False, False, M, N, K)[1] > 1
     X = synth.activations("gelu", M, K, seed=M, device=DEV)
     W = synth.weights(N, K, seed=N, device=DEV)
     b = synth.bias(N, seed=4, device=DEV, std=0.5)
@@ -1229,32 +1232,28 @@ def test_contraction_split_over_workgroups(M, N, K):
     Xs, Wb, bb = synth.bits(X[sel]), synth.bits(W), synth.bits(b)
     L = rtl.lib()
 
-    def both(call, planned, ref):
-        assert planned > 0
+    def both(call, query, ref, *rest):
+        planned, mandatory = int(query(M, N, K, *rest)), int(query(M, 1 << 20, K, *rest))   # (nothing is split at that N)
+        assert planned >= mandatory + 2 * M * N * 4                  # a split is planned
         check_y(call(None)[sel], ref)
-        planes = 2 * M * ((N + 7) // 8 * 8) * 4                    # the least a split needs
-        ws = torch.empty(max(planned - planes, 256), dtype=torch.uint8, device=DEV)
-        try:
-            check_y(call(ws)[sel], ref)
-        except rtl.RtlError as e:
-            assert e.status == 4                                   # cut into the mandatory part
+        check_y(call(torch.empty(mandatory, dtype=torch.uint8, device=DEV))[sel], ref)
     ref = oracle.dense_linear_oracle(Xs, Wb, bias=bb)
-    both(lambda ws: rtl.dense_linear(X, W, bias=b, ws=ws), int(L.rtl_dense_linear_workspace(M, N, K)), ref)
-    check_y(rtl.dense_linear(X, W, bias=b, ws=torch.empty(0, dtype=torch.uint8, device=DEV))[sel], ref)
+    both(lambda ws: rtl.dense_linear(X, W, bias=b, ws=ws), L.rtl_dense_linear_workspace, ref)
     for comp in (rtl.COMP_GROUP, rtl.COMP_ROW):
         ref = oracle.sparse_linear_oracle(Xs, Wb, bias=bb, scope=comp)["Y"]
         Y, guard_ok = guarded((M, N), torch.bfloat16, 7.0)
         rtl.sparse_linear(X, W, bias=b, comp=comp, out=Y)
         check_y(Y[sel], ref)
         guard_ok()
-        both(lambda ws: rtl.sparse_linear(X, W, bias=b, comp=comp, ws=ws), rtl.sparse_linear_workspace(M, N, K, comp), ref)
+        both(lambda ws: rtl.sparse_linear(X, W, bias=b, comp=comp, ws=ws), L.rtl_sparse_linear_workspace, ref, comp)
         Z = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
         assert torch.equal(rtl.sparse_linear_static(X, W, Z, bias=b, comp=comp), Y)
         ref = oracle.sparse_lora_linear_oracle(Xs, Wb, synth.bits(LA), synth.bits(LB), bias=bb, scope=comp)["Y"]
         both(lambda ws: rtl.sparse_lora_linear(X, W, LA, LB, bias=b, comp=comp, ws=ws),
-             rtl.sparse_lora_linear_workspace(M, N, K, 64, comp), ref)
+             L.rtl_sparse_lora_linear_workspace, ref, 64, comp)
     vals, meta, _ = rtl.sparsify_pack(X, comp=rtl.COMP_GROUP)
     assert torch.equal(rtl.packed_linear(vals, meta, W, bias=b), rtl.sparse_linear(X, W, bias=b, comp=rtl.COMP_GROUP))
+
     if K % 128 == 0:
         xs, Wq = fp8_scale(X), rtl.quantize_fp8(W)
         Wn, f = Wq.cpu().numpy(), float(xs.item())
@@ -1262,6 +1261,70 @@ def test_contraction_split_over_workgroups(M, N, K):
         check_y_fp8(rtl.sparse_linear_fp8(X, Wq, xs, bias=b)[sel], r, Wn, f, bias=bb)
         r = oracle.sparse_lora_linear_fp8_oracle(Xs, Wn, f, synth.bits(LA), synth.bits(LB), bias=bb, scope=oracle.GROUP)
         assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b)[sel]), r["Y"]) <= Y_TOL
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(140, 5504, 15360, 256), (140, 5497, 15360, 256), (141, 8413, 9216, 256), (139, 3084, 15360, 128),
+                                        (1054, 512, 15360, 128), (200, 3072, 24576, 128)])
+def test_fp8_contraction_split_over_workgroups(M, N, K, tile):
+    """Both part tiles with FP8 operands, plain and LoRA, every scope, with bias; again on the mandatory workspace."""
+    choice = gemm_choice(True, True, M, N, K)
+    assert choice[1] > 1 and choice[2] == tile
+    X = synth.activations("gelu", M, K, seed=M, device=DEV)
+    W = synth.weights(N, K, seed=N, device=DEV)
+    b = synth.bias(N, seed=4, device=DEV, std=0.5)
+    LA, LB = synth.lora(N, K, 64, seed=5, device=DEV, std_a=0.05, std_b=0.05)
+    xs, Wq = fp8_scale(X), rtl.quantize_fp8(W)
+    rows = sampled_rows(M, 4, seed=6)
+    cols = np.unique(np.concatenate([np.linspace(0, N - 1, 96).astype(np.int64), np.arange(max(0, N - 9), N)]))   # (the model is slow)
+    sel = torch.from_numpy(rows).to(DEV)
+    Xb, Xs, Wn, f, bb = synth.bits(X), synth.bits(X[sel]), Wq.cpu().numpy(), float(xs.item()), synth.bits(b)
+    Yr = oracle.linear_f32w(oracle.bf16_to_f32(Xs), oracle.lora_delta(synth.bits(LA), synth.bits(LB)))
+    L = rtl.lib()
+    for comp in (rtl.COMP_GROUP, rtl.COMP_ROW, rtl.COMP_TENSOR):
+        if comp == rtl.COMP_TENSOR:                  # the codes of NONE scope, the factor of all rows
+            s = np.float32(oracle.scales(Xb, oracle.topk24(Xb), oracle.TENSOR)[0])
+            r = oracle.sparse_linear_fp8_oracle(Xs, Wn, f, scope=oracle.NONE)
+            r["Y"] = r["Y"] * s + oracle.bf16_to_f32(bb)[None, :]
+            factor = np.float32(f) * s
+        else:
+            r = oracle.sparse_linear_fp8_oracle(Xs, Wn, f, bias=bb, scope=comp)
+            factor = np.float32(f) * (r["s"][:, None] if comp == rtl.COMP_ROW else np.float32(1.0))
+        planned, mandatory = L.rtl_sparse_linear_fp8_workspace(M, N, K, comp), L.rtl_sparse_linear_fp8_workspace(M, 1 << 20, K, comp)
+        assert planned >= mandatory + 2 * M * N * 4
+        for ws in (None, torch.empty(mandatory, dtype=torch.uint8, device=DEV)):
+            Y, guard_ok = guarded((M, N), torch.bfloat16, 7.0)
+            rtl.sparse_linear_fp8(X, Wq, xs, bias=b, comp=comp, out=Y, ws=ws)
+            assert rel_max_err(y_to_np(Y[sel]), r["Y"]) <= Y_TOL
+            check_y_fp8(Y[sel][:, torch.from_numpy(cols).to(DEV)], dict(r, Y=r["Y"][:, cols]), Wn[cols], factor, bias=bb[cols])
+            guard_ok()
+        mandatory = L.rtl_sparse_lora_linear_fp8_workspace(M, 1 << 20, K, 64, comp)
+        for ws in (None, torch.empty(mandatory, dtype=torch.uint8, device=DEV)):
+            Y = rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b, comp=comp, ws=ws)
+            assert rel_max_err(y_to_np(Y[sel]), r["Y"] + Yr) <= Y_TOL
+
+
+@pytest.mark.parametrize("M,N,K", [(37, 1000, 4736), (201, 3009, 1408), (200, 3072, 12288), (700, 3071, 12288)])
+def test_small_tiles_and_split_contraction_on_strided_views(M, N, K):
+    """Row strides of X, W, L_B and Y, an output whose rows are only 2-byte aligned, and a small tile or a split: the
+    same bits as the contiguous call."""
+    Xp = synth.activations("laplace", M, K + 24, seed=M, device=DEV)
+    Wp = synth.weights(N, K + 8, seed=N, device=DEV)
+    LA, LBp = synth.lora(N, K + 16, 64, seed=5, device=DEV, std_a=0.05, std_b=0.05)
+    X, W, LB = Xp[:, 8:K + 8], Wp[:, :K], LBp[:, :K]
+    Xc, Wc, LBc = X.contiguous(), W.contiguous(), LB.contiguous()
+    xs = fp8_scale(Xc)
+    Wqp = torch.zeros((N, K + 16), dtype=torch.uint8, device=DEV)
+    Wq = rtl.quantize_fp8(Wc, out=Wqp[:, :K])
+    calls = [lambda x, w, lb, q, o: rtl.dense_linear(x, w, out=o), lambda x, w, lb, q, o: rtl.sparse_linear(x, w, comp=rtl.COMP_ROW, out=o),
+             lambda x, w, lb, q, o: rtl.sparse_lora_linear(x, w, LA, lb, out=o), lambda x, w, lb, q, o: rtl.sparse_linear_fp8(x, q, xs, out=o),
+             lambda x, w, lb, q, o: rtl.sparse_lora_linear_fp8(x, q, xs, LA, lb, comp=rtl.COMP_TENSOR, out=o)]
+    for call in calls:
+        ref = call(Xc, Wc, LBc, Wq.contiguous(), None)
+        wide = torch.full((M, N + 5), 7.0, dtype=torch.bfloat16, device=DEV)
+        out = wide[:, 3:N + 3]
+        call(X, W, LB, Wq, out)
+        assert torch.equal(out, ref)
+        assert bool((wide[:, :3] == 7.0).all()) and bool((wide[:, N + 3:] == 7.0).all())
 
 
 @pytest.mark.parametrize("M,N,K", [(2304, 1024, 15360), (2752, 512, 12288), (2752, 1280, 12288), (333, 3071, 12288)])
