@@ -20,7 +20,8 @@
  *      RTL_ERR_SHAPE      negative size, K not a multiple of the required granule, ld < extent,
  *                         M, N or K above 2^30, or a row stride of a GEMM operand above 2^22 elements
  *      RTL_ERR_ALIGN      a pointer or a row stride breaks the stated alignment
- *      RTL_ERR_WORKSPACE  workspace NULL or smaller than the matching *_workspace() query
+ *      RTL_ERR_WORKSPACE  workspace NULL or smaller than the call needs; the matching *_workspace() query is always
+ *                         enough (the linears also run on less, see below; rtl_dense_linear needs none)
  *      RTL_ERR_ARG        an enum value out of range, or eps negative / not finite
  *      RTL_ERR_HIP        the HIP runtime reports no usable device, or refused the set-up or a
  *                         launch (message via hipGetLastError)
@@ -28,9 +29,16 @@
  *                         the argument checks and before anything is launched)
  *  - M == 0 or N == 0 is RTL_OK with no launch.
  *  - The *_workspace queries of the linears include room that lets a call spread a long contraction over more
- *    compute units (fp32 partial sums; few rows only). That part is optional: a smaller workspace is accepted as long
- *    as it holds the rest (RTL_ERR_WORKSPACE otherwise), the call is then slower and its fp32 sums are grouped
- *    differently. A given call on a given workspace size is deterministic.
+ *    compute units (fp32 partial sums; few rows only) and, with a LoRA residual, its sweep over more ranges of K. That part
+ *    is optional: a smaller workspace is accepted as long as it holds the rest, the call is then slower and its fp32 sums
+ *    are grouped differently. Whatever its size, a workspace is written to: calls that overlap in time must not share one.
+ *  - A call is deterministic: the same arguments on the same workspace size give the same bits. How the fp32 sums of
+ *    an output are grouped is, however, a rule on the whole problem: on the operand types, M, N, K and the workspace
+ *    size, and for the ROW and TENSOR factors on M and K. A row therefore need not come out with the same bits when it is
+ *    computed in a call with other rows (rows in chunks, another batch size) or other columns (q, k and v in one product or in
+ *    three); results then differ by the rounding of the fp32 sums, which can move a bf16 output by one step. On
+ *    workspaces of the queried size rtl_sparse_linear, rtl_sparse_linear_static and rtl_sparsify_pack +
+ *    rtl_packed_linear give the same bits for the same problem.
  *  - Arithmetic: bf16 operands, fp32 accumulation, fp32 -> bf16 round-to-nearest-even on store.
  */
 #ifndef RTLYNX_H
@@ -188,7 +196,8 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
  * The denominator of every speedup the paper reports ("GEMM" column of its kernel tables).
  * Same layouts and alignment rules as rtl_sparse_linear; K % 64 == 0.
  *   workspace  rtl_dense_linear_workspace(M, N, K) bytes, 256-byte aligned (may be 0). All of it is optional: NULL is
- *   accepted too.
+ *   accepted too, and one that is not 16-byte aligned is left alone. Otherwise up to the size passed may be written, so
+ *   overlapping calls need separate ones.
  * ------------------------------------------------------------------------------------------- */
 size_t rtl_dense_linear_workspace(int64_t M, int64_t N, int64_t K);
 rtl_status rtl_dense_linear(const void* X, const void* W, const void* bias, void* Y,
