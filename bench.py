@@ -17,11 +17,11 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-WORKLOAD = "mlp_down"          # benchmark configs[1]
+WORKLOAD = "mlp_down"          # the paper's MLP-down layer
 DENSE_BF16_PEAK_TFLOPS = 2500.0  # published dense bf16 MFMA peak; SMFMAC issues at this rate
 HBM_PEAK_GBS = 8000.0
 # HBM-side bytes per sparse-GEMM launch on the default workload, from the rocprofv3 --pmc
-# FETCH_SIZE / WRITE_SIZE runs summarised in profiles/gemm_kernel_sparse_mlp_down.md
+# FETCH_SIZE / WRITE_SIZE runs
 # (FETCH_SIZE x 2.000 and WRITE_SIZE x 1.000 KiB after calibration against a plain 1 GiB copy).
 # Summary: profiles/rtl_sparse_linear_kernels_mlp_down.md.
 GEMM_TRAFFIC_BYTES = {"mlp_down": int((184458 * 2.0 + 24576 * 1.0) * 1024)}

@@ -10,7 +10,7 @@ LIB = os.path.join(HERE, "librtlynx.so")
 SOURCES = ["api.hip", "pack.hip", "pack_lora.hip", "gemm.hip", "diag.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
-         # packed-fp32 instructions are kept out of the generated code on the test machines
+         # packed-fp32 instructions are kept out of the generated code: some of their forms have given wrong results on this hardware
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 

@@ -96,9 +96,8 @@ void give_partials(rtl::GemmArgs& g, uint8_t* base, size_t used, size_t bytes, s
 }
 // TENSOR scope: leaves the factor of the sums at `rowsums` to the tile loop, which puts it in scale[0] (and, with an
 // FP8 activation scale, their product in fused[0]).
-void give_factor(rtl::GemmArgs& g, const float* rowsums, int64_t M, float eps, float* scale, const float* x_scale, float* fused) {
+void give_factor(rtl::GemmArgs& g, const float* rowsums, float eps, float* scale, const float* x_scale, float* fused) {
     g.rowsums = rowsums;
-    g.factor_rows = M;
     g.factor_eps = eps;
     g.factor_out = scale;
     g.factor_mul = x_scale;
@@ -241,7 +240,7 @@ static rtl_status sparse_linear_on(uint8_t* base, size_t bytes, const SparseWs& 
     g.W = W;
     g.bias = static_cast<const uint16_t*>(bias);
     g.row_scale = comp == RTL_COMP_ROW ? scale : nullptr;
-    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), M, eps, scale, nullptr, nullptr);
+    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), eps, scale, nullptr, nullptr);
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
     give_partials(g, base, ws.total, bytes, planes_room(M, K));
@@ -326,7 +325,7 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
     g.W = W;
     g.bias = static_cast<const uint16_t*>(bias);
     g.row_scale = comp == RTL_COMP_ROW ? scale : nullptr;
-    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), M, eps, scale, nullptr, nullptr);
+    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), eps, scale, nullptr, nullptr);
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
     g.T = T;
@@ -412,7 +411,7 @@ rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_s
     g.W = Wq;
     g.bias = static_cast<const uint16_t*>(bias);
     g.row_scale = comp == RTL_COMP_ROW ? scale : nullptr;
-    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), M, eps, scale, x_scale, fused);
+    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), eps, scale, x_scale, fused);
     else g.tensor_scale = x_scale;                       // dequantisation rides on the epilogue
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;
@@ -466,7 +465,7 @@ rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float
     g.W = Wq;
     g.bias = static_cast<const uint16_t*>(bias);
     g.row_scale = comp == RTL_COMP_ROW ? scale : nullptr;
-    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), M, eps, scale, x_scale, fused);
+    if (comp == RTL_COMP_TENSOR) give_factor(g, reinterpret_cast<float*>(base + ws.pack), eps, scale, x_scale, fused);
     else g.tensor_scale = x_scale;                       // dequantisation of the sparse product only
     g.Y = static_cast<uint16_t*>(Y);
     g.M = M; g.N = N; g.K = K; g.lda = 0; g.ldw = ldw; g.ldy = ldy;

@@ -989,7 +989,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * WAVES_K * 64) void gemm_split_k
         if (a.rowsums) {
             // TENSOR scope: every workgroup adds the rows' sums up for itself (a few KB from L2, 1 to 2 us), which
             // spares the launch that would do only this (4.7 us and the gap before it)
-            const float sc = tensor_factor(a.rowsums, a.factor_rows, a.factor_eps);
+            const float sc = tensor_factor(a.rowsums, a.M, a.factor_eps);
             b.folded = a.factor_mul ? a.factor_mul[0] * sc : sc;
             if (blockIdx.x == 0 && threadIdx.x == 0) {
                 a.factor_out[0] = sc;
@@ -1354,8 +1354,7 @@ hipError_t launch_gemm(bool sparse, const GemmArgs& a_in, hipStream_t stream) {
             fold = ((a.M + s.bm - 1) / s.bm) * ((a.N + s.bn - 1) / s.bn) <= 512;
         }
         if (!fold) {
-            const hipError_t e = launch_tensor_scale(a.rowsums, a.factor_rows, a.factor_eps, a.factor_out, stream, a.factor_mul,
-                                                     a.factor_fused);
+            const hipError_t e = launch_tensor_scale(a.rowsums, a.M, a.factor_eps, a.factor_out, stream, a.factor_mul, a.factor_fused);
             if (e != hipSuccess) return e;
             a.rowsums = nullptr;
             a.tensor_scale = a.factor_fused ? a.factor_fused : a.factor_out;

@@ -73,10 +73,9 @@ struct GemmArgs {
     int64_t m_split;        // rows [0, m_split) are cut into body tiles, rows [m_split, M) into 256 x 128 tail tiles
     int body_tiles, tail_tiles;
     bool fp8;               // sparse only: E4M3 operands, K % 128 == 0, 16-byte metadata records
-    // TENSOR scope whose factor is still to be formed: the rows' sums [factor_rows][2]; the factor goes to
+    // TENSOR scope whose factor is still to be formed: the rows' sums [M][2]; the factor goes to
     // factor_out[0], times factor_mul[0] (nullable) to factor_fused[0], and is used in place of tensor_scale
     const float* rowsums;
-    int64_t factor_rows;
     float factor_eps;
     float* factor_out;
     const float* factor_mul;

@@ -463,7 +463,7 @@ def test_linears_on_strided_views(comp):
 # ------------------------------------------------------------------ FP8 + LoRA (whole Alg. 1 on FP8 operands)
 @pytest.mark.parametrize("comp", COMPS)
 def test_sparse_lora_linear_fp8_tiny_config(comp):
-    """rtl_sparse_lora_linear_fp8 against the oracle's composition: the benchmark spec's bound, and elementwise
+    """rtl_sparse_lora_linear_fp8 against the oracle's composition: the output bound, and elementwise
     with the allowance of the FP8 product (the instruction's cut, computed from the operands of every
     run) plus one bf16 rounding of the sum; with a zero L_A the call must equal rtl_sparse_linear_fp8 bit
     for bit (same sweep outputs, same tile loop, a tail that adds zeros)."""
@@ -497,7 +497,7 @@ def test_sparse_lora_linear_fp8_operand_and_sampled_rows(shape):
     """Ragged and full shapes: the FP8 compressed operand the one-pass sweep leaves must equal, bit for
     bit, the one rtl_sparse_linear_fp8's sweep leaves (head of the workspace; at K = 3072 the K ranges are
     three 64-k stages long, so range boundaries fall inside 128-k blocks), and sampled rows of Y must meet
-    the benchmark spec's bound."""
+    the output bound."""
     if isinstance(shape, str):
         X, W = synth.workload(shape, seed=0, device=DEV)
     else:
