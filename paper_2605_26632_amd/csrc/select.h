@@ -103,9 +103,11 @@ __device__ __forceinline__ GroupOut select_group(uint32_t d0, uint32_t d1, float
         // exact sequence: 3 in num, 2 in den, 1 for the quotient, 3 after the root, 1 and 1: 5. The two differ by
         // at most 13; the exact sequence only runs when a fast product lies within 16 units of a bf16 rounding
         // boundary, i.e. whenever they could round differently. The result is bit-identical.
-        // Against selection on 17-bit keys with fused multiply-adds for the norms (fast path of the whole sweep 67
-        // vector instructions per group, 51 now): sweep of rtl_sparse_linear [4096, 12288] 31.1 -> 28.1 us (5.6 TB/s), [4608, 3072] 10.8 ->
-        // 9.9, NONE 7.7 -> 7.3, FP8 GROUP [4608, 12288] 31.5 -> 29.6.
+        // The rounding of the dot product is that measurement, not a specification; its model has 3 half-units to spare.
+        // Against selection on 17-bit keys with fused multiply-adds for the norms (fast path of the block-mapped kernel, addressing
+        // and stores included, 67 vector instructions per group, 51 now; selection and compensation alone 51 and 37): sweep of
+        // rtl_sparse_linear back to back [4096, 12288] 30.8 -> 27.6 us (5.7 TB/s), inside calls 35.0 -> 31.8, [4608, 3072] 11.0 -> 10.3,
+        // NONE [4096, 12288] 25.9 -> 25.5.
         const float num = dot2_bf16(d1, dot2_bf16(d0, 0.f));
         const float d = dot2_bf16(pair, eps);
         float s = __builtin_amdgcn_sqrtf(num * __builtin_amdgcn_rcpf(d));
