@@ -236,6 +236,8 @@ def test_tile_choice_where_small_tiles_are_faster():
     assert gemm_choice(True, False, 10, 16416, 11776)[:2] == (0, 1)
     assert gemm_choice(False, False, 37, 3072, 12288)[:2] != (-1, 1)
     assert gemm_choice(False, False, 333, 3072, 12288)[1] > 1
+    for s in ((161, 6168, 128), (1981, 1024, 128), (2686, 640, 128), (319, 6336, 128)):      # dense 64 x 64: slower than the 256-row plan
+        assert gemm_choice(False, False, *s)[0] in (3, 4)
 
 
 def test_waves_of_a_row_make_no_extra_trips():
