@@ -4,11 +4,10 @@
 //   sparse: Y = S(X) W^T, S(X) compressed   (Alg. 1 "Y_s <- S(X) W^T", operand format of App. A;
 //                                            v_smfmac_f32_32x32x32_bf16)
 //
-// Both share one tile loop. A workgroup owns a BM x BN tile of Y and walks K in stages; a stage is
-// two matrix-instruction sub-steps deep (64 dense k for the sparse kernel, 32 for the dense one, so
-// both spend the same number of matrix cycles per stage). Stages travel HBM/L2 -> LDS with
-// direct-to-LDS loads (no register staging) through a ring of LDS buffers, and each wave keeps the
-// operand fragments of the next sub-step in flight while the matrix core works on the current one.
+// Both share one tile loop. A workgroup owns a BM x BN tile of Y and walks K in stages of 128-byte rows
+// of W (64 dense k in bf16, 128 in FP8). Stages travel HBM/L2 -> LDS with direct-to-LDS loads (no register
+// staging) through a ring of LDS buffers, and each wave keeps operand fragments in flight while the matrix
+// core works on others.
 // The sparse kernel reads its compressed operand in the k-major layout the pack sweep writes
 // (values and metadata of a 256-row tile contiguous per stage: whole 128-byte lines only); the
 // dense operands X and W are the caller's row-major tensors.
@@ -17,26 +16,38 @@
 // structure along K), so tokens map to the instruction's rows and the weight rows (K contiguous)
 // map to its columns: no transposition of either tensor is needed.
 //
-// Operand layout of v_smfmac_f32_32x32x32_bf16 (measured on the device with one-hot operands):
-//   lane l: i = l % 32, kb = l / 32
+// Matrix instructions of size S x S: 32 in the sparse kernels, 16 in the dense one, of the same rate per clock. The clock
+// is set by the package power limit. On N(0, 1) operands fed from LDS with 128 x 64 per wave the 16 x 16 ones reach
+// 1730 against 1556 TFLOP/s (dense bf16), 1470 against 1395 (sparse bf16, executed) and 2865 against 2725 (sparse FP8):
+// twice the operand reads per multiply-add cost less than halving the accumulator traffic saves. On zeros all reach 2130
+// to 2230. In a tile loop a stalled wave has half the time to come back before the matrix core runs dry, and the small
+// instructions lose 3 % (dense) to 8 % (sparse) of the cycles. Dense gains from 16 (rtl_dense_linear on inputs that come from
+// HBM, 32 -> 16, us: [4608, 9216, 3072] 229.5 -> 217.3, [4096, 3072, 12288] 268.4 -> 261.3, [4608, 3072, 3072] 82.6 -> 80.4,
+// [800, 9216, 3072] 61.1 -> 59.1); sparse ties ([4096, 3072, 12288] 188.1 -> 186.6, [4608, 12288, 3072] 199.9 -> 200.5,
+// [16896, 12288, 3072] 724.8 -> 723.9, FP8 [4608, 3072, 12288] 131.4 -> 131.2) and loses with 128 x 128 tiles ([1500, 3072, 3072] 31.6
+// -> 33.1).
+//
+// Operand layouts, measured on the device (one-hot operands, random small integers); lane l: i = l % S, kb = l / S.
+// v_smfmac_f32_32x32x32_bf16 | v_smfmac_f32_16x16x64_bf16:
 //   A (8 bf16)  : row i, the kept values of dense k in [16 kb, 16 kb + 16) in order
 //   idx (16 bit): ABID picks the 16-bit half of the lane's own index register; nibble g holds
 //                 pos0 | pos1 << 2 of the lane's g-th group
-//   B (16 bf16) : column i; element u < 8 is dense k = 8 kb + u, u >= 8 is k = 16 + 8 kb + (u - 8)
-//   D (16 fp32) : column i, register r is row 8 (r / 4) + 4 kb + r % 4
-// v_mfma_f32_32x32x16_bf16: A and B (8 bf16) hold k = 8 kb + v of row / column i; D as above.
+//   B (16 bf16) : column i; element u < 8 is dense k = 8 kb + u, u >= 8 is k = 16 | 32 + 8 kb + (u - 8)
+//   D           : column i, register r (of 16) is row 8 (r / 4) + 4 kb + r % 4 | (of 4) row 4 kb + r
+// v_mfma_f32_32x32x16_bf16 | v_mfma_f32_16x16x32_bf16: A and B (8 bf16) hold k = 8 kb + v of row / column i; D as above.
 // The labelling of k inside a stage is free as long as both operands agree; it is chosen so that
-// a lane reads whole 16-byte chunks from LDS and one 32-bit word of metadata per stage.
+// a lane reads whole 16-byte chunks from LDS and its metadata as one word per stage.
 //
 // FP8 variant of the sparse kernel (E4M3 codes on both operands, the W8A8 composition of the
-// implementation-details section): v_smfmac_f32_32x32x64_fp8_fp8, measured the same way:
+// implementation-details section): v_smfmac_f32_32x32x64_fp8_fp8 | v_smfmac_f32_16x16x128_fp8_fp8:
 //   A (16 fp8)  : row i, the kept values of dense k in [32 kb, 32 kb + 32) in order
 //   idx (32 bit): the whole register, nibble g = pos0 | pos1 << 2 of the lane's g-th group
-//   B (32 fp8)  : column i; element u < 16 is dense k = 16 kb + u, u >= 16 is k = 32 + 16 kb + (u - 16)
+//   B (32 fp8)  : column i; element u < 16 is dense k = 16 kb + u, u >= 16 is k = 32 | 64 + 16 kb + (u - 16)
 //   D           : as above
 // In bytes this is the bf16 geometry (16-byte A chunk, two 16-byte B chunks at the same chunk
 // indices), so a stage simply covers 128 dense k instead of 64 and the kernel differs only in the
-// instruction and in the metadata record (16 bytes per row and stage, one 32-bit word per sub-step).
+// instruction and in the metadata record (16 bytes per row and stage). Both sizes add their products in the same way
+// (runs of 8 kept values cut at 13 bits below the run's largest exponent sum).
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -49,6 +60,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) __bf16 bf16x16;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 
@@ -62,6 +74,15 @@ union Frag16 {
     bf16x16 v;
     i32x8 q;     // 32 fp8
 };
+
+// One dense bf16 matrix instruction of size S x S (16 or 32 k).
+template <int S> struct AccOf { typedef f32x16 type; };
+template <> struct AccOf<16> { typedef f32x4 type; };
+template <int S>
+__device__ __forceinline__ typename AccOf<S>::type dense_mma(bf16x8 a, bf16x8 b, typename AccOf<S>::type c) {
+    if constexpr (S == 32) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
 
 __device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
     uint32_t u = __float_as_uint(f);
@@ -104,32 +125,43 @@ __device__ __forceinline__ void wait_vmcnt_lgkm0() {   // vmcnt <= N, all LDS re
     __builtin_amdgcn_s_waitcnt(0x0070 | (N & 0xF) | ((N >> 4) << 14));
 }
 
-// Per-stage LDS footprint. Rows of the A tile hold 64 bytes in both kernels (32 kept bf16 of 64
-// dense k, or 32 dense k); rows of the B tile hold 128 bytes (sparse) or 64 bytes (dense).
-// D64 (dense only): stages of 64 dense k, 128-byte rows on both sides, so that every L2 request
-// of the row-major operands is a whole line; a sub-step is then two matrix instructions deep.
-// WAVES_K > 1: a stage holds one k block per K group (see gemm_tile), kGroup bytes each.
-template <bool SPARSE, int BM, int BN, int STAGES, int WAVES_M = 1, int WAVES_N = 1, bool FP8 = false,
-          bool D64 = false, int WAVES_K = 1>
+// Per-stage LDS footprint. Rows of the A tile hold 64 bytes in the sparse kernels (the kept half) and 128 in
+// the dense one; rows of the B tile hold 128 bytes, so that every L2 request of a row-major operand is a
+// whole line. WAVES_K > 1: a stage holds one k block per K group (see gemm_tile), kGroup bytes each.
+// Size of the matrix instructions (see the top of the file).
+template <bool SPARSE>
+constexpr int kMmaSize = SPARSE ? 32 : 16;
+
+template <bool SPARSE, int BM, int BN, int STAGES, int WAVES_M, int WAVES_N, bool FP8, int WAVES_K = 1>
 struct Smem {
-    static constexpr int kABytes = BM * (D64 ? 128 : 64);
+    static constexpr int kABytes = BM * (SPARSE ? 64 : 128);
     static constexpr int kMetaRec = FP8 ? 16 : 8;   // metadata bytes per row and stage
     static constexpr int kMetaBytes = SPARSE ? BM * kMetaRec : 0;
-    static constexpr int kBBytes = (SPARSE || D64) ? BN * 128 : BN * 64;
+    static constexpr int kBBytes = BN * 128;
     static constexpr int kGroup = kABytes + kMetaBytes + kBBytes;
     static constexpr int kStage = WAVES_K * kGroup;
     static constexpr int kRing = STAGES * kStage;
     // epilogue staging: every wave owns (BM / WAVES_M) rows of (BN / WAVES_N) bf16 plus 16 bytes
-    // of padding per row (keeps rows 4 apart, written together, in different banks)
+    // of padding per row (keeps the rows written together in different banks)
     static constexpr int kEpiRowBytes = (BN / WAVES_N) * 2 + 16;
-    // K groups: one fp32 plane of the tile per group instead; 8 floats of row padding put rows 4 apart
-    // (written together by the two lane halves) 32 banks apart
-    static constexpr int kPitch = BN + 8;
+    // K groups: one fp32 plane of the tile per group instead; the row padding puts rows 4 apart (written together by the
+    // two or four lane groups) 32 or 16 banks apart
+    static constexpr int kPitch = BN + (SPARSE ? 8 : 4);
     static constexpr int kPlane = BM * kPitch * 4;
     static constexpr int kEpi = WAVES_K > 1 ? WAVES_K * kPlane : WAVES_M * WAVES_N * (BM / WAVES_M) * kEpiRowBytes;
     static constexpr int kTotal = kRing > kEpi ? kRing : kEpi;
     static_assert(kTotal <= 160 * 1024, "LDS budget of a CU");
 };
+
+// f(0), f(1), ... f(N - 1) with compile-time indices
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
 
 // LDS swizzles. A 16-byte read of a wave is served 16 lanes at a time over 64 four-byte banks, so
 // the 16 consecutive tile rows those lanes address (same logical chunk c) must land in 16 different
@@ -184,24 +216,23 @@ __device__ __forceinline__ float mul_add_rn(float a, float b, float add) {
 // waves takes the k blocks g, g + WAVES_K, ... with operands and accumulators of its own, and the groups'
 // tiles are added up in LDS, in the order of g, when the loop is done.
 template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false,
-          bool D64 = false, int WAVES_K = 1, bool PART = false, bool FOLDED = false>
+          int WAVES_K = 1, bool PART = false, bool FOLDED = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, const int part = 0, const int kblk0 = 0,
                                           const int kblks = 0) {
     static_assert(!PART || WAVES_K == 1, "partial sums leave from the accumulators");
-    static_assert(!D64 || (!SPARSE && MODE != 1), "64-k stages: dense kernels only");
     static_assert(MODE == 0 || (MODE == 1 && SPARSE), "mode/operand combination");
     static_assert(!FP8 || SPARSE, "FP8 operands: sparse kernels only");
     constexpr int NW = WAVES_M * WAVES_N;             // waves that share a block of operands
     constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
-    constexpr int TM = WTM / 32, TN = WTN / 32;
-    static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be made of 32x32 blocks");
-    using L = Smem<SPARSE, BM, BN, STAGES, WAVES_M, WAVES_N, FP8, D64, WAVES_K>;
+    constexpr int S = kMmaSize<SPARSE>, TM = WTM / S, TN = WTN / S;
+    static_assert(WTM % S == 0 && WTN % S == 0 && (S == 32 || TM > 1), "wave tile must be made of S x S blocks");
+    using L = Smem<SPARSE, BM, BN, STAGES, WAVES_M, WAVES_N, FP8, WAVES_K>;
+    using Acc = typename AccOf<S>::type;
+    constexpr int RB = S == 32 ? 16 : 4;              // accumulator registers of a block
     constexpr int ESZ = FP8 ? 1 : 2;                  // bytes per operand element
-    constexpr int KSTAGE = SPARSE ? 128 / ESZ : (D64 ? 64 : 32);   // dense k per stage
-    constexpr int A_ELEMS = D64 ? 64 : 64 / ESZ;      // elements of an A row per stage: 64 bytes (D64: 128)
-    constexpr int NMMA = D64 ? 2 * TM * TN : TM * TN; // matrix instructions of a sub-step
-    constexpr int MREC = L::kMetaRec;                 // metadata bytes per row and stage
+    constexpr int KSTAGE = 128 / ESZ;                 // dense k per stage
     constexpr int IXW = FP8 ? 2 : 1;                  // metadata words a lane holds per stage and row block
+    constexpr int MREC = L::kMetaRec;                 // metadata bytes per row and stage
     // one wave-wide direct-to-LDS load moves 64 chunks of 16 bytes = 1 KiB
     constexpr int A_LOADS = L::kABytes / 1024;
     static_assert(A_LOADS % NW == 0, "tile loads must divide over the waves");
@@ -241,7 +272,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
     // Sparse A is the k-major value buffer: 64 bytes per row and stage, the rows of a stage
     // contiguous, so the tile's stage is one 16 KiB run; dense A is row-major X.
     const int64_t rows_pad = a.rows_pad;    // rows per k block of the k-major operand (whole activation)
-    const int64_t a_stride = SPARSE ? rows_pad * 64 : (int64_t)(A_ELEMS * ESZ);   // bytes between stages
+    const int64_t a_stride = SPARSE ? rows_pad * 64 : (int64_t)128;   // bytes between stages
     const uint8_t* base_a = SPARSE
         ? static_cast<const uint8_t*>(a.A) + m0 * 64
         : static_cast<const uint8_t*>(a.A) + m0 * a.lda * ESZ;
@@ -256,7 +287,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
     for (int s = 0; s < A_PER_W; ++s) {
         const int p = (wave * A_PER_W + s) * 64 + lane;
         int row, c;
-        if constexpr (D64) unswz8(p, row, c); else unswz4(p, row, c);
+        if constexpr (SPARSE) unswz4(p, row, c); else unswz8(p, row, c);
         const int64_t gr = min((int64_t)row, rows_a - 1);
         // (the k-major buffer is padded to whole tiles: rows past M hold unspecified bytes whose
         //  products only reach outputs that are never stored)
@@ -267,7 +298,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
     for (int s = 0; s < B_PER_W; ++s) {
         const int p = wave * B_CH + min(s * 64 + lane, B_CH - 1);   // masked lanes of a half load: any valid chunk
         int row, c;
-        if constexpr (SPARSE || D64) unswz8(p, row, c); else unswz4(p, row, c);
+        unswz8(p, row, c);
         const int64_t gr = min((int64_t)row, rows_b - 1);
         ob[s] = (uint32_t)(gr * a.ldw * ESZ + c * 16);
     }
@@ -282,6 +313,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
     }
 
     const int64_t meta_stride = rows_pad * MREC;   // bytes between stage blocks
+    // (pinned to SGPRs here: left to itself the compiler may walk them along K in VGPRs, with two v_readfirstlane per
+    // request, which cost the bf16 loops 1.5 to 2.7 % at [4096, 3072, 12288] and [4608, 12288, 3072])
+    base_a = reinterpret_cast<const uint8_t*>(uniform64(base_a));
+    base_b = reinterpret_cast<const uint8_t*>(uniform64(base_b));
+    if constexpr (SPARSE) base_m = reinterpret_cast<const uint8_t*>(uniform64(base_m));
     // Load number n (0 .. LOADS_PER_STAGE-1) of this wave for stage kt into ring buffer `stage`.
     // The loads of a stage are issued one at a time between matrix instructions: the texture
     // addresser takes a wave-wide 1 KiB request every ~16 cycles and a wave stalls at a request
@@ -305,194 +341,139 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
                         base + L::kABytes + (wave * M_PER_W + s) * 256);
         }
     };
-    auto gload = [&](int kt, int stage) {
-        gload_one(kt, stage, std::integral_constant<int, 0>{});
-        gload_one(kt, stage, std::integral_constant<int, 1>{});
-        gload_one(kt, stage, std::integral_constant<int, 2>{});
-        gload_one(kt, stage, std::integral_constant<int, 3>{});
-        gload_one(kt, stage, std::integral_constant<int, 4>{});
-        gload_one(kt, stage, std::integral_constant<int, 5>{});
-        gload_one(kt, stage, std::integral_constant<int, 6>{});
-        gload_one(kt, stage, std::integral_constant<int, 7>{});
-        gload_one(kt, stage, std::integral_constant<int, 8>{});
-        gload_one(kt, stage, std::integral_constant<int, 9>{});
-        gload_one(kt, stage, std::integral_constant<int, 10>{});
-        gload_one(kt, stage, std::integral_constant<int, 11>{});
-        gload_one(kt, stage, std::integral_constant<int, 12>{});
-        gload_one(kt, stage, std::integral_constant<int, 13>{});
-        gload_one(kt, stage, std::integral_constant<int, 14>{});
-        gload_one(kt, stage, std::integral_constant<int, 15>{});
-    };
     constexpr int LOADS_PER_STAGE = A_PER_W + B_PER_W + (SPARSE ? M_PER_W : 0);
-    static_assert(LOADS_PER_STAGE <= 16, "unrolled by hand up to 16 loads");
+    auto gload = [&](int kt, int stage) {
+        static_for<LOADS_PER_STAGE>([&](auto n) { gload_one(kt, stage, n); });
+    };
 
     // ---- accumulators -------------------------------------------------------------------------
-    f32x16 acc[TM][TN];
+    Acc acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int r = 0; r < RB; ++r) acc[i][j][r] = 0.f;
 
-    const int li = lane & 31, kb = lane >> 5;
-    const int arow0 = wm * WTM + li;   // + i * 32
-    const int brow0 = wn * WTN + li;   // + j * 32
+    const int li = lane % S, kb = lane / S;
+    auto acc_row = [&](int r) { return S == 32 ? 8 * (r / 4) + 4 * kb + (r % 4) : 4 * kb + r; };   // row of register r inside its block
+    const int arow0 = wm * WTM + li;   // + i * S
+    const int brow0 = wn * WTN + li;   // + j * S
 
-    // operand fragments of one sub-step
+    // ---- sparse: a stage in two halves of k. Two sets of fragments, one per half, each filled half a stage ahead ------------
     struct Frags {
-        std::conditional_t<D64, Frag16, Frag8> a[TM];   // D64: two 16-k halves
-        Frag16 b[TN];   // dense kernel with 32-k stages uses b[j].u[0] only
-    };
-    // metadata words of the current / next stage (sparse only); FP8: word 2 i + sub of row block i
-    int ix_cur[TM * IXW], ix_nxt[TM * IXW];
-
-    auto read_frags = [&](int stage, int sub, Frags& f) {
+        Frag8 a[TM];
+        Frag16 b[TN];
+    } f[SPARSE ? 2 : 1];
+    int ix[TM * IXW], ix_nxt[TM * IXW];      // metadata words of this and the next stage; FP8: word 2 i + half of row block i
+    // LDS read e behind the matrix instructions of half H: the fragments of the other half (H = 0: second half of this
+    // stage, H = 1: first half of the next), metadata words first, then A fragments, then B column block by column block.
+    auto read_half = [&](int stage, auto h_tag, auto e_tag) {
+        constexpr int SUB = 1 - decltype(h_tag)::value, e = decltype(e_tag)::value, NI = SUB == 0 ? TM : 0;
         const uint8_t* base = stage_base(stage);
         const uint8_t* bB = base + L::kABytes + L::kMetaBytes;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            if constexpr (D64) {
-                f.a[i].u[0] = *reinterpret_cast<const uint4*>(base + swz8(arow0 + i * 32, 4 * sub + kb));
-                f.a[i].u[1] = *reinterpret_cast<const uint4*>(base + swz8(arow0 + i * 32, 4 * sub + 2 + kb));
-            } else {
-                f.a[i].u = *reinterpret_cast<const uint4*>(base + swz4(arow0 + i * 32, 2 * (SPARSE ? kb : sub) + (SPARSE ? sub : kb)));
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int row = brow0 + j * 32;
-            if constexpr (D64) {
-                f.b[j].u[0] = *reinterpret_cast<const uint4*>(bB + swz8(row, 4 * sub + kb));
-                f.b[j].u[1] = *reinterpret_cast<const uint4*>(bB + swz8(row, 4 * sub + 2 + kb));
-            } else if constexpr (SPARSE) {
-                f.b[j].u[0] = *reinterpret_cast<const uint4*>(bB + swz8(row, 2 * sub + kb));
-                f.b[j].u[1] = *reinterpret_cast<const uint4*>(bB + swz8(row, 4 + 2 * sub + kb));
-            } else {
-                f.b[j].u[0] = *reinterpret_cast<const uint4*>(bB + swz4(row, 2 * sub + kb));
-            }
-        }
-    };
-    auto read_idx = [&](int stage, int (&ix)[TM * IXW]) {
-        if constexpr (SPARSE) {
-            const uint8_t* bM = stage_base(stage) + L::kABytes;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                if constexpr (FP8) {
-                    const int2 w = *reinterpret_cast<const int2*>(bM + (arow0 + i * 32) * 16 + kb * 8);
-                    ix[2 * i] = w.x;
-                    ix[2 * i + 1] = w.y;
-                } else {
-                    ix[i] = *reinterpret_cast<const int*>(bM + (arow0 + i * 32) * 8 + kb * 4);
-                }
-            }
-        }
-    };
-    // Read number n of the fragment set of (stage, SUB), in the order the matrix instructions need
-    // them: metadata words (sub-step 0 only), A fragments, then B fragments column block by block.
-    auto read_one = [&](int stage, auto sub_tag, Frags& f, int (&ix)[TM * IXW], auto n_tag) {
-        constexpr int SUB = decltype(sub_tag)::value, n = decltype(n_tag)::value;
-        constexpr int NI = (SPARSE && SUB == 0) ? TM : 0;     // metadata reads first
-        const uint8_t* base = stage_base(stage);
-        const uint8_t* bB = base + L::kABytes + L::kMetaBytes;
-        if constexpr (n < NI) {
+        if constexpr (e < NI) {
+            const uint8_t* rec = base + L::kABytes + (arow0 + e * S) * MREC;
             if constexpr (FP8) {
-                const int2 w = *reinterpret_cast<const int2*>(base + L::kABytes + (arow0 + n * 32) * 16 + kb * 8);
-                ix[2 * n] = w.x;
-                ix[2 * n + 1] = w.y;
+                const int2 w = reinterpret_cast<const int2*>(rec)[kb];
+                ix_nxt[2 * e] = w.x;
+                ix_nxt[2 * e + 1] = w.y;
             } else {
-                ix[n] = *reinterpret_cast<const int*>(base + L::kABytes + (arow0 + n * 32) * 8 + kb * 4);
+                ix_nxt[e] = reinterpret_cast<const int*>(rec)[kb];
             }
-        } else if constexpr (D64) {
-            // 16-k half h of every fragment, first halves first (the order the instructions use them)
-            constexpr int h = n / (TM + TN), m = n % (TM + TN);
-            if constexpr (h < 2 && m < TM)
-                f.a[m].u[h] = *reinterpret_cast<const uint4*>(base + swz8(arow0 + m * 32, 4 * SUB + 2 * h + kb));
-            else if constexpr (h < 2)
-                f.b[m - TM].u[h] = *reinterpret_cast<const uint4*>(bB + swz8(brow0 + (m - TM) * 32, 4 * SUB + 2 * h + kb));
-        } else if constexpr (n < NI + TM) {
-            constexpr int i = n - NI;
-            f.a[i].u = *reinterpret_cast<const uint4*>(
-                base + swz4(arow0 + i * 32, SPARSE ? 2 * kb + SUB : 2 * SUB + kb));
-        } else if constexpr (SPARSE && n < NI + TM + 2 * TN) {
-            constexpr int m = n - NI - TM, j = m / 2, h = m % 2;
-            f.b[j].u[h] = *reinterpret_cast<const uint4*>(bB + swz8(brow0 + j * 32, 4 * h + 2 * SUB + kb));
-        } else if constexpr (!SPARSE && n < TM + TN) {
-            constexpr int j = n - TM;
-            f.b[j].u[0] = *reinterpret_cast<const uint4*>(bB + swz4(brow0 + j * 32, 2 * SUB + kb));
+        } else if constexpr (e < NI + TM) {
+            f[SUB].a[e - NI].u = *reinterpret_cast<const uint4*>(base + swz4(arow0 + (e - NI) * S, 2 * kb + SUB));
+        } else if constexpr (e < NI + TM + 2 * TN) {
+            constexpr int j = (e - NI - TM) / 2, c = (e - NI - TM) % 2;
+            f[SUB].b[j].u[c] = *reinterpret_cast<const uint4*>(bB + swz8(brow0 + j * S, 4 * c + 2 * SUB + kb));
         }
     };
-    auto mma_one = [&](const Frags& f, const int (&ix)[TM * IXW], auto sub_tag, auto n_tag) {
-        constexpr int SUB = decltype(sub_tag)::value;
-        constexpr int n = decltype(n_tag)::value;
-        constexpr int blk = n % (TM * TN), half = n / (TM * TN);   // half: 16-k half of a D64 sub-step
-        constexpr int i = blk % TM, j = blk / TM;
-        if constexpr (D64) {
-            if constexpr (n < NMMA) {
-                if constexpr (half == 0)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf16x8(f.a[i].v.lo), bf16x8(f.b[j].v.lo),
-                                                                        acc[i][j], 0, 0, 0);
-                else
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf16x8(f.a[i].v.hi), bf16x8(f.b[j].v.hi),
-                                                                        acc[i][j], 0, 0, 0);
-            }
-        } else {
-            if constexpr (n < TM * TN) {
-                if constexpr (FP8)
-                    acc[i][j] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(f.a[i].q, f.b[j].q, acc[i][j],
-                                                                             ix[2 * i + SUB], 0, 0);
-                else if constexpr (SPARSE)
-                    acc[i][j] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(f.a[i].v, f.b[j].v, acc[i][j],
-                                                                          ix[i], 0, SUB);
-                else
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i].v, bf16x8(f.b[j].v.lo),
-                                                                        acc[i][j], 0, 0, 0);
-            }
-        }
+    // Half H of a stage's matrix work. Behind each matrix instruction go two of the LDS reads above (when READ) and one of
+    // the ring-refill requests LO <= n < HI of stage kt_load into ring buffer buf. Spreading both keeps the LDS command
+    // queue and the texture addresser from filling up, which would stall the wave in front of its next matrix instruction.
+    constexpr int NMMA = TM * TN;
+    auto half = [&](auto h_tag, auto read_tag, int rstage, auto lo_tag, auto hi_tag, int kt_load, int buf) {
+        constexpr int H = decltype(h_tag)::value, LO = decltype(lo_tag)::value, CNT = decltype(hi_tag)::value - LO;
+        constexpr int LPM = (CNT + NMMA - 1) / NMMA;          // requests behind each matrix instruction (one, but for small wave tiles)
+        constexpr int READS = (H == 1 ? TM : 0) + TM + 2 * TN;
+        static_for<NMMA>([&](auto n_tag) {
+            constexpr int n = decltype(n_tag)::value, i = n % TM, j = n / TM;
+            if constexpr (!SPARSE) return;
+            else if constexpr (FP8)
+                acc[i][j] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(f[H].a[i].q, f[H].b[j].q, acc[i][j], ix[2 * i + H], 0, 0);
+            else
+                acc[i][j] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(f[H].a[i].v, f[H].b[j].v, acc[i][j], ix[i], 0, H);
+            constexpr int e1 = n == NMMA - 1 ? READS : 2 * n + 2;
+            if constexpr (decltype(read_tag)::value)
+                static_for<(e1 > 2 * n ? e1 - 2 * n : 0)>([&](auto e) { read_half(rstage, h_tag, std::integral_constant<int, 2 * n + decltype(e)::value>{}); });
+            constexpr int g0 = n * LPM < CNT ? n * LPM : CNT, g1 = (n + 1) * LPM < CNT ? (n + 1) * LPM : CNT;
+            static_for<g1 - g0>([&](auto e) { gload_one(kt_load, buf, std::integral_constant<int, LO + g0 + decltype(e)::value>{}); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
     };
-    // Matrix work of sub-step SUB on fragments f. After each matrix instruction the wave issues two
-    // LDS reads of the NEXT fragment set (rstage, RSUB) into rf / rix (when READ), and one of the
-    // ring-refill requests LO <= n < HI of stage kt_load into ring buffer buf. Spreading both keeps
-    // the LDS command queue and the texture addresser from filling up, which would stall the wave
-    // in front of its next matrix instruction.
-    auto mma = [&](const Frags& f, const int (&ix)[TM * IXW], auto sub_tag, auto read_tag, auto rsub_tag,
-                   int rstage, Frags& rf, int (&rix)[TM * IXW], auto lo_tag, auto hi_tag, int kt_load, int buf) {
-        constexpr int LO = decltype(lo_tag)::value, HI = decltype(hi_tag)::value;
-        constexpr bool READ = decltype(read_tag)::value;
-        static_assert(NMMA <= 16, "unrolled by hand up to 16 matrix instructions");
-        constexpr int LPM = (HI - LO + NMMA - 1) / NMMA;      // requests behind each matrix instruction (one, but for small wave tiles)
-        static_assert(((SPARSE || D64) ? 2 * TM + 2 * TN : TM + TN) <= 2 * NMMA + 2, "two reads per matrix instruction must cover a fragment set");
-#define RTL_MMA_STEP(N)                                                                       \
-        mma_one(f, ix, sub_tag, std::integral_constant<int, N>{});                            \
-        if constexpr (N < NMMA) {                                                             \
-            if constexpr (READ) {                                                             \
-                read_one(rstage, rsub_tag, rf, rix, std::integral_constant<int, 2 * N>{});     \
-                read_one(rstage, rsub_tag, rf, rix, std::integral_constant<int, 2 * N + 1>{}); \
-                if constexpr (N == NMMA - 1) {                                                \
-                    read_one(rstage, rsub_tag, rf, rix, std::integral_constant<int, 2 * N + 2>{}); \
-                    read_one(rstage, rsub_tag, rf, rix, std::integral_constant<int, 2 * N + 3>{}); \
-                }                                                                             \
-            }                                                                                 \
-            if constexpr (LPM >= 1 && LO + N * LPM < HI) gload_one(kt_load, buf, std::integral_constant<int, LO + N * LPM>{}); \
-            if constexpr (LPM >= 2 && LO + N * LPM + 1 < HI) gload_one(kt_load, buf, std::integral_constant<int, LO + N * LPM + 1>{}); \
-            if constexpr (LPM >= 3 && LO + N * LPM + 2 < HI) gload_one(kt_load, buf, std::integral_constant<int, LO + N * LPM + 2>{}); \
-            if constexpr (LPM >= 4 && LO + N * LPM + 3 < HI) gload_one(kt_load, buf, std::integral_constant<int, LO + N * LPM + 3>{}); \
-            __builtin_amdgcn_sched_barrier(0);                                                \
+
+    // ---- dense: a stage row block by row block, two matrix instructions (chunks of k) per block, the barrier behind the first
+    //      R0 row blocks. One set of fragments: the A registers of a row block are refilled for the next stage behind its last
+    //      matrix instruction, the B registers behind theirs in the last row block (two sets would not fit beside
+    //      256 x 256 accumulators) -----------------------------------------------------------------------------------
+    constexpr int R0 = TM >= 4 ? 2 : 1, ROW = 2 * TN, M1 = (TM - R0) * ROW;       // ROW: matrix instructions of a row block
+    Frag16 fa[SPARSE ? 1 : TM], fb[SPARSE ? 1 : TN];
+    // LDS read e of a stage: 0 .. 2 TM - 1 the two chunks of each row block, then the chunks of the columns in the order in
+    // which the last row block is done with them.
+    constexpr int A_RD = 2 * TM, B_RD = 2 * TN;
+    auto read_row = [&](int stage, auto e_tag) {
+        constexpr int e = decltype(e_tag)::value;
+        const uint8_t* base = stage_base(stage);
+        const uint8_t* bB = base + L::kABytes;
+        if constexpr (e < A_RD)
+            fa[e / 2].u[e % 2] = *reinterpret_cast<const uint4*>(base + swz8(arow0 + e / 2 * S, 4 * (e % 2) + kb));
+        else
+            fb[(e - A_RD) % TN].u[(e - A_RD) / TN] =
+                *reinterpret_cast<const uint4*>(bB + swz8(brow0 + (e - A_RD) % TN * S, 4 * ((e - A_RD) / TN) + kb));
+    };
+    // Which of them go behind which of the M1 matrix instructions that follow the barrier: as soon as their registers are
+    // free, evenly spread. (The last row block's two follow the first matrix instructions of the next stage.)
+    struct Slots {
+        int item[M1][4], count[M1], total;
+    };
+    static constexpr Slots kSlots = [] {
+        Slots t{};
+        int a = 0, b = 0;
+        for (int m = 0; m < M1; ++m) {
+            const int left = A_RD - 2 + B_RD - t.total;
+            for (int budget = (left + M1 - m - 1) / (M1 - m); budget > 0 && t.count[m] < 4; --budget) {
+                const int rows = R0 + m / ROW;                               // row blocks done with their registers
+                if (a < 2 * (rows < TM - 1 ? rows : TM - 1)) t.item[m][t.count[m]++] = a++;
+                else if (b < B_RD && b <= m - (M1 - ROW)) t.item[m][t.count[m]++] = A_RD + b++;
+                else break;
+                ++t.total;
+            }
         }
-        RTL_MMA_STEP(0) RTL_MMA_STEP(1) RTL_MMA_STEP(2) RTL_MMA_STEP(3)
-        RTL_MMA_STEP(4) RTL_MMA_STEP(5) RTL_MMA_STEP(6) RTL_MMA_STEP(7)
-        RTL_MMA_STEP(8) RTL_MMA_STEP(9) RTL_MMA_STEP(10) RTL_MMA_STEP(11)
-        RTL_MMA_STEP(12) RTL_MMA_STEP(13) RTL_MMA_STEP(14) RTL_MMA_STEP(15)
-#undef RTL_MMA_STEP
+        return t;
+    }();
+    static_assert(SPARSE || kSlots.total == A_RD - 2 + B_RD, "every read has a slot");
+    auto mma_row = [&](auto i_tag, auto n_tag) {             // matrix instruction n of row block i
+        constexpr int i = decltype(i_tag)::value, n = decltype(n_tag)::value, j = n % TN, c = n / TN;
+        const bf16x16 x = fa[i].v, y = fb[j].v;
+        acc[i][j] = dense_mma<S>(c == 0 ? bf16x8(x.lo) : bf16x8(x.hi), c == 0 ? bf16x8(y.lo) : bf16x8(y.hi), acc[i][j]);
+    };
+    // Requests LO <= n < HI of stage kt_load behind the first HI - LO of every D-th of NM matrix instructions (spread evenly
+    // where that does not reach). D = 1 / 2 / 3 / 4 / even, us: [4608, 9216, 3072] 226.0 / 217.3 / 216.4 / 217.3 / 218.3, [4096,
+    // 3072, 12288] 279.0 / 261.3 / 262.0 / 265.2, [4608, 3072, 3072] 85.1 / 80.4 / 81.2 / 81.9: a late one arrives late.
+    auto requests = [&](auto n_tag, auto nm_tag, auto lo_tag, auto hi_tag, int kt_load, int buf) {
+        constexpr int n = decltype(n_tag)::value, NM = decltype(nm_tag)::value, LO = decltype(lo_tag)::value, CNT = decltype(hi_tag)::value - LO;
+        constexpr int D = CNT > 0 && NM >= 2 * CNT ? 2 : 1;
+        constexpr int g0 = D > 1 ? (n + D - 1) / D : n * CNT / NM, g1 = D > 1 ? n / D + 1 : (n + 1) * CNT / NM;
+        static_for<(g0 < g1 && (D == 1 || g0 < CNT) ? g1 - g0 : 0)>(
+            [&](auto e) { gload_one(kt_load, buf, std::integral_constant<int, LO + g0 + decltype(e)::value>{}); });
     };
 
     // The barrier of a stage. A group of one wave shares its ring with nobody: its own waits are enough.
     auto stage_barrier = [&]() {
+        asm volatile("" ::: "memory");
         if constexpr (NW > 1) __builtin_amdgcn_s_barrier();
-        else asm volatile("" ::: "memory");
+        asm volatile("" ::: "memory");
     };
-    constexpr int kMaxLpm = 4;
-    static_assert((LOADS_PER_STAGE + 1) / 2 <= kMaxLpm * NMMA && (STAGES > 2 || LOADS_PER_STAGE <= kMaxLpm * NMMA), "every request has a slot behind a matrix instruction");
 
     // ---- prologue: the whole ring in flight, stage 0 visible ----------------------------------
 #pragma unroll
@@ -502,51 +483,66 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
     else wait_vmcnt_lgkm0<0>();
     stage_barrier();
 
-    Frags f0, f1;
     if (WAVES_K == 1 || KT > 0) {
-        read_frags(0, 0, f0);
-        read_idx(0, ix_cur);
+        if constexpr (SPARSE) {
+            static_for<2 * TM + 2 * TN>([&](auto e) { read_half(0, std::integral_constant<int, 1>{}, e); });
+#pragma unroll
+            for (int i = 0; i < TM * IXW; ++i) ix[i] = ix_nxt[i];
+        } else {
+            static_for<A_RD - 2>([&](auto e) { read_row(0, e); });
+            static_for<B_RD>([&](auto e) { read_row(0, std::integral_constant<int, A_RD + decltype(e)::value>{}); });
+        }
     }
-    wait_vmcnt_lgkm0<63>();            // fragments of sub-step 0 are in registers
+    wait_vmcnt_lgkm0<63>();            // first fragments are in registers
 
     // One stage of the main loop. Schedule inside a stage kt:
-    //   read fragments of sub-step 1 |
-    //   matrix work of sub-step 0, interleaved with the second part of the requests of stage
-    //   kt+STAGES-1 (its buffer, the one of stage kt-1, was released by the previous barrier) |
+    //   matrix work of the first part, interleaved with the rest of the reads of stage kt and the second part of the
+    //   requests of stage kt+STAGES-1 (its buffer, the one of stage kt-1, was released by the previous barrier) |
     //   wait: own reads of stage kt done, stage kt+1 landed | barrier |
-    //   read fragments of stage kt+1 sub-step 0 |
-    //   matrix work of sub-step 1, interleaved with the first part of the requests of stage
-    //   kt+STAGES (into the buffer of stage kt, which nobody reads any more).
+    //   matrix work of the second part, interleaved with the first reads of stage kt+1 and the first part of the
+    //   requests of stage kt+STAGES (into the buffer of stage kt, which nobody reads any more).
     // Every stage has about two stage times to arrive and the request stream never bursts.
     // PENDING: whole stages younger than kt+1 in flight at the wait (compile-time per phase).
-    // requests issued in the second half. A ring of two has no buffer to spare for the early part:
+    // SPLIT: requests issued in the second half. A ring of two has no buffer to spare for the early part:
     // all requests of stage kt+2 go out after the barrier of stage kt, one stage time ahead.
     constexpr int SPLIT = STAGES == 2 ? LOADS_PER_STAGE : (LOADS_PER_STAGE + 1) / 2;
     using c0 = std::integral_constant<int, 0>;
+    using c1 = std::integral_constant<int, 1>;
     using cS = std::integral_constant<int, SPLIT>;
     using cL = std::integral_constant<int, LOADS_PER_STAGE>;
     using T = std::true_type;
     using F = std::false_type;
     int cur = 0;                       // LDS buffer of stage kt
     auto stage_step = [&](int kt, auto load_a, auto load_b, auto has_next, auto pending) {
-        constexpr bool LOAD_A = decltype(load_a)::value, LOAD_B = decltype(load_b)::value;
-        constexpr bool HAS_NEXT = decltype(has_next)::value;
+        constexpr bool LOAD_A = decltype(load_a)::value, LOAD_B = decltype(load_b)::value, HAS_NEXT = decltype(has_next)::value;
         constexpr int PENDING = decltype(pending)::value;
         const int nxt = cur + 1 == STAGES ? 0 : cur + 1;
         const int prv = cur == 0 ? STAGES - 1 : cur - 1;
-        using s0 = std::integral_constant<int, 0>;
-        using s1 = std::integral_constant<int, 1>;
-        // sub-step 0 runs while the fragments of sub-step 1 are fetched
-        if constexpr (LOAD_A) mma(f0, ix_cur, s0{}, T{}, s1{}, cur, f1, ix_nxt, cS{}, cL{}, kt + STAGES - 1, prv);
-        else mma(f0, ix_cur, s0{}, T{}, s1{}, cur, f1, ix_nxt, c0{}, c0{}, 0, 0);
+        using a_lo = std::conditional_t<LOAD_A, cS, c0>;
+        using a_hi = std::conditional_t<LOAD_A, cL, c0>;
+        using b_hi = std::conditional_t<LOAD_B, cS, c0>;
+        if constexpr (SPARSE) half(c0{}, T{}, cur, a_lo{}, a_hi{}, kt + STAGES - 1, prv);
+        else static_for<R0 * ROW>([&](auto n) {
+            constexpr int m = decltype(n)::value;
+            mma_row(std::integral_constant<int, m / ROW>{}, std::integral_constant<int, m % ROW>{});
+            if constexpr (m < 2) read_row(cur, std::integral_constant<int, A_RD - 2 + m>{});
+            requests(n, std::integral_constant<int, R0 * ROW>{}, a_lo{}, a_hi{}, kt + STAGES - 1, prv);
+            __builtin_amdgcn_sched_barrier(0);
+        });
         wait_vmcnt_lgkm0<PENDING * LOADS_PER_STAGE>();
         stage_barrier();
-        // sub-step 1 runs while the first fragments (and metadata) of stage kt+1 are fetched
-        if constexpr (LOAD_B) mma(f1, ix_cur, s1{}, std::integral_constant<bool, HAS_NEXT>{}, s0{}, nxt, f0, ix_nxt, c0{}, cS{}, kt + STAGES, cur);
-        else mma(f1, ix_cur, s1{}, std::integral_constant<bool, HAS_NEXT>{}, s0{}, nxt, f0, ix_nxt, c0{}, c0{}, 0, 0);
-        if constexpr (SPARSE && HAS_NEXT) {
+        if constexpr (SPARSE) half(c1{}, has_next, nxt, c0{}, b_hi{}, kt + STAGES, cur);
+        else static_for<M1>([&](auto n) {
+            constexpr int m = decltype(n)::value;
+            mma_row(std::integral_constant<int, R0 + m / ROW>{}, std::integral_constant<int, m % ROW>{});
+            if constexpr (HAS_NEXT)
+                static_for<kSlots.count[m]>([&](auto e) { read_row(nxt, std::integral_constant<int, kSlots.item[m][decltype(e)::value]>{}); });
+            requests(n, std::integral_constant<int, M1>{}, c0{}, b_hi{}, kt + STAGES, cur);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (HAS_NEXT && SPARSE) {
 #pragma unroll
-            for (int i = 0; i < TM * IXW; ++i) ix_cur[i] = ix_nxt[i];
+            for (int i = 0; i < TM * IXW; ++i) ix[i] = ix_nxt[i];
         }
         cur = nxt;
     };
@@ -585,15 +581,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
         wait_vmcnt_lgkm0<0>();
         __syncthreads();                         // the ring is free
         float* const planes = reinterpret_cast<float*>(smem);
-        auto put_plane = [&](const f32x16 (&v)[TM][TN]) {    // this wave's block of its group's plane
+        auto put_plane = [&](const Acc (&v)[TM][TN]) {       // this wave's block of its group's plane
             float* p = planes + wk * (L::kPlane / 4);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)             // register r is row 8 (r / 4) + 4 kb + r % 4 of column li
-                        p[(wm * WTM + i * 32 + 8 * (r / 4) + 4 * kb + (r % 4)) * L::kPitch + wn * WTN + j * 32 + li] = v[i][j][r];
+                    for (int r = 0; r < RB; ++r)
+                        p[(wm * WTM + i * S + acc_row(r)) * L::kPitch + wn * WTN + j * S + li] = v[i][j][r];
         };
         constexpr int THREADS = NW * WAVES_K * 64;
         constexpr int CPR = BN / 8, CHUNKS = BM * CPR;       // a thread finishes runs of 8 columns
@@ -617,31 +613,31 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
         }
         float res[MODE == 1 ? PER : 1][8];
         if constexpr (MODE == 1) {
-            // Residual Y_r = T L_A^T (T = X L_B^T as two bf16 planes hi + lo, rank 64): eight steps of 16 ranks
-            // (four per plane) dealt over the K groups, operands straight from memory (a few KB that sit in L2),
+            // Residual Y_r = T L_A^T (T = X L_B^T as two bf16 planes hi + lo, rank 64): steps of 16 or 32 ranks
+            // dealt over the K groups, operands straight from memory (a few KB that sit in L2),
             // added up through the same planes. The factors belong to the sparse product only.
-            f32x16 t[TM][TN];
+            constexpr int RANKS = 512 / S, STEPS = 2 * kLoraRank / RANKS;        // ranks of a step; steps of both planes
+            Acc t[TM][TN];
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) t[i][j][r] = 0.f;
-            for (int s = wk; s < 8; s += WAVES_K) {
+                    for (int r = 0; r < RB; ++r) t[i][j][r] = 0.f;
+            for (int s = wk; s < STEPS; s += WAVES_K) {
                 const uint16_t* tp = a.T + (s & 1 ? 0 : a.t_plane);      // lo plane first
-                const int col = (s >> 1) * 16 + 8 * kb;
-                Frag8 fa[TM], fb[TN];
+                const int col = (s >> 1) * RANKS + 8 * kb;
+                Frag8 ft[TM], fl[TN];
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
-                    fa[i].u = *reinterpret_cast<const uint4*>(tp + min(m0 + arow0 + i * 32, a.M - 1) * kLoraRank + col);
+                    ft[i].u = *reinterpret_cast<const uint4*>(tp + min(m0 + arow0 + i * S, a.M - 1) * kLoraRank + col);
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    fb[j].u = *reinterpret_cast<const uint4*>(a.LA + min(n0 + brow0 + j * 32, a.N - 1) * a.ldla + col);
+                    fl[j].u = *reinterpret_cast<const uint4*>(a.LA + min(n0 + brow0 + j * S, a.N - 1) * a.ldla + col);
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int i = 0; i < TM; ++i)
-                        t[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i].v, fb[j].v, t[i][j], 0, 0, 0);
+                    for (int i = 0; i < TM; ++i) t[i][j] = dense_mma<S>(ft[i].v, fl[j].v, t[i][j]);
             }
             __syncthreads();                                 // the sparse planes have been read
             put_plane(t);
@@ -712,13 +708,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
         // ---- LoRA tail (Alg. 1: Y <- Y_s + Y_r, accumulated on chip) --------------------------
         // The ROW / TENSOR factors belong to the sparse product only, so they are applied to the
         // accumulators first. Then Y_r = T L_A^T, T = X L_B^T (bf16 [M,64]), is added by four dense
-        // matrix-instruction steps over the rank; SMFMAC and MFMA 32x32 share one accumulator layout.
+        // matrix-instruction steps over the rank; SMFMAC and MFMA of one size share one accumulator layout.
         if (a.row_scale || has_tensor_scale) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t row = min(m0 + wm * WTM + i * 32 + 8 * (r / 4) + 4 * kb + (r % 4), a.M - 1);
+                for (int r = 0; r < RB; ++r) {
+                    const int64_t row = min(m0 + wm * WTM + i * S + acc_row(r), a.M - 1);
                     const float f = (a.row_scale ? a.row_scale[row] : 1.0f) * ts;
 #pragma unroll
                     for (int j = 0; j < TN; ++j) acc[i][j][r] *= f;
@@ -728,7 +724,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
         wait_vmcnt_lgkm0<0>();
         __builtin_amdgcn_s_barrier();          // the ring is free: reuse it for the two rank tiles
         constexpr int T_LOADS = BM * 128 / 1024, LA_LOADS = BN * 128 / 1024;   // rows of 64 bf16
-        static_assert(T_LOADS % NW == 0 && LA_LOADS % NW == 0, "rank tiles must divide over the waves");
+        static_assert(T_LOADS % NW == 0, "rank tiles must divide over the waves");
         static_assert((2 * BM + BN) * 128 <= L::kTotal, "rank tiles fit in the ring");
         const int64_t plane = a.t_plane;                // T is two bf16 planes: hi, lo
 #pragma unroll
@@ -742,48 +738,49 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
                           lds0 + h * BM * 128 + (wave * (T_LOADS / NW) + s) * 1024);
             }
 #pragma unroll
-        for (int s = 0; s < LA_LOADS / NW; ++s) {
-            const int p = (wave * (LA_LOADS / NW) + s) * 64 + lane;
+        for (int s = 0; s < (LA_LOADS + NW - 1) / NW; ++s) {
+            const int unit = s * NW + wave;
+            if (unit >= LA_LOADS) break;
+            const int p = unit * 64 + lane;
             int row, c;
             unswz8(p, row, c);
-            lds_dma16(a.LA + min(n0 + row, a.N - 1) * a.ldla + c * 8,
-                      lds0 + 2 * BM * 128 + (wave * (LA_LOADS / NW) + s) * 1024);
+            lds_dma16(a.LA + min(n0 + row, a.N - 1) * a.ldla + c * 8, lds0 + 2 * BM * 128 + unit * 1024);
         }
         wait_vmcnt_lgkm0<0>();
         __builtin_amdgcn_s_barrier();
 #pragma unroll
-        for (int sub = 0; sub < kLoraRank / 16; ++sub) {
-            Frag8 th[TM], tl[TM], lb[TN];
+        for (int sub = 0; sub < kLoraRank * S / 512; ++sub) {      // 512 / S ranks each
+            Frag8 lb[TN];
+            const int c = 64 / S * sub + kb;
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                th[i].u = *reinterpret_cast<const uint4*>(smem + swz8(arow0 + i * 32, 2 * sub + kb));
-                tl[i].u = *reinterpret_cast<const uint4*>(smem + BM * 128 + swz8(arow0 + i * 32, 2 * sub + kb));
+            for (int j = 0; j < TN; ++j)
+                lb[j].u = *reinterpret_cast<const uint4*>(smem + 2 * BM * 128 + swz8(brow0 + j * S, c));
+#pragma unroll
+            for (int h = 1; h >= 0; --h) {             // lo plane first
+                Frag8 t[TM];
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    t[i].u = *reinterpret_cast<const uint4*>(smem + h * BM * 128 + swz8(arow0 + i * S, c));
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) acc[i][j] = dense_mma<S>(t[i].v, lb[j].v, acc[i][j]);
             }
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                lb[j].u = *reinterpret_cast<const uint4*>(smem + 2 * BM * 128 + swz8(brow0 + j * 32, 2 * sub + kb));
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tl[i].v, lb[j].v, acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(th[i].v, lb[j].v, acc[i][j], 0, 0, 0);
-                }
         }
       }
     }
 
     if constexpr (PART) {
-        // 32 lanes of a register hold 32 neighbouring columns of one row: whole 128-byte lines
+        // S lanes of a register hold S neighbouring columns of one row
         float* plane = a.partials + (int64_t)part * a.M * a.part_pitch;
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            const int64_t col = n0 + wn * WTN + j * 32 + li;
+            const int64_t col = n0 + wn * WTN + j * S + li;
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t row = m0 + wm * WTM + i * 32 + 8 * (r / 4) + 4 * kb + (r % 4);
+                for (int r = 0; r < RB; ++r) {
+                    const int64_t row = m0 + wm * WTM + i * S + acc_row(r);
                     if (row < a.M && col < a.N) plane[row * a.part_pitch + col] = acc[i][j][r];
                 }
         }
@@ -808,28 +805,31 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
         wait_vmcnt_lgkm0<0>();
         __builtin_amdgcn_s_barrier();     // every wave is done reading the ring
         uint8_t* ep = smem + wave * (WTM * ROWB);
-        // Two accumulator registers (rows r, r + 1 of one column) are converted by one packed
-        // fp32 -> bf16 instruction (round to nearest even) and leave as two 16-bit LDS writes. The
-        // plain case (no factors, no bias) is kept free of any other per-element work: with 128
-        // elements per lane the epilogue is otherwise bound by its vector ALU work, not by stores.
+        // Two accumulator registers (rows r, r + PS of one column) are converted by one packed
+        // fp32 -> bf16 instruction (round to nearest even). The plain case (no factors, no bias) is kept
+        // free of any other per-element work: with 128 elements per lane the epilogue is otherwise bound
+        // by its vector ALU work, not by stores.
         typedef float f32x2 __attribute__((ext_vector_type(2)));
         typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        // A lane holds rows rl, rl + 1 of ONE column; its neighbour (lane ^ 1) holds the same rows
+        // A lane holds rows rl, rl + PS of ONE column; its neighbour (lane ^ 1) holds the same rows
         // of the next column. The pair swaps halves (one DPP move, one byte permute) so that the
-        // even lane owns row rl and the odd lane row rl + 1 of BOTH columns: one 32-bit LDS write
-        // per lane instead of two 16-bit ones.
+        // even lane owns row rl and the odd lane row rl + PS of BOTH columns: one 32-bit LDS write
+        // per lane instead of two 16-bit ones. (S = 16: rows two apart, so that the eight runs of eight words that one
+        // write consists of fall into different banks.)
+        constexpr int PS = S == 32 ? 1 : 2;
         const bool odd = lane & 1;
         const uint32_t sel = odd ? 0x03020706u : 0x05040100u;   // v_perm_b32: bytes 0-3 = own, 4-7 = partner
-        const int rsel = odd ? ROWB : 0;                        // odd lanes write the row below
+        const int rsel = odd ? PS * ROWB : 0;                   // odd lanes write the row PS below
         auto put2 = [&](float v0, float v1, int rl, int cl) {
             const f32x2 pv = {v0, v1};
             const uint32_t own = __builtin_bit_cast(uint32_t, __builtin_convertvector(pv, bf16x2));
             const uint32_t partner = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);
             // even: (own.lo, partner.lo) = row rl, columns (cl, cl + 1)
-            // odd : (partner.hi, own.hi) = row rl + 1, columns (cl - 1, cl)
+            // odd : (partner.hi, own.hi) = row rl + PS, columns (cl - 1, cl)
             const uint32_t w = __builtin_amdgcn_perm(partner, own, sel);
             *reinterpret_cast<uint32_t*>(ep + rl * ROWB + rsel + (cl & ~1) * 2) = w;
         };
+        auto first_of_pair = [](int q) { return S == 32 ? 2 * q : q; };     // registers r, r + PS, q = 0 .. RB / 2 - 1
         const bool scaled = MODE != 1 && (a.row_scale || has_tensor_scale);
         if (!scaled && !a.bias) {
 #pragma unroll
@@ -837,32 +837,34 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int r = 0; r < 16; r += 2)
-                        put2(acc[i][j][r], acc[i][j][r + 1], i * 32 + 8 * (r / 4) + 4 * kb + (r % 4), j * 32 + li);
+                    for (int q = 0; q < RB / 2; ++q) {
+                        const int r = first_of_pair(q);
+                        put2(acc[i][j][r], acc[i][j][r + PS], i * S + acc_row(r), j * S + li);
+                    }
         } else {
-            // the factors of the lane's 16 rows per row block are fetched once, not once per column block,
+            // the factors of the lane's rows per row block are fetched once, not once per column block,
             // four consecutive rows per load, all loads in flight together
             float bv[TN];
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const int64_t col = min(n0 + wn * WTN + j * 32 + li, a.N - 1);
+                const int64_t col = min(n0 + wn * WTN + j * S + li, a.N - 1);
                 bv[j] = a.bias ? __uint_as_float((uint32_t)a.bias[col] << 16) : 0.f;
             }
-            float f[TM][16];
+            float fr[TM][RB];
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {       // registers 4 q .. 4 q + 3 are four consecutive rows
-                    const int64_t row = m0 + wm * WTM + i * 32 + 8 * q + 4 * kb;
+                for (int q = 0; q < RB / 4; ++q) {  // registers 4 q .. 4 q + 3 are four consecutive rows
+                    const int64_t row = m0 + wm * WTM + i * S + acc_row(4 * q);
                     if (!scaled || !a.row_scale) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) f[i][4 * q + e] = 1.0f;
+                        for (int e = 0; e < 4; ++e) fr[i][4 * q + e] = 1.0f;
                     } else if (row + 3 < a.M && (reinterpret_cast<uintptr_t>(a.row_scale + row) & 15) == 0) {
                         const float4 v = *reinterpret_cast<const float4*>(a.row_scale + row);
-                        f[i][4 * q] = v.x; f[i][4 * q + 1] = v.y; f[i][4 * q + 2] = v.z; f[i][4 * q + 3] = v.w;
+                        fr[i][4 * q] = v.x; fr[i][4 * q + 1] = v.y; fr[i][4 * q + 2] = v.z; fr[i][4 * q + 3] = v.w;
                     } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) f[i][4 * q + e] = a.row_scale[min(row + e, a.M - 1)];
+                        for (int e = 0; e < 4; ++e) fr[i][4 * q + e] = a.row_scale[min(row + e, a.M - 1)];
                     }
                 }
             const float tsf = scaled ? ts : 1.0f;
@@ -871,9 +873,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; r += 2)
-                        put2(acc[i][j][r] * (f[i][r] * tsf) + bv[j], acc[i][j][r + 1] * (f[i][r + 1] * tsf) + bv[j],
-                             i * 32 + 8 * (r / 4) + 4 * kb + (r % 4), j * 32 + li);
+                    for (int q = 0; q < RB / 2; ++q) {
+                        const int r = first_of_pair(q);
+                        put2(acc[i][j][r] * (fr[i][r] * tsf) + bv[j], acc[i][j][r + PS] * (fr[i][r + PS] * tsf) + bv[j],
+                             i * S + acc_row(r), j * S + li);
+                    }
         }
         // same wave reads back what it wrote: LDS operations of a wave complete in order
         constexpr int CPR = WTN / 8;               // 16-byte chunks per tile row
@@ -900,14 +904,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
     } else {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            const int64_t col = n0 + wn * WTN + j * 32 + li;
+            const int64_t col = n0 + wn * WTN + j * S + li;
             if (col >= a.N) continue;
             const float bv = a.bias ? __uint_as_float((uint32_t)a.bias[col] << 16) : 0.f;
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t row = m0 + wm * WTM + i * 32 + 8 * (r / 4) + 4 * kb + (r % 4);
+                for (int r = 0; r < RB; ++r) {
+                    const int64_t row = m0 + wm * WTM + i * S + acc_row(r);
                     if (row >= a.M) continue;
                     a.Y[row * a.ldy + col] = finish(acc[i][j][r], row, bv);
                 }
@@ -924,7 +928,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
 // body tile's time. Every XCD works through its share of the body tiles first, then its share of
 // the tail tiles (workgroups are dispatched in id order). tail_tiles == 0: a plain one-shape launch.
 constexpr int kTailBN = 128;
-template <bool SPARSE, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false, bool D64 = false>
+template <bool SPARSE, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false>
 __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
     static_assert(WAVES_M * WAVES_N == 8, "both tile shapes run with eight waves");
     const int xcd = (int)blockIdx.x % 8, local = (int)blockIdx.x / 8;
@@ -933,7 +937,7 @@ __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
     if (local < nb_x) {
         GemmArgs b = a;
         if (nt > 0) b.M = a.m_split;
-        gemm_tile<SPARSE, 256, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, D64>(b, xcd_share_start(nb, xcd) + local);
+        gemm_tile<SPARSE, 256, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8>(b, xcd_share_start(nb, xcd) + local);
     } else {
         // the tail region as a problem of its own: same operands, shifted by m_split rows
         constexpr int ESZ = FP8 ? 1 : 2;
@@ -945,7 +949,7 @@ __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
         if (a.row_scale) t.row_scale = a.row_scale + a.m_split;
         if constexpr (MODE == 1) t.T = a.T + a.m_split * kLoraRank;
         const int idx = xcd_share_start(nb + nt, xcd) - xcd_share_start(nb, xcd) + (local - nb_x);
-        gemm_tile<SPARSE, 256, kTailBN, 2, 4, STAGES, MODE, FP8, D64>(t, idx);
+        gemm_tile<SPARSE, 256, kTailBN, 2, 4, STAGES, MODE, FP8>(t, idx);
     }
 }
 
@@ -953,18 +957,18 @@ __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
 // per kernel by the prepare functions (called for every configuration from prepare_gemm_kernels, i.e.
 // from rtl_init or from the first entry-point call on a device), never from a launch, so that launches
 // consist of the kernel node only and can be recorded into a HIP graph.
-template <bool SPARSE, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false, bool D64 = false>
+template <bool SPARSE, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false>
 struct Mixed {
-    using LB = Smem<SPARSE, 256, BN, STAGES, WAVES_M, WAVES_N, FP8, D64>;
-    using LT = Smem<SPARSE, 256, kTailBN, STAGES, 2, 4, FP8, D64>;
+    using LB = Smem<SPARSE, 256, BN, STAGES, WAVES_M, WAVES_N, FP8>;
+    using LT = Smem<SPARSE, 256, kTailBN, STAGES, 2, 4, FP8>;
     static constexpr int kLds = LB::kTotal > LT::kTotal ? LB::kTotal : LT::kTotal;
     static hipError_t prepare() {
-        auto kern = gemm_mixed_kernel<SPARSE, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, D64>;
+        auto kern = gemm_mixed_kernel<SPARSE, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8>;
         return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     }
     // a.m_split, a.body_tiles and a.tail_tiles come from the planner
     static hipError_t launch(const GemmArgs& a, hipStream_t stream) {
-        auto kern = gemm_mixed_kernel<SPARSE, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, D64>;
+        auto kern = gemm_mixed_kernel<SPARSE, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8>;
         hipLaunchKernelGGL(kern, dim3((unsigned)(a.body_tiles + a.tail_tiles)), dim3(512), kLds, stream, a);
         return hipGetLastError();
     }
@@ -997,12 +1001,12 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * WAVES_K * 64) void gemm_split_k
             }
         }
     }
-    gemm_tile<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, !SPARSE, WAVES_K, false, SPARSE>(b, xcd_share_start(total, xcd) + local);
+    gemm_tile<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, WAVES_K, false, SPARSE>(b, xcd_share_start(total, xcd) + local);
 }
 
 template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES, int MODE = 0, bool FP8 = false>
 struct Split {
-    using L = Smem<SPARSE, BM, BN, STAGES, WAVES_M, WAVES_N, FP8, !SPARSE, WAVES_K>;
+    using L = Smem<SPARSE, BM, BN, STAGES, WAVES_M, WAVES_N, FP8, WAVES_K>;
     static hipError_t prepare() {
         auto kern = gemm_split_kernel<SPARSE, BM, BN, WAVES_M, WAVES_N, WAVES_K, STAGES, MODE, FP8>;
         return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, L::kTotal);
@@ -1028,7 +1032,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void gemm_part_kernel(const
     const int idx = xcd_share_start(total, xcd) + local;       // an XCD's share: few parts, neighbouring tiles
     const int part = idx / tiles, blocks = (int)(a.K / (FP8 ? 128 : 64));
     const int b0 = (int)((int64_t)blocks * part / a.k_splits), b1 = (int)((int64_t)blocks * (part + 1) / a.k_splits);
-    gemm_tile<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, !SPARSE, 1, true>(a, idx % tiles, part, b0, b1 - b0);
+    gemm_tile<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, 1, true>(a, idx % tiles, part, b0, b1 - b0);
 }
 
 // Adds the planes up in order, then factors, bias, bf16. A thread finishes eight columns of a row, the planes'
@@ -1077,7 +1081,7 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const GemmArgs a, con
 
 template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false>
 struct Part {
-    using L = Smem<SPARSE, BM, BN, STAGES, WAVES_M, WAVES_N, FP8, !SPARSE>;
+    using L = Smem<SPARSE, BM, BN, STAGES, WAVES_M, WAVES_N, FP8>;
     static hipError_t prepare() {
         auto kern = gemm_part_kernel<SPARSE, BM, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8>;
         return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, L::kTotal);
@@ -1318,8 +1322,8 @@ hipError_t prepare_gemm_kernels() {
     run(Mixed<true, 192, 4, 2, 3>::prepare());
     run(Mixed<true, 256, 2, 4, 3, 1>::prepare());
     run(Mixed<true, 256, 2, 4, 3>::prepare());
-    run(Mixed<false, 192, 4, 2, 2, 0, false, true>::prepare());
-    run(Mixed<false, 256, 2, 4, 2, 0, false, true>::prepare());
+    run(Mixed<false, 192, 2, 4, 2>::prepare());
+    run(Mixed<false, 256, 2, 4, 2>::prepare());
     auto prep = [](auto k) { return decltype(k)::prepare(); };
     for (int i = 0; i < 5; ++i) {
         run(with_split<true, 0, false>(i, prep));
@@ -1396,8 +1400,8 @@ hipError_t launch_gemm(bool sparse, const GemmArgs& a_in, hipStream_t stream) {
         return Mixed<true, 256, 2, 4, 3>::launch(a, stream);
     }
     // dense: stages of 64 k (whole-line requests on the row-major operands), ring of two
-    if (plan.use_192) return Mixed<false, 192, 4, 2, 2, 0, false, true>::launch(a, stream);
-    return Mixed<false, 256, 2, 4, 2, 0, false, true>::launch(a, stream);
+    if (plan.use_192) return Mixed<false, 192, 2, 4, 2>::launch(a, stream);
+    return Mixed<false, 256, 2, 4, 2>::launch(a, stream);
 }
 
 }  // namespace rtl

@@ -3,6 +3,8 @@
 Integer/bit work (masks, metadata, packed values) must match exactly; outputs of the linears
 within Y_TOL on both error metrics.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -1116,6 +1118,41 @@ def test_small_tiles_sparse_dense_and_lora(M, N, K, comp):
     ref = oracle.sparse_lora_linear_oracle(Xs, Wb, synth.bits(LA), synth.bits(LB), bias=bb, scope=comp)["Y"]
     check_y(rtl.sparse_lora_linear(X, W, LA, LB, bias=b, comp=comp)[sel], ref)
     check_y(rtl.dense_linear(X, W, bias=b)[sel], oracle.dense_linear_oracle(Xs, Wb, bias=bb))
+
+
+# The 256-row plan with every number of stages from one to more than twice the ring,
+# last tiles that are ragged in both directions, 256 x 192 tiles, 256 x 256 tiles and 256 x 192 + 256 x 128 tiles.
+@pytest.mark.parametrize("M,N,body,tails", [(2305, 3201, 192, False), (2311, 6151, 256, False), (2311, 8008, 192, True)])
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 320, 384, 448, 640])
+def test_256_row_plan_every_stage_count(M, N, K, body, tails):
+    plan = (ctypes.c_int64 * 4)()
+    assert rtl.lib().rtl_diag_tile_plan(M, N, 0, plan) == 0 and plan[0] == body and (plan[3] > 0) == tails
+    assert all(gemm_choice(sp, f8, M, N, K)[:2] == (-1, 1) for sp, f8 in ((True, False), (False, False), (True, True)))
+    X = synth.activations("laplace_outlier", M, K, seed=K, device=DEV)
+    W = synth.weights(N, K, seed=K + 1, device=DEV, std=0.5)
+    b = synth.bias(N, seed=4, device=DEV, std=1.0)
+    LA, LB = synth.lora(N, K, 64, seed=5, device=DEV, std_a=0.3, std_b=0.3)
+    rows = np.unique(np.concatenate([sampled_rows(M, 6, seed=6), [0, 1535, 1536, 2047, 2048, M - 1]]))
+    sel = torch.from_numpy(rows).to(DEV)
+    Xs, Wb, bb = synth.bits(X[sel]), synth.bits(W), synth.bits(b)
+    for comp, bias in ((rtl.COMP_GROUP, None), (rtl.COMP_ROW, b)):
+        Y, guard_ok = guarded((M, N), torch.bfloat16, 7.0)
+        rtl.sparse_linear(X, W, bias=bias, comp=comp, out=Y)
+        check_y(Y[sel], oracle.sparse_linear_oracle(Xs, Wb, bias=None if bias is None else bb, scope=comp)["Y"])
+        guard_ok()
+        ref = oracle.sparse_lora_linear_oracle(Xs, Wb, synth.bits(LA), synth.bits(LB), bias=bb, scope=comp)["Y"]
+        check_y(rtl.sparse_lora_linear(X, W, LA, LB, bias=b, comp=comp)[sel], ref)
+    Y, guard_ok = guarded((M, N), torch.bfloat16, 7.0)
+    rtl.dense_linear(X, W, bias=b, out=Y)
+    check_y(Y[sel], oracle.dense_linear_oracle(Xs, Wb, bias=bb))
+    guard_ok()
+    if K % 128 == 0:
+        xs, Wq = fp8_scale(X), rtl.quantize_fp8(W)
+        Wn, f = Wq.cpu().numpy(), float(xs.item())
+        r = oracle.sparse_linear_fp8_oracle(Xs, Wn, f, bias=bb, scope=oracle.GROUP)
+        check_y_fp8(rtl.sparse_linear_fp8(X, Wq, xs, bias=b)[sel], r, Wn, f, bias=bb, max_rows=3)
+        r = oracle.sparse_lora_linear_fp8_oracle(Xs, Wn, f, synth.bits(LA), synth.bits(LB), bias=bb, scope=oracle.GROUP)
+        assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b)[sel]), r["Y"]) <= Y_TOL
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 1, 128), (33, 31, 384), (37, 1000, 4736), (97, 3072, 3200), (201, 3009, 1408),
