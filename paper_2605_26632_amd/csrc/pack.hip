@@ -15,6 +15,7 @@
 // path with NONE / GROUP scope), sparsify_pack_block_kernel runs instead: its mapping follows the
 // output layout (32 rows x 64-k blocks per wave) and every access is a whole line. (The FP8 sweep keeps
 // the row mapping: with its heavier per-group arithmetic the block mapping measured the same.)
+#include <type_traits>
 #include "rtl_internal.h"
 #include "select.h"
 #include "tensor_factor.h"
@@ -37,9 +38,10 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 // `vals`: bf16 [M,K/2], or one-byte E4M3 codes [M,K/2] when FP8 (then x_scale[0] is the divisor).
+// Workgroup `block` of the row mapping (kWavesPerBlock waves).
 template <int COMP, bool FP8>
-__global__ __launch_bounds__(kWavesPerBlock * 64) void sparsify_pack_kernel(
-    const uint16_t* __restrict__ X, int64_t M, int K, int64_t ldx, float eps,
+__device__ __forceinline__ void sweep_rows(
+    const unsigned block, const uint16_t* __restrict__ X, int64_t M, int K, int64_t ldx, float eps,
     void* __restrict__ vals, uint8_t* __restrict__ meta, uint8_t* __restrict__ vals_km,
     uint8_t* __restrict__ meta_km, int64_t Mpad, float* __restrict__ scale,
     float* __restrict__ rowsums, const float* __restrict__ x_scale, int parts, int span) {
@@ -48,7 +50,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void sparsify_pack_kernel(
     // every SIMD enough waves in flight. ROW / TENSOR add the waves' sums up in LDS, so there the waves of a
     // row sit in one workgroup (parts divides kWavesPerBlock).
     constexpr bool SUMS = COMP == RTL_COMP_ROW || COMP == RTL_COMP_TENSOR;
-    const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+    const int64_t gw = (int64_t)block * kWavesPerBlock + (threadIdx.x >> 6);
     const int64_t row = gw / parts;
     const int part = (int)(gw % parts);
     if (row >= M && (!SUMS || parts == 1)) return;   // whole wave leaves together (it has no barrier to meet)
@@ -148,6 +150,15 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void sparsify_pack_kernel(
     }
 }
 
+template <int COMP, bool FP8>
+__global__ __launch_bounds__(kWavesPerBlock * 64) void sparsify_pack_kernel(
+    const uint16_t* __restrict__ X, int64_t M, int K, int64_t ldx, float eps,
+    void* __restrict__ vals, uint8_t* __restrict__ meta, uint8_t* __restrict__ vals_km,
+    uint8_t* __restrict__ meta_km, int64_t Mpad, float* __restrict__ scale,
+    float* __restrict__ rowsums, const float* __restrict__ x_scale, int parts, int span) {
+    sweep_rows<COMP, FP8>(blockIdx.x, X, M, K, ldx, eps, vals, meta, vals_km, meta_km, Mpad, scale, rowsums, x_scale, parts, span);
+}
+
 // The same sweep for the case that matters most: only the k-major outputs are wanted (what
 // rtl_sparse_linear feeds its tile loop) and nothing is summed along a row (NONE / GROUP). Then the
 // mapping can follow the OUTPUT layout instead of the input rows: a wave takes 32 rows and a run of
@@ -159,15 +170,15 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void sparsify_pack_kernel(
 // time, which costs HBM efficiency once the activation is large.
 constexpr int kBlockWaves = 4;      // waves per workgroup: the same 32 rows, consecutive runs of blocks
 constexpr int kBlockUnroll = 2;     // 64-k blocks in flight per wave
-template <int COMP>
-__global__ __launch_bounds__(kBlockWaves * 64) void sparsify_pack_block_kernel(
-    const uint16_t* __restrict__ X, int64_t M, int KB, int64_t ldx, float eps, uint8_t* __restrict__ vals_km,
+template <int COMP, int WAVES>
+__device__ __forceinline__ void sweep_blocks(
+    const unsigned block, const uint16_t* __restrict__ X, int64_t M, int KB, int64_t ldx, float eps, uint8_t* __restrict__ vals_km,
     uint8_t* __restrict__ meta_km, int64_t Mpad, int per, unsigned row_blocks) {
     const int lane = threadIdx.x & 63, r8 = lane >> 3, c = lane & 7;
     const int wave = threadIdx.x >> 6;
     // workgroup id = run group * row_blocks + row block: neighbours take neighbouring rows of one K range
-    const int64_t m0 = (int64_t)(blockIdx.x % row_blocks) * 32;
-    const int b0 = ((int)(blockIdx.x / row_blocks) * kBlockWaves + wave) * per;   // first block of this wave's run
+    const int64_t m0 = (int64_t)(block % row_blocks) * 32;
+    const int b0 = ((int)(block / row_blocks) * WAVES + wave) * per;   // first block of this wave's run
     const int b1 = min(KB, b0 + per);
     const uint16_t* xr[4];
 #pragma unroll
@@ -204,6 +215,94 @@ __global__ __launch_bounds__(kBlockWaves * 64) void sparsify_pack_block_kernel(
             }
         }
     }
+}
+
+template <int COMP>
+__global__ __launch_bounds__(kBlockWaves * 64) void sparsify_pack_block_kernel(
+    const uint16_t* __restrict__ X, int64_t M, int KB, int64_t ldx, float eps, uint8_t* __restrict__ vals_km,
+    uint8_t* __restrict__ meta_km, int64_t Mpad, int per, unsigned row_blocks) {
+    sweep_blocks<COMP, kBlockWaves>(blockIdx.x, X, M, KB, ldx, eps, vals_km, meta_km, Mpad, per, row_blocks);
+}
+
+// Few rows with the LoRA residual: sweep and T = X L_B^T in one launch, by workgroups of their own. Workgroups
+// [0, t_blocks) form T, the others run the sweep as the plain call does.
+// A workgroup of T takes 16 rows x 16 ranks over the whole contraction: its eight waves deal the 64-k blocks out among
+// themselves (block w, w + 8, ...), a lane holds 32 bytes of a row per block, in two pieces of 16 (a load takes 64 contiguous bytes of each
+// of 16 rows), as the operands of two v_mfma_f32_16x16x32_bf16, straight from memory, and the waves' sums are added in LDS in
+// the order of the waves. So T needs no partial planes and no second launch. It is bound by the rate at which one compute
+// unit gets its 64 K bytes (about 40 GB/s, however many blocks are in flight), which is why the tile is the smallest one:
+// 32 x 16 and 32 x 32 take 1.5 and 2 times as long up to 512 rows (whole FP8 call [512, 3072, 3072]: 21.6, 24.3, 27.5 us), and why
+// long contractions stay with the split ones of pack_lora.hip.
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+union DownFrag {
+    uint4 u;
+    bf16x8 v;
+};
+constexpr int kDownTile = 16, kDownUnroll = 4;           // rows and ranks of a tile; 64-k blocks of a wave in flight
+constexpr int kDownParts = kLoraRank / kDownTile;        // workgroups of a row tile
+__device__ __forceinline__ void down_tile(const unsigned block, const uint16_t* __restrict__ X, int64_t M, int KB, int64_t ldx,
+                                          const uint16_t* __restrict__ LB, int64_t ldlb, uint16_t* __restrict__ T) {
+    __shared__ float part[kWavesPerBlock][kDownTile * kDownTile];
+    const int lane = threadIdx.x & 63, li = lane & 15, kb = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // the workgroups of a row tile on one XCD (ids go round robin): X from its L2 after the first
+    const int64_t m0 = ((int64_t)(block / (8 * kDownParts)) * 8 + block % 8) * kDownTile;
+    const int rank0 = (int)(block / 8) % kDownParts * kDownTile;
+    if (m0 >= M) return;                                                     // whole workgroup
+    const uint16_t* xa = X + min(m0 + li, M - 1) * ldx + kb * 8;             // rows past M: never stored
+    const uint16_t* lb = LB + (int64_t)(rank0 + li) * ldlb + kb * 8;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto blocks = [&](const int b, auto count) {         // blocks b, b + 8, ...: all loads in flight together
+        constexpr int U = decltype(count)::value;
+        DownFrag x[U][2], l[U][2];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int64_t k = (int64_t)(b + u * kWavesPerBlock) * 64 + h * 32;
+                x[u][h].u = *reinterpret_cast<const uint4*>(xa + k);
+                l[u][h].u = *reinterpret_cast<const uint4*>(lb + k);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[u][h].v, l[u][h].v, acc, 0, 0, 0);
+    };
+    int b = wave;
+    for (; b + (kDownUnroll - 1) * kWavesPerBlock < KB; b += kDownUnroll * kWavesPerBlock)
+        blocks(b, std::integral_constant<int, kDownUnroll>{});
+    for (; b < KB; b += kWavesPerBlock) blocks(b, std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[wave][(4 * kb + r) * kDownTile + li] = acc[r];      // row 4 kb + r, rank li
+    __syncthreads();
+    const int e = threadIdx.x;
+    const int64_t m = m0 + e / kDownTile;
+    if (e >= kDownTile * kDownTile || m >= M) return;
+    float v = part[0][e];
+#pragma unroll
+    for (int w = 1; w < kWavesPerBlock; ++w) v += part[w][e];
+    const uint32_t hi = f32_to_bf16_rne(v);              // two bf16 planes: hi = bf16(T), lo = bf16(T - hi)
+    uint16_t* t = T + m * kLoraRank + rank0 + e % kDownTile;
+    t[0] = (uint16_t)hi;
+    t[M * kLoraRank] = (uint16_t)f32_to_bf16_rne(v - __uint_as_float(hi << 16));
+}
+
+// bf16 NONE / GROUP take the block mapping of the sweep (then parts = row blocks, span = 64-k blocks per wave), the others the
+// row mapping.
+template <int COMP, bool FP8>
+__global__ __launch_bounds__(kWavesPerBlock * 64) void sparsify_down_kernel(
+    const uint16_t* __restrict__ X, int64_t M, int K, int64_t ldx, float eps, uint8_t* __restrict__ vals_km,
+    uint8_t* __restrict__ meta_km, int64_t Mpad, float* __restrict__ scale, float* __restrict__ rowsums,
+    const float* __restrict__ x_scale, int parts, int span, const uint16_t* __restrict__ LB, int64_t ldlb,
+    uint16_t* __restrict__ T, unsigned t_blocks) {
+    if (blockIdx.x < t_blocks) down_tile(blockIdx.x, X, M, K / 64, ldx, LB, ldlb, T);
+    else if constexpr (!FP8 && (COMP == RTL_COMP_NONE || COMP == RTL_COMP_GROUP))
+        sweep_blocks<COMP, kWavesPerBlock>(blockIdx.x - t_blocks, X, M, K / 64, ldx, eps, vals_km, meta_km, Mpad, span, (unsigned)parts);
+    else
+        sweep_rows<COMP, FP8>(blockIdx.x - t_blocks, X, M, K, ldx, eps, nullptr, nullptr, vals_km, meta_km, Mpad, scale, rowsums,
+                              x_scale, parts, span);
 }
 
 // TENSOR scope: fold the per-row sums and emit the single factor. `fused` (nullable) receives the factor times
@@ -370,6 +469,43 @@ hipError_t launch_sparsify_pack_fp8(const uint16_t* X, int64_t M, int64_t K, int
                                     hipStream_t stream) {
     return launch_pack_any<true>(X, M, K, ldx, comp, eps, vals8, meta, vals_km, meta_km, scale, rowsums,
                                  x_scale, stream);
+}
+
+hipError_t launch_sparsify_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps, const uint16_t* LB,
+                                int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, uint16_t* T, float* scale, float* rowsums,
+                                hipStream_t stream, const float* x_scale) {
+    const int64_t tiles = (M + kDownTile - 1) / kDownTile;
+    const unsigned t_blocks = (unsigned)((tiles + 7) / 8 * 8 * kDownParts);
+    int split[2];
+    int64_t blocks;
+    if (!x_scale && (comp == RTL_COMP_NONE || comp == RTL_COMP_GROUP)) {
+        const int KB = (int)(K / 64);
+        split[0] = (int)((M + 31) / 32);
+        split[1] = KB >= 96 ? kBlockUnroll : 1;
+        blocks = split[0] * (int64_t)(((KB + split[1] - 1) / split[1] + kWavesPerBlock - 1) / kWavesPerBlock);
+    } else {
+        row_split((int)comp, M, K, split);
+        blocks = (M * split[0] + kWavesPerBlock - 1) / kWavesPerBlock;
+    }
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(t_blocks + (unsigned)blocks), dim3(kWavesPerBlock * 64), 0, stream, X, M, (int)K, ldx, eps,
+                           vals_km, meta_km, kmajor_rows(M), scale, rowsums, x_scale, split[0], split[1], LB, ldlb, T, t_blocks);
+    };
+    switch (comp) {
+        case RTL_COMP_NONE:
+            x_scale ? go(sparsify_down_kernel<RTL_COMP_NONE, true>) : go(sparsify_down_kernel<RTL_COMP_NONE, false>);
+            break;
+        case RTL_COMP_GROUP:
+            x_scale ? go(sparsify_down_kernel<RTL_COMP_GROUP, true>) : go(sparsify_down_kernel<RTL_COMP_GROUP, false>);
+            break;
+        case RTL_COMP_ROW:
+            x_scale ? go(sparsify_down_kernel<RTL_COMP_ROW, true>) : go(sparsify_down_kernel<RTL_COMP_ROW, false>);
+            break;
+        case RTL_COMP_TENSOR:
+            x_scale ? go(sparsify_down_kernel<RTL_COMP_TENSOR, true>) : go(sparsify_down_kernel<RTL_COMP_TENSOR, false>);
+            break;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_tensor_scale(const float* rowsums, int64_t M, float eps, float* scale, hipStream_t stream,

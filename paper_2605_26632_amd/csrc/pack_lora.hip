@@ -15,6 +15,7 @@
 //   * two groups of four for the Top-2 selection, whose kept values and positions leave in the k-major
 //     layout the tile loop streams: 32 bytes of values and 4 bytes of metadata per lane and stage,
 //     contiguous over the wave (rows of a 64-k block are 64 and 8 bytes apart).
+// Few rows with a short contraction take sparsify_down_kernel (pack.hip) instead, see launch_pack_down.
 // ROW and TENSOR scopes sum squares along the whole row; every workgroup leaves the sums of its K range
 // beside its partial plane and lora_reduce_kernel adds them up in range order as well.
 #include "rtl_internal.h"
@@ -320,6 +321,13 @@ size_t pack_down_scratch_min(int64_t M, int64_t K) { return pack_down_bytes(M, p
 hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps,
                             const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, float* scratch,
                             size_t scratch_bytes, uint16_t* T, float* scale, float* rowsums, hipStream_t stream, const float* x_scale) {
+    // Few rows and a short contraction: the sweep with T beside it in the same launch (sparsify_down_kernel) ends before this one
+    // and its reduction. Whole call [M, 3072, K], fused sweep -> that, us, bf16 | FP8: [37, 512] 11.7 -> 8.8 | 11.5 -> 7.9, [512, 1024]
+    // 19.8 -> 15.9 | 19.3 -> 14.5, [512, 3072] 27.0 -> 25.8 | 25.6 -> 21.6, [1029, 3072] 39.8 -> 39.0 | 27.5 -> 26.5, [2048, 1024] 26.1 -> 23.9
+    // | 26.9 -> 21.8, [2048, 1536] 29.9 -> 28.1 | 28.3 -> 25.8. Beyond the line it loses: [1536, 3072] 48.5 -> 50.0, [2048, 2048] 33.7 ->
+    // 34.0, [512, 4608] 40.8 -> 41.6, [4608, 1536] 46.3 -> 49.6.
+    if ((M <= 1280 && K <= 3072) || (M <= 2048 && K <= 1536))
+        return launch_sparsify_down(X, M, K, ldx, comp, eps, LB, ldlb, vals_km, meta_km, T, scale, rowsums, stream, x_scale);
     int per = 1;
     const size_t fit = scratch_bytes / pack_down_bytes(M, 1);
     const int splits = pack_down_ranges(M, K, &per, fit > kMaxRanges ? kMaxRanges : (int)fit);

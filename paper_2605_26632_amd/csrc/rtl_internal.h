@@ -118,6 +118,10 @@ hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx
                             const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, float* scratch,
                             size_t scratch_bytes, uint16_t* T, float* scale, float* rowsums, hipStream_t stream,
                             const float* x_scale = nullptr);
+// The form of it for few rows (pack.hip): sweep and T in one launch, no scratch.
+hipError_t launch_sparsify_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps,
+                                const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, uint16_t* T,
+                                float* scale, float* rowsums, hipStream_t stream, const float* x_scale);
 // (x_scale set: FP8 form: kept values as E4M3 codes of (s x) / x_scale[0] in the FP8 k-major layout, K % 128 == 0.)
 // TENSOR scope: the single factor from the per-row sums [M][2] (fixed order, fp64), into scale[0]; `fused`
 // (nullable) receives scale[0] * mul[0].

@@ -581,6 +581,33 @@ def test_sparse_lora_linear_zero_factor_equals_sparse_linear():
     assert torch.equal(Y0, rtl.sparse_linear(X, W, comp=rtl.COMP_GROUP))
 
 
+@pytest.mark.parametrize("comp", COMPS)
+@pytest.mark.parametrize("M,K", [(1, 128), (15, 640), (17, 2048), (129, 3072), (1280, 384), (1281, 1536), (2048, 512),
+                                 (129, 3200), (1281, 1664)])
+def test_lora_down_projection_of_few_rows(M, K, comp):
+    """T = X L_B^T formed beside the sweep (rows not whole 16-row tiles, fewer 64-k blocks than waves, rests of the unrolled
+    trips, both corners of the rule; the last two shapes lie outside it). With W = 0 the call is the residual alone:
+    Y = (X L_B^T) L_A^T, and with L_A = 0 it is the plain call, bit for bit where its sweep is (FP8 alike)."""
+    N = 136
+    X = synth.activations("laplace_outlier", M, K, seed=61, device=DEV)
+    W = synth.weights(N, K, seed=62, device=DEV)
+    LA, LB = synth.lora(N, K, 64, seed=63, device=DEV, std_a=0.3, std_b=0.3)
+    xs = (X.float().abs().max() * (2.0 ** 0.5) / 448.0).reshape(1).to(torch.float32)
+    Wq = rtl.quantize_fp8(W)
+    t = X.double() @ LB.double().t()
+    ref = t @ LA.double().t()
+    # fp32 sums of K products (relative to the sum of magnitudes), the hi / lo pair (2^-17), 64 more products, one bf16 rounding
+    mag = (X.double().abs() @ LB.double().abs().t()) @ LA.double().abs().t()
+    bound = 2.0 ** -8 * ref.abs() + (K * 2.0 ** -24 + 2.0 ** -16 + 64 * 2.0 ** -24) * mag
+    for Y in (rtl.sparse_lora_linear(X, torch.zeros_like(W), LA, LB, comp=comp),
+              rtl.sparse_lora_linear_fp8(X, torch.zeros_like(Wq), xs, LA, LB, comp=comp)):
+        assert bool(((Y.double() - ref).abs() <= bound).all())
+    if (M, K) not in ((129, 3200), (1281, 1664)) or comp in (rtl.COMP_NONE, rtl.COMP_GROUP):
+        assert torch.equal(rtl.sparse_lora_linear(X, W, torch.zeros_like(LA), LB, comp=comp), rtl.sparse_linear(X, W, comp=comp))
+        assert torch.equal(rtl.sparse_lora_linear_fp8(X, Wq, xs, torch.zeros_like(LA), LB, comp=comp),
+                           rtl.sparse_linear_fp8(X, Wq, xs, comp=comp))
+
+
 @pytest.mark.parametrize("comp", [rtl.COMP_NONE, rtl.COMP_GROUP])
 @pytest.mark.parametrize("shape", ["tiny", "mlp_down", "hr_out_proj", "hr_mlp_down", (300, 200, 192), (129, 64, 64),
                                    (1000, 128, 1088)])
