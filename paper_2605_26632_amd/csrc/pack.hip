@@ -337,25 +337,36 @@ __global__ __launch_bounds__(256) void quantize_fp8_kernel(const uint16_t* __res
     *reinterpret_cast<uint2*>(Wq + r * ldq + c) = make_uint2(o[0], o[1]);
 }
 
-// One thread per (row, 64-k block) and 16-byte piece: rows run fastest so that the k-major writes of
-// a warp are contiguous. Piece 0..3 = the block's 64 bytes of values; piece 0 also moves the
-// 8-byte metadata record.
-__global__ __launch_bounds__(256) void operand_to_kmajor_kernel(const uint16_t* __restrict__ vals,
-                                                                const uint8_t* __restrict__ meta,
-                                                                int64_t M, int64_t KB, int64_t Mpad,
-                                                                uint8_t* __restrict__ vals_km,
-                                                                uint8_t* __restrict__ meta_km) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= M * KB * 4) return;
-    const int piece = (int)(t & 3);
-    const int64_t row = (t >> 2) % M, kb = (t >> 2) / M;
-    const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(vals) +
-                                                    (row * KB + kb) * 64 + piece * 16);
-    *reinterpret_cast<uint4*>(vals_km + (kb * Mpad + row) * 64 + piece * 16) = v;
-    if (piece == 0) {
-        const uint2 m = *reinterpret_cast<const uint2*>(meta + row * KB * 8 + kb * 8);
-        *reinterpret_cast<uint2*>(meta_km + (kb * Mpad + row) * 8) = m;
-    }
+// Copy of the canonical operand into the k-major layout. A workgroup takes 64 rows and U neighbouring 64-k blocks: thread
+// (row r, piece p) moves piece p (16 bytes) of the row's U value blocks, all loads in flight together, and the metadata
+// records of the blocks p, p + 4, .... Reads are runs of 64 U bytes of a row, writes 4 KB contiguous per block.
+template <int U>
+__global__ __launch_bounds__(256) void operand_to_kmajor_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta,
+                                                                int64_t M, int KB, int64_t Mpad, uint8_t* __restrict__ vals_km,
+                                                                uint8_t* __restrict__ meta_km, unsigned row_blocks) {
+    const int piece = (int)threadIdx.x & 3;
+    const int64_t row = (int64_t)(blockIdx.x % row_blocks) * 64 + (threadIdx.x >> 2);
+    const int b0 = (int)(blockIdx.x / row_blocks) * U;
+    if (row >= M) return;
+    const uint8_t* src = reinterpret_cast<const uint8_t*>(vals) + (row * KB + b0) * 64 + piece * 16;
+    const uint8_t* msrc = meta + (row * KB + b0) * 8;
+    const int last = KB - 1 - b0;                        // (blocks past K: the last one again, not stored)
+    uint4 v[U];
+    uint2 m[(U + 3) / 4];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        v[u] = *reinterpret_cast<const uint4*>(src + min(u, last) * 64);
+#pragma unroll
+    for (int u = 0; u < (U + 3) / 4; ++u)
+        m[u] = *reinterpret_cast<const uint2*>(msrc + min(4 * u + piece, last) * 8);
+    uint8_t* dst = vals_km + (b0 * Mpad + row) * 64 + piece * 16;
+    uint8_t* mdst = meta_km + (b0 * Mpad + row) * 8;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (b0 + u < KB) *reinterpret_cast<uint4*>(dst + u * Mpad * 64) = v[u];
+#pragma unroll
+    for (int u = 0; u < (U + 3) / 4; ++u)
+        if (4 * u + piece < U && b0 + 4 * u + piece < KB) *reinterpret_cast<uint2*>(mdst + (4 * u + piece) * Mpad * 8) = m[u];
 }
 
 }  // namespace
@@ -363,14 +374,23 @@ __global__ __launch_bounds__(256) void operand_to_kmajor_kernel(const uint16_t* 
 // Querying one kernel makes the runtime load this translation unit's code object.
 hipError_t prepare_pack_kernels() {
     hipFuncAttributes attr;
-    return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(operand_to_kmajor_kernel));
+    return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(tensor_scale_kernel));
 }
 
 hipError_t launch_operand_to_kmajor(const uint16_t* vals, const uint8_t* meta, int64_t M, int64_t K,
                                     uint8_t* vals_km, uint8_t* meta_km, hipStream_t stream) {
-    const int64_t KB = K / 64, n = M * KB * 4;
-    hipLaunchKernelGGL(operand_to_kmajor_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                       vals, meta, M, KB, kmajor_rows(M), vals_km, meta_km);
+    const int KB = (int)(K / 64);
+    const unsigned row_blocks = (unsigned)((M + 63) / 64);
+    auto go = [&](auto kernel, int u) {
+        hipLaunchKernelGGL(kernel, dim3(row_blocks * (unsigned)((KB + u - 1) / u)), dim3(256), 0, stream, vals, meta, M, KB,
+                           kmajor_rows(M), vals_km, meta_km, row_blocks);
+    };
+    // Four or two blocks per thread where that leaves four workgroups a compute unit, else one: whole rtl_packed_linear call with
+    // 1 / 2 / 4 / 8 blocks, us: [4608, 1024, 3072] 38.6 / 36.0 / 34.2 / 33.1, [4096, 1024, 12288] 90.8 / 86.2 / 86.3 / 86.5, [16896, 512,
+    // 3072] 57.1 / 55.0 / 55.6 / 55.9; [512, 1024, 3072] 11.8 / 11.9 / 12.3 / 12.9, [1029, 512, 1024] 9.5 / 9.5 / 9.8 / 10.4.
+    if ((int64_t)row_blocks * KB >= 4 * 1024) go(operand_to_kmajor_kernel<4>, 4);
+    else if ((int64_t)row_blocks * KB >= 2 * 1024) go(operand_to_kmajor_kernel<2>, 2);
+    else go(operand_to_kmajor_kernel<1>, 1);
     return hipGetLastError();
 }
 
