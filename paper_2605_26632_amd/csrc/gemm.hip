@@ -1191,8 +1191,15 @@ struct SplitShape {
     int bm, bn;
     double fixed, block;
 };
+// Sparse 256 x 96 (eight waves of 32 rows, ring of four) stands between the 128 x 128 tile and the 256-row plan: with the plan's
+// 256 x 128 tiles an output of 130 to 192 tiles leaves compute units idle and each of the others pulls 34 KB a stage, here up to 256
+// pull 30. Its constants put the line where measurement has it; 58 of 170 drawn shapes of all sparse kinds that it can run
+// in one pass ([129..4608, 512..21504, 512..15360], inputs from HBM) took it with {4.4, 0.385}, 5.5 % faster in the mean: sparse [512, 9216,
+// 3072] 39.6 -> 36.6 us, [3738, 1184, 8448] 100.1 -> 90.0, FP8 [512, 12288, 3072] 28.2 -> 26.4, LoRA [512, 12288, 3072] 46.9 ->
+// 45.0; the five that lost (K <= 1920, 3 to 6 %) are what the larger fixed part leaves to the plan.
 constexpr SplitShape kSparseShapes[] = {
-    {32, 32, 1.2, 0.087}, {64, 32, 1.9, 0.108}, {64, 64, 2.4, 0.153}, {128, 64, 2.3, 0.19}, {128, 128, 2.8, 0.30}};
+    {32, 32, 1.2, 0.087}, {64, 32, 1.9, 0.108}, {64, 64, 2.4, 0.153}, {128, 64, 2.3, 0.19}, {128, 128, 2.8, 0.30},
+    {256, 96, 5.2, 0.37}};
 constexpr SplitShape kDenseShapes[] = {
     {32, 32, 1.2, 0.10}, {64, 32, 1.8, 0.135}, {64, 64, 1.0, 0.18}, {128, 64, 2.5, 0.262}, {128, 128, 3.8, 0.36},
     {256, 128, 4.0, 0.48}};
@@ -1228,9 +1235,9 @@ static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_
         const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn);
         if (tiles > 4096) continue;                        // far more than a few passes: never the better one
         double block = s.block;
-        if (s.bm == 256) {                                 // 256 x 128 with a ring of three: one pass only, slower as the chip fills
-            if (tiles > 256) continue;
-            if (tiles > 96) block += 0.0026 * (double)(tiles - 96);
+        if (s.bm == 256) {                                 // one pass only, slower as the chip fills (its rivals are, in the sparse case)
+            if (tiles > 256 || (!dense && M > 4608)) continue;     // (sparse: not measured beyond)
+            if (dense && tiles > 96) block += 0.0026 * (double)(tiles - 96);
         }
         const int64_t passes = (tiles + 255) / 256;
         if (passes > 1 && s.bm >= 128 && s.bn >= 128 && M > 2048) continue;
@@ -1290,7 +1297,8 @@ static hipError_t with_split(int i, Op op) {
             case 1: return op(Split<true, 64, 32, 1, 1, 4, 4, MODE, FP8>{});
             case 2: return op(Split<true, 64, 64, 1, 2, 2, 3, MODE, FP8>{});
             case 3: return op(Split<true, 128, 64, 2, 2, 2, 3, MODE, FP8>{});
-            default: return op(Split<true, 128, 128, 2, 2, 1, 3, MODE, FP8>{});
+            case 4: return op(Split<true, 128, 128, 2, 2, 1, 3, MODE, FP8>{});
+            default: return op(Split<true, 256, 96, 8, 1, 1, 4, MODE, FP8>{});
         }
     } else {
         switch (i) {
@@ -1325,7 +1333,7 @@ hipError_t prepare_gemm_kernels() {
     run(Mixed<false, 192, 2, 4, 2>::prepare());
     run(Mixed<false, 256, 2, 4, 2>::prepare());
     auto prep = [](auto k) { return decltype(k)::prepare(); };
-    for (int i = 0; i < 5; ++i) {
+    for (int i = 0; i < 6; ++i) {
         run(with_split<true, 0, false>(i, prep));
         run(with_split<true, 1, false>(i, prep));
         run(with_split<true, 0, true>(i, prep));

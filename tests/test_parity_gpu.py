@@ -581,6 +581,33 @@ def test_sparse_lora_linear_zero_factor_equals_sparse_linear():
     assert torch.equal(Y0, rtl.sparse_linear(X, W, comp=rtl.COMP_GROUP))
 
 
+@pytest.mark.parametrize("M,N,K", [(257, 12283, 3136), (129, 21504, 7168), (2050, 2651, 4480)])
+def test_sparse_tiles_of_256_by_96(M, N, K):
+    """The 256 x 96 tile: one row in the last panel, partial last column tiles (also an odd width, 2-byte stores), an odd number of
+    k blocks, and every kind of operand; TENSOR forms its factor in the kernel up to 2048 rows and before it beyond."""
+    X = synth.activations("laplace_outlier", M, K, seed=71, device=DEV)
+    W = synth.weights(N, K, seed=72, device=DEV)
+    b = synth.bias(N, seed=73, device=DEV)
+    LA, LB = synth.lora(N, K, 64, seed=74, device=DEV, std_a=0.1, std_b=0.1)
+    assert gemm_choice(True, False, M, N, K)[:2] == (5, 1)
+    rows = np.array([0, M // 2, M - 2, M - 1])
+    sel = torch.from_numpy(rows).to(DEV)
+    Xb, Wb = synth.bits(X[sel]), synth.bits(W)
+    for comp in (rtl.COMP_GROUP, rtl.COMP_ROW):
+        ref = oracle.sparse_lora_linear_oracle(Xb, Wb, synth.bits(LA), synth.bits(LB), bias=synth.bits(b), scope=comp)
+        check_y(rtl.sparse_linear(X, W, bias=b, comp=comp)[sel], ref["Y_s"])
+        check_y(rtl.sparse_lora_linear(X, W, LA, LB, bias=b, comp=comp)[sel], ref["Y"])
+    vals, meta, scale = rtl.sparsify_pack(X, comp=rtl.COMP_TENSOR)
+    Y = rtl.sparse_linear(X, W, bias=b, comp=rtl.COMP_TENSOR)
+    assert torch.equal(Y, rtl.packed_linear(vals, meta, W, bias=b, tensor_scale=scale))
+    if K % 128 == 0 and gemm_choice(True, True, M, N, K)[0] == 5:
+        xs, Wq = fp8_scale(X), rtl.quantize_fp8(W)
+        r = oracle.sparse_lora_linear_fp8_oracle(Xb, Wq.cpu().numpy(), float(xs.item()), synth.bits(LA), synth.bits(LB),
+                                                 bias=synth.bits(b), scope=oracle.GROUP)
+        Y = rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b, comp=rtl.COMP_GROUP)
+        assert rel_max_err(Y[sel].float().cpu().numpy(), r["Y"]) <= Y_TOL
+
+
 @pytest.mark.parametrize("comp", COMPS)
 @pytest.mark.parametrize("M,K", [(1, 128), (15, 640), (17, 2048), (129, 3072), (1280, 384), (1281, 1536), (2048, 512),
                                  (129, 3200), (1281, 1664)])
