@@ -1197,12 +1197,14 @@ struct SplitShape {
 // in one pass ([129..4608, 512..21504, 512..15360], inputs from HBM) took it with {4.4, 0.385}, 5.5 % faster in the mean: sparse [512, 9216,
 // 3072] 39.6 -> 36.6 us, [3738, 1184, 8448] 100.1 -> 90.0, FP8 [512, 12288, 3072] 28.2 -> 26.4, LoRA [512, 12288, 3072] 46.9 ->
 // 45.0; the five that lost (K <= 1920, 3 to 6 %) are what the larger fixed part leaves to the plan.
+// Dense 256 x 96 (ring of three) for the same reason where 256 x 128 tiles do not reach all units: 39 of 120 drawn shapes took it, 7 % faster
+// in the mean and none slower: [2028, 2560, 1792] 26.1 -> 21.7 us, [734, 7520, 13440] 174.6 -> 159.4, [370, 11648, 9216] 128 -> 118.
 constexpr SplitShape kSparseShapes[] = {
     {32, 32, 1.2, 0.087}, {64, 32, 1.9, 0.108}, {64, 64, 2.4, 0.153}, {128, 64, 2.3, 0.19}, {128, 128, 2.8, 0.30},
     {256, 96, 5.2, 0.37}};
 constexpr SplitShape kDenseShapes[] = {
     {32, 32, 1.2, 0.10}, {64, 32, 1.8, 0.135}, {64, 64, 1.0, 0.18}, {128, 64, 2.5, 0.262}, {128, 128, 3.8, 0.36},
-    {256, 128, 4.0, 0.48}};
+    {256, 128, 4.0, 0.48}, {256, 96, 3.9, 0.445}};
 
 // How the problem should run. Times are estimated from the measured constants: a small shape needs ceil(tiles / 256)
 // passes over the 256 compute units; with more than one, all units pull operands all the time and slow each other down
@@ -1237,7 +1239,8 @@ static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_
         double block = s.block;
         if (s.bm == 256) {                                 // one pass only, slower as the chip fills (its rivals are, in the sparse case)
             if (tiles > 256 || (!dense && M > 4608)) continue;     // (sparse: not measured beyond)
-            if (dense && tiles > 96) block += 0.0026 * (double)(tiles - 96);
+            if (dense && s.bn == 128 && tiles > 96) block += 0.0026 * (double)(tiles - 96);
+            if (dense && s.bn == 96 && tiles > 128) block += 0.0019 * (double)(tiles - 128);
         }
         const int64_t passes = (tiles + 255) / 256;
         if (passes > 1 && s.bm >= 128 && s.bn >= 128 && M > 2048) continue;
@@ -1307,7 +1310,8 @@ static hipError_t with_split(int i, Op op) {
             case 2: return op(Split<false, 64, 64, 1, 2, 2, 4>{});
             case 3: return op(Split<false, 128, 64, 2, 2, 2, 3>{});
             case 4: return op(Split<false, 128, 128, 2, 2, 1, 3>{});
-            default: return op(Split<false, 256, 128, 2, 4, 1, 3>{});
+            case 5: return op(Split<false, 256, 128, 2, 4, 1, 3>{});
+            default: return op(Split<false, 256, 96, 4, 2, 1, 3>{});
         }
     }
 }
@@ -1339,7 +1343,7 @@ hipError_t prepare_gemm_kernels() {
         run(with_split<true, 0, true>(i, prep));
         run(with_split<true, 1, true>(i, prep));
     }
-    for (int i = 0; i < 6; ++i) run(with_split<false, 0, false>(i, prep));
+    for (int i = 0; i < 7; ++i) run(with_split<false, 0, false>(i, prep));
     for (int i = 0; i < 2; ++i) {
         run(with_part<false, 0, false>(i != 0, prep));
         run(with_part<true, 0, false>(i != 0, prep));
