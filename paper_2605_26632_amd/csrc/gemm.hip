@@ -1,6 +1,6 @@
 // Linear layers on the gfx950 matrix cores.
 //
-//   dense : Y = X W^T                       (paper Eq. linear_layer; v_mfma_f32_32x32x16_bf16)
+//   dense : Y = X W^T                       (paper Eq. linear_layer; v_mfma_f32_16x16x32_bf16)
 //   sparse: Y = S(X) W^T, S(X) compressed   (Alg. 1 "Y_s <- S(X) W^T", operand format of App. A;
 //                                            v_smfmac_f32_32x32x32_bf16)
 //
