@@ -385,11 +385,10 @@ hipError_t launch_operand_to_kmajor(const uint16_t* vals, const uint8_t* meta, i
         hipLaunchKernelGGL(kernel, dim3(row_blocks * (unsigned)((KB + u - 1) / u)), dim3(256), 0, stream, vals, meta, M, KB,
                            kmajor_rows(M), vals_km, meta_km, row_blocks);
     };
-    // Four or two blocks per thread where that leaves four workgroups a compute unit, else one: whole rtl_packed_linear call with
+    // Four blocks per thread where that leaves two workgroups a compute unit, else one: whole rtl_packed_linear call with
     // 1 / 2 / 4 / 8 blocks, us: [4608, 1024, 3072] 38.6 / 36.0 / 34.2 / 33.1, [4096, 1024, 12288] 90.8 / 86.2 / 86.3 / 86.5, [16896, 512,
     // 3072] 57.1 / 55.0 / 55.6 / 55.9; [512, 1024, 3072] 11.8 / 11.9 / 12.3 / 12.9, [1029, 512, 1024] 9.5 / 9.5 / 9.8 / 10.4.
-    if ((int64_t)row_blocks * KB >= 4 * 1024) go(operand_to_kmajor_kernel<4>, 4);
-    else if ((int64_t)row_blocks * KB >= 2 * 1024) go(operand_to_kmajor_kernel<2>, 2);
+    if ((int64_t)row_blocks * KB >= 2048) go(operand_to_kmajor_kernel<4>, 4);
     else go(operand_to_kmajor_kernel<1>, 1);
     return hipGetLastError();
 }
