@@ -356,7 +356,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
             for (int r = 0; r < RB; ++r) acc[i][j][r] = 0.f;
 
     const int li = lane % S, kb = lane / S;
-    auto acc_row = [&](int r) { return S == 32 ? 8 * (r / 4) + 4 * kb + (r % 4) : 4 * kb + r; };   // row of register r inside its block
+    // Register r of a block is row 4 kb + reg_row(r) of it. The lane's part goes into one base wherever rows are addressed, so that
+    // the rest is constant: as one sum per register, 11 of the 96 paired LDS writes of the sparse 256 x 256 epilogue fell apart.
+    auto reg_row = [](int r) { return S == 32 ? 8 * (r / 4) + r % 4 : r; };
+    const int64_t lane_row = m0 + wm * WTM + 4 * kb;
     const int arow0 = wm * WTM + li;   // + i * S
     const int brow0 = wn * WTN + li;   // + j * S
 
@@ -582,14 +585,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
         __syncthreads();                         // the ring is free
         float* const planes = reinterpret_cast<float*>(smem);
         auto put_plane = [&](const Acc (&v)[TM][TN]) {       // this wave's block of its group's plane
-            float* p = planes + wk * (L::kPlane / 4);
+            float* p = planes + wk * (L::kPlane / 4) + (wm * WTM + 4 * kb) * L::kPitch + wn * WTN + li;
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
                     for (int r = 0; r < RB; ++r)
-                        p[(wm * WTM + i * S + acc_row(r)) * L::kPitch + wn * WTN + j * S + li] = v[i][j][r];
+                        p[(i * S + reg_row(r)) * L::kPitch + j * S] = v[i][j][r];
         };
         constexpr int THREADS = NW * WAVES_K * 64;
         constexpr int CPR = BN / 8, CHUNKS = BM * CPR;       // a thread finishes runs of 8 columns
@@ -714,7 +717,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int r = 0; r < RB; ++r) {
-                    const int64_t row = min(m0 + wm * WTM + i * S + acc_row(r), a.M - 1);
+                    const int64_t row = min(lane_row + (i * S + reg_row(r)), a.M - 1);
                     const float f = (a.row_scale ? a.row_scale[row] : 1.0f) * ts;
 #pragma unroll
                     for (int j = 0; j < TN; ++j) acc[i][j][r] *= f;
@@ -780,7 +783,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int r = 0; r < RB; ++r) {
-                    const int64_t row = m0 + wm * WTM + i * S + acc_row(r);
+                    const int64_t row = lane_row + (i * S + reg_row(r));
                     if (row < a.M && col < a.N) plane[row * a.part_pitch + col] = acc[i][j][r];
                 }
         }
@@ -819,15 +822,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
         constexpr int PS = S == 32 ? 1 : 2;
         const bool odd = lane & 1;
         const uint32_t sel = odd ? 0x03020706u : 0x05040100u;   // v_perm_b32: bytes 0-3 = own, 4-7 = partner
-        const int rsel = odd ? PS * ROWB : 0;                   // odd lanes write the row PS below
-        auto put2 = [&](float v0, float v1, int rl, int cl) {
+        uint8_t* const ep_lane = ep + (4 * kb + (odd ? PS : 0)) * ROWB + (li & ~1) * 2;   // odd lanes write the row PS below
+        auto put2 = [&](float v0, float v1, int rl, int cl) {   // rl, cl: beyond the lane's own row and column, constants
             const f32x2 pv = {v0, v1};
             const uint32_t own = __builtin_bit_cast(uint32_t, __builtin_convertvector(pv, bf16x2));
             const uint32_t partner = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);
-            // even: (own.lo, partner.lo) = row rl, columns (cl, cl + 1)
-            // odd : (partner.hi, own.hi) = row rl + PS, columns (cl - 1, cl)
+            // even: (own.lo, partner.lo) = its row, its column and the next
+            // odd : (partner.hi, own.hi) = its row + PS, the column before and its own
             const uint32_t w = __builtin_amdgcn_perm(partner, own, sel);
-            *reinterpret_cast<uint32_t*>(ep + rl * ROWB + rsel + (cl & ~1) * 2) = w;
+            *reinterpret_cast<uint32_t*>(ep_lane + rl * ROWB + cl * 2) = w;
         };
         auto first_of_pair = [](int q) { return S == 32 ? 2 * q : q; };     // registers r, r + PS, q = 0 .. RB / 2 - 1
         const bool scaled = MODE != 1 && (a.row_scale || has_tensor_scale);
@@ -839,7 +842,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
 #pragma unroll
                     for (int q = 0; q < RB / 2; ++q) {
                         const int r = first_of_pair(q);
-                        put2(acc[i][j][r], acc[i][j][r + PS], i * S + acc_row(r), j * S + li);
+                        put2(acc[i][j][r], acc[i][j][r + PS], i * S + reg_row(r), j * S);
                     }
         } else {
             // the factors of the lane's rows per row block are fetched once, not once per column block,
@@ -855,7 +858,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int q = 0; q < RB / 4; ++q) {  // registers 4 q .. 4 q + 3 are four consecutive rows
-                    const int64_t row = m0 + wm * WTM + i * S + acc_row(4 * q);
+                    const int64_t row = lane_row + (i * S + reg_row(4 * q));
                     if (!scaled || !a.row_scale) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) fr[i][4 * q + e] = 1.0f;
@@ -876,7 +879,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
                     for (int q = 0; q < RB / 2; ++q) {
                         const int r = first_of_pair(q);
                         put2(acc[i][j][r] * (fr[i][r] * tsf) + bv[j], acc[i][j][r + PS] * (fr[i][r + PS] * tsf) + bv[j],
-                             i * S + acc_row(r), j * S + li);
+                             i * S + reg_row(r), j * S);
                     }
         }
         // same wave reads back what it wrote: LDS operations of a wave complete in order
@@ -911,7 +914,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
             for (int i = 0; i < TM; ++i) {
 #pragma unroll
                 for (int r = 0; r < RB; ++r) {
-                    const int64_t row = m0 + wm * WTM + i * S + acc_row(r);
+                    const int64_t row = lane_row + (i * S + reg_row(r));
                     if (row >= a.M) continue;
                     a.Y[row * a.ldy + col] = finish(acc[i][j][r], row, bv);
                 }
