@@ -576,8 +576,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
     }
 
     const bool own_factor = FOLDED && a.rowsums;
-    const bool has_tensor_scale = own_factor || a.tensor_scale;
-    auto tensor_scale = [&]() { return own_factor ? a.folded : (a.tensor_scale ? a.tensor_scale[0] : 1.0f); };
+    // Only the sparse product has factors. (Known at compile time it keeps their 32 registers out of the 256 x 256 dense epilogue,
+    // which spilled seven of its own without it.)
+    const bool has_row_scale = SPARSE && a.row_scale, has_tensor_scale = SPARSE && (own_factor || a.tensor_scale);
+    auto tensor_scale = [&]() { return own_factor ? a.folded : (has_tensor_scale ? a.tensor_scale[0] : 1.0f); };
 
     if constexpr (WAVES_K > 1) {
         // ---- add the K groups up in LDS, factors, residual, bias, bf16, store --------------------------------
@@ -670,7 +672,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int64_t row = m0 + (u * THREADS + (int)threadIdx.x) / CPR;
-            f[u] = a.row_scale ? a.row_scale[min(row, a.M - 1)] : 1.0f;
+            f[u] = has_row_scale ? a.row_scale[min(row, a.M - 1)] : 1.0f;
         }
         const float ts = tensor_scale();
         const bool wide_ok = ((reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) && (a.ldy % 8 == 0) && valid == 8;
@@ -712,13 +714,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
         // The ROW / TENSOR factors belong to the sparse product only, so they are applied to the
         // accumulators first. Then Y_r = T L_A^T, T = X L_B^T (bf16 [M,64]), is added by four dense
         // matrix-instruction steps over the rank; SMFMAC and MFMA of one size share one accumulator layout.
-        if (a.row_scale || has_tensor_scale) {
+        if (has_row_scale || has_tensor_scale) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int r = 0; r < RB; ++r) {
                     const int64_t row = min(lane_row + (i * S + reg_row(r)), a.M - 1);
-                    const float f = (a.row_scale ? a.row_scale[row] : 1.0f) * ts;
+                    const float f = (has_row_scale ? a.row_scale[row] : 1.0f) * ts;
 #pragma unroll
                     for (int j = 0; j < TN; ++j) acc[i][j][r] *= f;
                 }
@@ -793,7 +795,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
     // ---- epilogue: optional fp32 scales, bias, bf16 RNE, store --------------------------------
     auto finish = [&](float v, int64_t row, float bv) {
         if constexpr (MODE != 1) {
-            if (a.row_scale) v *= a.row_scale[row];
+            if (has_row_scale) v *= a.row_scale[row];
             if (has_tensor_scale) v *= ts;
         }
         if (a.bias) v += bv;
@@ -833,7 +835,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
             *reinterpret_cast<uint32_t*>(ep_lane + rl * ROWB + cl * 2) = w;
         };
         auto first_of_pair = [](int q) { return S == 32 ? 2 * q : q; };     // registers r, r + PS, q = 0 .. RB / 2 - 1
-        const bool scaled = MODE != 1 && (a.row_scale || has_tensor_scale);
+        const bool scaled = MODE != 1 && (has_row_scale || has_tensor_scale);
         if (!scaled && !a.bias) {
 #pragma unroll
             for (int j = 0; j < TN; ++j)
@@ -859,7 +861,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
 #pragma unroll
                 for (int q = 0; q < RB / 4; ++q) {  // registers 4 q .. 4 q + 3 are four consecutive rows
                     const int64_t row = lane_row + (i * S + reg_row(4 * q));
-                    if (!scaled || !a.row_scale) {
+                    if (!scaled || !has_row_scale) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) fr[i][4 * q + e] = 1.0f;
                     } else if (row + 3 < a.M && (reinterpret_cast<uintptr_t>(a.row_scale + row) & 15) == 0) {

@@ -254,3 +254,23 @@ def test_waves_of_a_row_make_no_extra_trips():
                 assert sum((r + 1535) // 1536 for r in runs) == (K + 1535) // 1536, (comp, M, K, parts, span)
                 if comp >= 2:
                     assert 8 % parts == 0
+
+
+def test_kernels_need_no_scratch_memory(tmp_path):
+    """No kernel of the library spills registers: scratch memory would cost every launch and is allocated by the runtime behind
+    the caller's back. Read from the metadata notes of the code objects inside the built library."""
+    import subprocess
+    readelf = "/opt/rocm/llvm/bin/llvm-readelf"
+    if not os.path.exists(readelf):
+        pytest.skip("no llvm-readelf")
+    blob = open(rtl.LIB_PATH, "rb").read()
+    starts = [m.start() for m in re.finditer(b"\x7fELF\x02\x01\x01\x40", blob)]      # ELF64, OS ABI AMDGPU_HSA
+    sizes, kernels = [], 0
+    for n, at in enumerate(starts):
+        p = tmp_path / ("%d.co" % n)
+        p.write_bytes(blob[at:])
+        notes = subprocess.run([readelf, "--notes", str(p)], capture_output=True, text=True).stdout
+        kernels += notes.count(".symbol:")
+        sizes += re.findall(r"\.private_segment_fixed_size:\s+(\d+)|\.vgpr_spill_count:\s+(\d+)", notes)
+    assert kernels > 60
+    assert {int(a or b) for a, b in sizes} == {0}
