@@ -933,6 +933,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
 // body tile's time. Every XCD works through its share of the body tiles first, then its share of
 // the tail tiles (workgroups are dispatched in id order). tail_tiles == 0: a plain one-shape launch.
 constexpr int kTailBN = 128;
+// Waves and ring of the 256 x 128 tail tile. Sparse: as the body. Dense: a ring of three (144 KB), where the body has room for two:
+// with two, a stage is requested only when the one before it has landed, and a plan of tail tiles alone (the operands arrive
+// more slowly than they are used) waits for every stage in full. 64 x 64 per wave instead of 128 x 32, because the columns'
+// fragments are refilled behind one row block's instructions and two of them are too few to hide it. us: [2967, 2624, 7936] 149.0 -> 111.9
+// (128 x 32 112.7), [3900, 2040, 3072] 62.5 -> 47.5 (48.2), [2967, 2624, 1024] 20.2 -> 18.8 (19.5), [6468, 2848, 5056] 203.1 -> 174.3.
+template <bool SPARSE>
+struct Tail {
+    static constexpr int kWavesM = SPARSE ? 2 : 4, kWavesN = SPARSE ? 4 : 2;
+    static constexpr int stages(int body) { return SPARSE ? body : 3; }
+};
 template <bool SPARSE, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false>
 __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
     static_assert(WAVES_M * WAVES_N == 8, "both tile shapes run with eight waves");
@@ -954,7 +964,7 @@ __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
         if (a.row_scale) t.row_scale = a.row_scale + a.m_split;
         if constexpr (MODE == 1) t.T = a.T + a.m_split * kLoraRank;
         const int idx = xcd_share_start(nb + nt, xcd) - xcd_share_start(nb, xcd) + (local - nb_x);
-        gemm_tile<SPARSE, 256, kTailBN, 2, 4, STAGES, MODE, FP8>(t, idx);
+        gemm_tile<SPARSE, 256, kTailBN, Tail<SPARSE>::kWavesM, Tail<SPARSE>::kWavesN, Tail<SPARSE>::stages(STAGES), MODE, FP8>(t, idx);
     }
 }
 
@@ -965,7 +975,7 @@ __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
 template <bool SPARSE, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false>
 struct Mixed {
     using LB = Smem<SPARSE, 256, BN, STAGES, WAVES_M, WAVES_N, FP8>;
-    using LT = Smem<SPARSE, 256, kTailBN, STAGES, 2, 4, FP8>;
+    using LT = Smem<SPARSE, 256, kTailBN, Tail<SPARSE>::stages(STAGES), Tail<SPARSE>::kWavesM, Tail<SPARSE>::kWavesN, FP8>;
     static constexpr int kLds = LB::kTotal > LT::kTotal ? LB::kTotal : LT::kTotal;
     static hipError_t prepare() {
         auto kern = gemm_mixed_kernel<SPARSE, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8>;
@@ -1315,7 +1325,7 @@ static hipError_t with_split(int i, Op op) {
             case 2: return op(Split<false, 64, 64, 1, 2, 2, 4>{});
             case 3: return op(Split<false, 128, 64, 2, 2, 2, 3>{});
             case 4: return op(Split<false, 128, 128, 2, 2, 1, 3>{});
-            case 5: return op(Split<false, 256, 128, 2, 4, 1, 3>{});
+            case 5: return op(Split<false, 256, 128, 4, 2, 1, 3>{});
             default: return op(Split<false, 256, 96, 4, 2, 1, 3>{});
         }
     }
@@ -1323,7 +1333,7 @@ static hipError_t with_split(int i, Op op) {
 
 template <bool SPARSE, int MODE, bool FP8, class Op>
 static hipError_t with_part(bool big, Op op) {
-    if (big) return op(Part<SPARSE, 256, 128, 2, 4, 3, MODE, FP8>{});
+    if (big) return op(Part<SPARSE, 256, 128, Tail<SPARSE>::kWavesM, Tail<SPARSE>::kWavesN, 3, MODE, FP8>{});
     return op(Part<SPARSE, 128, 128, 2, 2, 3, MODE, FP8>{});
 }
 
@@ -1416,7 +1426,7 @@ hipError_t launch_gemm(bool sparse, const GemmArgs& a_in, hipStream_t stream) {
         if (lora) return Mixed<true, 256, 2, 4, 3, 1>::launch(a, stream);
         return Mixed<true, 256, 2, 4, 3>::launch(a, stream);
     }
-    // dense: stages of 64 k (whole-line requests on the row-major operands), ring of two
+    // dense: stages of 64 k (whole-line requests on the row-major operands), body tiles with a ring of two
     if (plan.use_192) return Mixed<false, 192, 2, 4, 2>::launch(a, stream);
     return Mixed<false, 256, 2, 4, 2>::launch(a, stream);
 }
