@@ -216,7 +216,7 @@ __device__ __forceinline__ float mul_add_rn(float a, float b, float add) {
 // waves takes the k blocks g, g + WAVES_K, ... with operands and accumulators of its own, and the groups'
 // tiles are added up in LDS, in the order of g, when the loop is done.
 template <bool SPARSE, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false,
-          int WAVES_K = 1, bool PART = false, bool FOLDED = false>
+          int WAVES_K = 1, bool PART = false, bool FOLDED = false, bool PIN = true>
 __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, const int part = 0, const int kblk0 = 0,
                                           const int kblks = 0) {
     static_assert(!PART || WAVES_K == 1, "partial sums leave from the accumulators");
@@ -313,11 +313,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs a, const int tile, cons
     }
 
     const int64_t meta_stride = rows_pad * MREC;   // bytes between stage blocks
-    // (pinned to SGPRs here: left to itself the compiler may walk them along K in VGPRs, with two v_readfirstlane per
-    // request, which cost the bf16 loops 1.5 to 2.7 % at [4096, 3072, 12288] and [4608, 12288, 3072])
-    base_a = reinterpret_cast<const uint8_t*>(uniform64(base_a));
-    base_b = reinterpret_cast<const uint8_t*>(uniform64(base_b));
-    if constexpr (SPARSE) base_m = reinterpret_cast<const uint8_t*>(uniform64(base_m));
+    // PIN: in SGPRs from here on. Left to itself the compiler may walk them along K in VGPRs, with two v_readfirstlane per
+    // request, which cost the bf16 loops 1.5 to 2.7 % at [4096, 3072, 12288] and [4608, 12288, 3072]. The FP8 loops of the 256-row
+    // plan are not all better off with it (kPinStages).
+    if constexpr (PIN) {
+        base_a = reinterpret_cast<const uint8_t*>(uniform64(base_a));
+        base_b = reinterpret_cast<const uint8_t*>(uniform64(base_b));
+        if constexpr (SPARSE) base_m = reinterpret_cast<const uint8_t*>(uniform64(base_m));
+    }
     // Load number n (0 .. LOADS_PER_STAGE-1) of this wave for stage kt into ring buffer `stage`.
     // The loads of a stage are issued one at a time between matrix instructions: the texture
     // addresser takes a wave-wide 1 KiB request every ~16 cycles and a wave stalls at a request
@@ -943,7 +946,7 @@ struct Tail {
     static constexpr int kWavesM = SPARSE ? 2 : 4, kWavesN = SPARSE ? 4 : 2;
     static constexpr int stages(int body) { return SPARSE ? body : 3; }
 };
-template <bool SPARSE, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false>
+template <bool SPARSE, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE, bool FP8, bool PIN>
 __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
     static_assert(WAVES_M * WAVES_N == 8, "both tile shapes run with eight waves");
     const int xcd = (int)blockIdx.x % 8, local = (int)blockIdx.x / 8;
@@ -952,7 +955,7 @@ __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
     if (local < nb_x) {
         GemmArgs b = a;
         if (nt > 0) b.M = a.m_split;
-        gemm_tile<SPARSE, 256, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8>(b, xcd_share_start(nb, xcd) + local);
+        gemm_tile<SPARSE, 256, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, 1, false, false, PIN>(b, xcd_share_start(nb, xcd) + local);
     } else {
         // the tail region as a problem of its own: same operands, shifted by m_split rows
         constexpr int ESZ = FP8 ? 1 : 2;
@@ -964,7 +967,8 @@ __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
         if (a.row_scale) t.row_scale = a.row_scale + a.m_split;
         if constexpr (MODE == 1) t.T = a.T + a.m_split * kLoraRank;
         const int idx = xcd_share_start(nb + nt, xcd) - xcd_share_start(nb, xcd) + (local - nb_x);
-        gemm_tile<SPARSE, 256, kTailBN, Tail<SPARSE>::kWavesM, Tail<SPARSE>::kWavesN, Tail<SPARSE>::stages(STAGES), MODE, FP8>(t, idx);
+        gemm_tile<SPARSE, 256, kTailBN, Tail<SPARSE>::kWavesM, Tail<SPARSE>::kWavesN, Tail<SPARSE>::stages(STAGES), MODE, FP8, 1, false, false,
+                  PIN>(t, idx);
     }
 }
 
@@ -972,18 +976,18 @@ __global__ __launch_bounds__(512) void gemm_mixed_kernel(const GemmArgs a) {
 // per kernel by the prepare functions (called for every configuration from prepare_gemm_kernels, i.e.
 // from rtl_init or from the first entry-point call on a device), never from a launch, so that launches
 // consist of the kernel node only and can be recorded into a HIP graph.
-template <bool SPARSE, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false>
+template <bool SPARSE, int BN, int WAVES_M, int WAVES_N, int STAGES, int MODE = 0, bool FP8 = false, bool PIN = !FP8>
 struct Mixed {
     using LB = Smem<SPARSE, 256, BN, STAGES, WAVES_M, WAVES_N, FP8>;
     using LT = Smem<SPARSE, 256, kTailBN, Tail<SPARSE>::stages(STAGES), Tail<SPARSE>::kWavesM, Tail<SPARSE>::kWavesN, FP8>;
     static constexpr int kLds = LB::kTotal > LT::kTotal ? LB::kTotal : LT::kTotal;
     static hipError_t prepare() {
-        auto kern = gemm_mixed_kernel<SPARSE, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8>;
+        auto kern = gemm_mixed_kernel<SPARSE, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, PIN>;
         return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     }
     // a.m_split, a.body_tiles and a.tail_tiles come from the planner
     static hipError_t launch(const GemmArgs& a, hipStream_t stream) {
-        auto kern = gemm_mixed_kernel<SPARSE, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8>;
+        auto kern = gemm_mixed_kernel<SPARSE, BN, WAVES_M, WAVES_N, STAGES, MODE, FP8, PIN>;
         hipLaunchKernelGGL(kern, dim3((unsigned)(a.body_tiles + a.tail_tiles)), dim3(512), kLds, stream, a);
         return hipGetLastError();
     }
@@ -1305,6 +1309,13 @@ void gemm_choice(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K, size_t 
     out[2] = c.part_256 ? 256 : 128;
 }
 
+// FP8 calls of the 256-row plan: stream bases pinned to SGPRs (PIN of gemm_tile) with 256-column bodies from 20 stages of 128 k on.
+// Not pinned -> pinned, us: 256-column bodies [14238, 13344, K] K = 1024 193.3 -> 201.6, 1280 224.4 -> 248.5, 2048 282.4 -> 281.0, 2560
+// 339.9 -> 337.9, 3072 382.4 -> 374.3; [10000, 20000, K] 1280 231.4 -> 241.8, 2560 357.2 -> 350.8, 3072 404.5 -> 392.8; [12000, 2048, K] 1024
+// 40.6 -> 41.2, 2048 59.0 -> 60.7, 2560 65.1 -> 64.2; [9734, 5760, K] 768 63.9 -> 64.0, 2560 117.0 -> 115.7. 192-column bodies [5326, 3680, K]
+// 1024 31.8 -> 32.9, 3072 57.2 -> 57.9; [2887, 3072, 6144] 53.8 -> 53.7. (It is W's base that does it; a reason was not found.)
+constexpr int kPinStages = 20;
+
 // Runs `op` (launch or prepare) of small shape `i`. Ring depths: as many stages as LDS holds, two workgroups
 // per unit for 64 x 64 and 128 x 128 (sparse).
 template <bool SPARSE, int MODE, bool FP8, class Op>
@@ -1343,8 +1354,10 @@ hipError_t prepare_gemm_kernels() {
     auto run = [&](hipError_t r) { if (e == hipSuccess) e = r; };
     run(Mixed<true, 192, 4, 2, 3, 0, true>::prepare());
     run(Mixed<true, 256, 2, 4, 3, 0, true>::prepare());
+    run(Mixed<true, 256, 2, 4, 3, 0, true, true>::prepare());
     run(Mixed<true, 192, 4, 2, 3, 1, true>::prepare());
     run(Mixed<true, 256, 2, 4, 3, 1, true>::prepare());
+    run(Mixed<true, 256, 2, 4, 3, 1, true, true>::prepare());
     run(Mixed<true, 192, 4, 2, 3, 1>::prepare());
     run(Mixed<true, 192, 4, 2, 3>::prepare());
     run(Mixed<true, 256, 2, 4, 3, 1>::prepare());
@@ -1410,11 +1423,14 @@ hipError_t launch_gemm(bool sparse, const GemmArgs& a_in, hipStream_t stream) {
         return a.T ? with_split<true, 1, false>(split, go) : with_split<true, 0, false>(split, go);
     }
     if (sparse && a.fp8) {
+        const bool pin = a.K >= 128 * kPinStages;
         if (a.T != nullptr) {          // LoRA tail in bf16 on top of the FP8 product
             if (plan.use_192) return Mixed<true, 192, 4, 2, 3, 1, true>::launch(a, stream);
+            if (pin) return Mixed<true, 256, 2, 4, 3, 1, true, true>::launch(a, stream);
             return Mixed<true, 256, 2, 4, 3, 1, true>::launch(a, stream);
         }
         if (plan.use_192) return Mixed<true, 192, 4, 2, 3, 0, true>::launch(a, stream);
+        if (pin) return Mixed<true, 256, 2, 4, 3, 0, true, true>::launch(a, stream);
         return Mixed<true, 256, 2, 4, 3, 0, true>::launch(a, stream);
     }
     if (sparse) {

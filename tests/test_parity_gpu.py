@@ -1222,6 +1222,25 @@ def test_256_row_plan_every_stage_count(M, N, K, body, tails):
         assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b)[sel]), r["Y"]) <= Y_TOL
 
 
+@pytest.mark.parametrize("K", [2432, 2560])
+def test_fp8_256_column_bodies_on_both_sides_of_the_pinning_rule(K):
+    """19 and 20 stages of 128 k, plain and LoRA, ragged in both directions."""
+    M, N = 2311, 6151
+    plan = (ctypes.c_int64 * 4)()
+    assert rtl.lib().rtl_diag_tile_plan(M, N, 0, plan) == 0 and plan[0] == 256 and gemm_choice(True, True, M, N, K)[:2] == (-1, 1)
+    X = synth.activations("laplace_outlier", M, K, seed=21, device=DEV)
+    W = synth.weights(N, K, seed=22, device=DEV)
+    b = synth.bias(N, seed=23, device=DEV)
+    LA, LB = synth.lora(N, K, 64, seed=24, device=DEV, std_a=0.1, std_b=0.1)
+    sel = torch.tensor([0, 1535, 2048, M - 1], device=DEV)
+    xs, Wq = fp8_scale(X), rtl.quantize_fp8(W)
+    Xs, Wn, f, bb = synth.bits(X[sel]), Wq.cpu().numpy(), float(xs.item()), synth.bits(b)
+    r = oracle.sparse_linear_fp8_oracle(Xs, Wn, f, bias=bb, scope=oracle.GROUP)
+    check_y_fp8(rtl.sparse_linear_fp8(X, Wq, xs, bias=b)[sel], r, Wn, f, bias=bb, max_rows=2)
+    r = oracle.sparse_lora_linear_fp8_oracle(Xs, Wn, f, synth.bits(LA), synth.bits(LB), bias=bb, scope=oracle.GROUP)
+    assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b)[sel]), r["Y"]) <= Y_TOL
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 1, 128), (33, 31, 384), (37, 1000, 4736), (97, 3072, 3200), (201, 3009, 1408),
                                    (393, 3041, 1664), (700, 3000, 640)])
 def test_small_tiles_fp8(M, N, K):
