@@ -337,17 +337,19 @@ __global__ __launch_bounds__(256) void quantize_fp8_kernel(const uint16_t* __res
     *reinterpret_cast<uint2*>(Wq + r * ldq + c) = make_uint2(o[0], o[1]);
 }
 
-// Copy of the canonical operand into the k-major layout. A workgroup takes 64 rows and U neighbouring 64-k blocks: thread
-// (row r, piece p) moves piece p (16 bytes) of the row's U value blocks, all loads in flight together, and the metadata
-// records of the blocks p, p + 4, .... Reads are runs of 64 U bytes of a row, writes 4 KB contiguous per block.
+// Copy of the canonical operand into the k-major layout. A workgroup takes R = 2^log_rows rows (64, fewer where M is smaller) and 64 / R
+// groups of U neighbouring 64-k blocks: thread (group g, row r, piece p) moves piece p (16 bytes) of the row's U value blocks,
+// all loads in flight together, and the metadata records of the blocks p, p + 4, .... Reads are runs of 64 U bytes of a row,
+// writes 64 R bytes contiguous per block. (With R = 64 whatever M, calls of a few rows are 2 to 3 % slower: whole call [1, 6080, 1024]
+// 6.74 -> 6.99 us, [2, 11104, 512] 6.97 -> 7.18.)
 template <int U>
 __global__ __launch_bounds__(256) void operand_to_kmajor_kernel(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta,
                                                                 int64_t M, int KB, int64_t Mpad, uint8_t* __restrict__ vals_km,
-                                                                uint8_t* __restrict__ meta_km, unsigned row_blocks) {
+                                                                uint8_t* __restrict__ meta_km, unsigned row_blocks, int log_rows) {
     const int piece = (int)threadIdx.x & 3;
-    const int64_t row = (int64_t)(blockIdx.x % row_blocks) * 64 + (threadIdx.x >> 2);
-    const int b0 = (int)(blockIdx.x / row_blocks) * U;
-    if (row >= M) return;
+    const int64_t row = ((int64_t)(blockIdx.x % row_blocks) << log_rows) + ((threadIdx.x >> 2) & ((1u << log_rows) - 1));
+    const int b0 = (int)(((blockIdx.x / row_blocks) << (6 - log_rows)) + (threadIdx.x >> (2 + log_rows))) * U;
+    if (row >= M || b0 >= KB) return;
     const uint8_t* src = reinterpret_cast<const uint8_t*>(vals) + (row * KB + b0) * 64 + piece * 16;
     const uint8_t* msrc = meta + (row * KB + b0) * 8;
     const int last = KB - 1 - b0;                        // (blocks past K: the last one again, not stored)
@@ -380,14 +382,19 @@ hipError_t prepare_pack_kernels() {
 hipError_t launch_operand_to_kmajor(const uint16_t* vals, const uint8_t* meta, int64_t M, int64_t K,
                                     uint8_t* vals_km, uint8_t* meta_km, hipStream_t stream) {
     const int KB = (int)(K / 64);
+    int log_rows = 0;
+    while (log_rows < 6 && ((int64_t)1 << log_rows) < M) ++log_rows;
     const unsigned row_blocks = (unsigned)((M + 63) / 64);
     auto go = [&](auto kernel, int u) {
-        hipLaunchKernelGGL(kernel, dim3(row_blocks * (unsigned)((KB + u - 1) / u)), dim3(256), 0, stream, vals, meta, M, KB,
-                           kmajor_rows(M), vals_km, meta_km, row_blocks);
+        const int per = u << (6 - log_rows);             // k blocks of a workgroup
+        hipLaunchKernelGGL(kernel, dim3(row_blocks * (unsigned)((KB + per - 1) / per)), dim3(256), 0, stream, vals, meta, M, KB,
+                           kmajor_rows(M), vals_km, meta_km, row_blocks, log_rows);
     };
     // Four blocks per thread where that leaves two workgroups a compute unit, else one: whole rtl_packed_linear call with
     // 1 / 2 / 4 / 8 blocks, us: [4608, 1024, 3072] 38.6 / 36.0 / 34.2 / 33.1, [4096, 1024, 12288] 90.8 / 86.2 / 86.3 / 86.5, [16896, 512,
-    // 3072] 57.1 / 55.0 / 55.6 / 55.9; [512, 1024, 3072] 11.8 / 11.9 / 12.3 / 12.9, [1029, 512, 1024] 9.5 / 9.5 / 9.8 / 10.4.
+    // 3072] 57.1 / 55.0 / 55.6 / 55.9; [512, 1024, 3072] 11.8 / 11.9 / 12.3 / 12.9, [1029, 512, 1024] 9.5 / 9.5 / 9.8 / 10.4. Around the line, 1 / 2 / 4
+    // blocks, row_blocks x KB = 768 [512, 512, 6144] 15.1 / 15.3 / 15.4, 1152 [4608, 512, 1024] 15.4 / 15.5 / 15.6, 1632 [1029, 512, 6144] 25.0 / 24.8 / 24.7,
+    // 1728 [4608, 512, 1536] 18.9 / 19.0 / 18.9, 2304 [4608, 512, 2048] 22.0 / 21.8 / 21.5, 3072 [2048, 512, 6144] 28.2 / 27.8 / 27.1.
     if ((int64_t)row_blocks * KB >= 2048) go(operand_to_kmajor_kernel<4>, 4);
     else go(operand_to_kmajor_kernel<1>, 1);
     return hipGetLastError();

@@ -422,6 +422,24 @@ def test_kmajor_operand_is_the_relayout_of_the_canonical_outputs(M, K, comp):
         assert torch.equal(m_km, mbytes.permute(1, 0, 2)), "metadata, fp8=%s" % fp8
 
 
+@pytest.mark.parametrize("M,K", [(1, 64), (1, 4160), (2, 2112), (3, 4096), (5, 192), (17, 1088), (32, 512), (33, 640), (63, 64),
+                                 (64, 320), (65, 4160), (520, 12288), (4608, 1920), (4600, 1984), (8193, 1088)])
+def test_packed_linear_copies_the_operand(M, K):
+    """The k-major copy at the head of rtl_packed_linear's workspace holds exactly the canonical bytes (rows per workgroup from 1
+    to 64, one and four blocks per thread, partial last groups of rows and of blocks); rows past M stay as they were."""
+    X = synth.activations("laplace", M, K, seed=M + K, device=DEV)
+    W = synth.weights(64, K, seed=5, device=DEV)
+    vals, meta, _ = rtl.sparsify_pack(X, comp=rtl.COMP_NONE)
+    Mpad, KB = (M + 255) // 256 * 256, K // 64
+    ws = torch.full((int(rtl.lib().rtl_packed_linear_workspace(M, 64, K)) + 256,), 0xA5, dtype=torch.uint8, device=DEV)
+    rtl.packed_linear(vals, meta, W, ws=ws)
+    v_km = ws[:Mpad * KB * 64].view(KB, Mpad, 64)
+    m_km = ws[Mpad * KB * 64:Mpad * KB * 72].view(KB, Mpad, 8)
+    assert torch.equal(v_km[:, :M], vals.view(torch.uint8).reshape(M, KB, 64).permute(1, 0, 2))
+    assert torch.equal(m_km[:, :M], meta.reshape(M, KB, 8).permute(1, 0, 2))
+    assert bool((v_km[:, M:] == 0xA5).all()) and bool((m_km[:, M:] == 0xA5).all())
+
+
 @pytest.mark.parametrize("comp", COMPS)
 def test_diag_pack_sweep_is_the_first_half_of_sparse_linear(comp):
     """rtl_diag_pack_sweep (what bench.py times as the sparsification share of a call) must leave the
