@@ -318,15 +318,20 @@ static size_t pack_down_bytes(int64_t M, int splits) {     // partial planes, th
 size_t pack_down_scratch_bytes(int64_t M, int64_t K) { return pack_down_bytes(M, pack_down_ranges(M, K, nullptr, kMaxRanges)); }
 size_t pack_down_scratch_min(int64_t M, int64_t K) { return pack_down_bytes(M, pack_down_ranges(M, K, nullptr, 16)); }
 
+// Few rows and a short contraction: the sweep with T beside it in the same launch (sparsify_down_kernel) ends before the fused
+// sweep and its reduction. Up to 1024 rows T's workgroups have a compute unit each; beyond, some units have two of them, and a unit
+// gets their operands no faster for it. Whole call [M, 2048, K] GROUP, that over the fused sweep, bf16 | FP8: [1024, 2048] 0.93 | 0.82,
+// [1024, 3072] 0.94 | 0.89, [1040, 3072] 1.01 | 1.01 (NONE 1.07 | 1.05), [1280, 1792] 0.96 | 0.86 (1.01 | 0.93), [1280, 2048] 0.99 | 0.88
+// (1.05 | 0.95), [1280, 2560] 1.06 | 0.99 (1.09 | 1.06), [1400, 2048] 1.04 | 1.03, [2048, 1536] 0.94 | 0.89 (0.97 | 0.93), [2304, 1536] 0.98 | 0.94 (1.03 |
+// 1.00), [2048, 2048] 1.01 | 1.02; [16, 3072] 1.00 | 0.95, [16, 3840] 1.10 | 1.05, [512, 3840] 0.98 | 0.85, [512, 4608] 1.04 | 0.95.
+static bool sweep_with_down(int64_t M, int64_t K, bool fp8) {
+    return K <= (M <= 1024 ? 3072 : M <= 1280 ? (fp8 ? 2304 : 1792) : M <= 2048 ? 1536 : 0);
+}
+
 hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps,
                             const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, float* scratch,
                             size_t scratch_bytes, uint16_t* T, float* scale, float* rowsums, hipStream_t stream, const float* x_scale) {
-    // Few rows and a short contraction: the sweep with T beside it in the same launch (sparsify_down_kernel) ends before this one
-    // and its reduction. Whole call [M, 3072, K], fused sweep -> that, us, bf16 | FP8: [37, 512] 11.7 -> 8.8 | 11.5 -> 7.9, [512, 1024]
-    // 19.8 -> 15.9 | 19.3 -> 14.5, [512, 3072] 27.0 -> 25.8 | 25.6 -> 21.6, [1029, 3072] 39.8 -> 39.0 | 27.5 -> 26.5, [2048, 1024] 26.1 -> 23.9
-    // | 26.9 -> 21.8, [2048, 1536] 29.9 -> 28.1 | 28.3 -> 25.8. Beyond the line it loses: [1536, 3072] 48.5 -> 50.0, [2048, 2048] 33.7 ->
-    // 34.0, [512, 4608] 40.8 -> 41.6, [4608, 1536] 46.3 -> 49.6.
-    if ((M <= 1280 && K <= 3072) || (M <= 2048 && K <= 1536))
+    if (sweep_with_down(M, K, x_scale != nullptr))
         return launch_sparsify_down(X, M, K, ldx, comp, eps, LB, ldlb, vals_km, meta_km, T, scale, rowsums, stream, x_scale);
     int per = 1;
     const size_t fit = scratch_bytes / pack_down_bytes(M, 1);

@@ -640,11 +640,11 @@ def test_dense_tiles_of_256_by_96(M, N, K):
 
 
 @pytest.mark.parametrize("comp", COMPS)
-@pytest.mark.parametrize("M,K", [(1, 128), (15, 640), (17, 2048), (129, 3072), (1280, 384), (1281, 1536), (2048, 512),
+@pytest.mark.parametrize("M,K", [(1, 128), (15, 640), (17, 2048), (129, 3072), (1024, 3072), (1280, 384), (1280, 1792), (1281, 1536), (2048, 512),
                                  (129, 3200), (1281, 1664)])
 def test_lora_down_projection_of_few_rows(M, K, comp):
     """T = X L_B^T formed beside the sweep (rows not whole 16-row tiles, fewer 64-k blocks than waves, rests of the unrolled
-    trips, both corners of the rule; the last two shapes lie outside it). With W = 0 the call is the residual alone:
+    trips, the corners of the rule; the last two shapes lie outside it). With W = 0 the call is the residual alone:
     Y = (X L_B^T) L_A^T, and with L_A = 0 it is the plain call, bit for bit where its sweep is (FP8 alike)."""
     N = 136
     X = synth.activations("laplace_outlier", M, K, seed=61, device=DEV)
