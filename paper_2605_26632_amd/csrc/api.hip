@@ -281,11 +281,11 @@ rtl_status rtl_sparse_linear_static(const void* X, const void* W, const void* bi
 }
 
 // rtl_sparse_lora_linear workspace: [rtl_sparse_linear workspace | T as two bf16 planes [2][M,64] |
-// per-K-range partial planes and row sums of the one-pass sweep]
+// per-K-range partial planes and row sums of the one-pass sweep (none where few rows have T formed whole)]
 size_t rtl_sparse_lora_linear_workspace(int64_t M, int64_t N, int64_t K, int64_t R, rtl_comp comp) {
     if (M <= 0 || N <= 0 || K <= 0 || R != rtl::kLoraRank || !comp_ok(comp)) return 0;
     return with_partials(sparse_ws(M, K, comp).total + round_up((size_t)M * rtl::kLoraRank * 4, 256) +
-                             round_up(rtl::pack_down_scratch_bytes(M, K), 256),
+                             round_up(rtl::pack_down_scratch_bytes(M, K, false), 256),
                          planes_room(M, K), true, false, M, N, K);
 }
 
@@ -304,7 +304,7 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
         return RTL_ERR_ALIGN;
     const SparseWs ws = sparse_ws(M, K, comp);
     const size_t t_off = ws.total, p_off = t_off + round_up((size_t)M * rtl::kLoraRank * 4, 256);
-    const size_t need = p_off + round_up(rtl::pack_down_scratch_min(M, K), 256);   // the query asks for the preferred size
+    const size_t need = p_off + round_up(rtl::pack_down_scratch_min(M, K, false), 256);   // the query asks for the preferred size
     if (!workspace || workspace_bytes < need) return RTL_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return RTL_ERR_ALIGN;
     RTL_REQUIRE_DEVICE();
@@ -331,7 +331,7 @@ rtl_status rtl_sparse_lora_linear(const void* X, const void* W, const void* LA, 
     g.T = T;
     g.LA = static_cast<const uint16_t*>(LA);
     g.ldla = ldla;
-    give_partials(g, base, p_off + round_up(rtl::pack_down_scratch_bytes(M, K), 256), workspace_bytes, planes_room(M, K));
+    give_partials(g, base, p_off + round_up(rtl::pack_down_scratch_bytes(M, K, false), 256), workspace_bytes, planes_room(M, K));
     e = rtl::launch_gemm(true, g, s);
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }
@@ -424,7 +424,7 @@ rtl_status rtl_sparse_linear_fp8(const void* X, const void* Wq, const float* x_s
 size_t rtl_sparse_lora_linear_fp8_workspace(int64_t M, int64_t N, int64_t K, int64_t R, rtl_comp comp) {
     if (M <= 0 || N <= 0 || K <= 0 || R != rtl::kLoraRank || !comp_ok(comp)) return 0;
     return with_partials(sparse_ws(M, K, comp, 1).total + round_up((size_t)M * rtl::kLoraRank * 4, 256) +
-                             round_up(rtl::pack_down_scratch_bytes(M, K), 256),
+                             round_up(rtl::pack_down_scratch_bytes(M, K, true), 256),
                          planes_room(M, K, 1), true, true, M, N, K);
 }
 
@@ -443,7 +443,7 @@ rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float
         return RTL_ERR_ALIGN;
     const SparseWs ws = sparse_ws(M, K, comp, 1);
     const size_t t_off = ws.total, p_off = t_off + round_up((size_t)M * rtl::kLoraRank * 4, 256);
-    const size_t need = p_off + round_up(rtl::pack_down_scratch_min(M, K), 256);   // the query asks for the preferred size
+    const size_t need = p_off + round_up(rtl::pack_down_scratch_min(M, K, true), 256);   // the query asks for the preferred size
     if (!workspace || workspace_bytes < need) return RTL_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return RTL_ERR_ALIGN;
     RTL_REQUIRE_DEVICE();
@@ -472,7 +472,7 @@ rtl_status rtl_sparse_lora_linear_fp8(const void* X, const void* Wq, const float
     g.T = T;
     g.LA = static_cast<const uint16_t*>(LA);
     g.ldla = ldla;
-    give_partials(g, base, p_off + round_up(rtl::pack_down_scratch_bytes(M, K), 256), workspace_bytes, planes_room(M, K, 1));
+    give_partials(g, base, p_off + round_up(rtl::pack_down_scratch_bytes(M, K, true), 256), workspace_bytes, planes_room(M, K, 1));
     e = rtl::launch_gemm(true, g, s);
     return e == hipSuccess ? RTL_OK : RTL_ERR_HIP;
 }

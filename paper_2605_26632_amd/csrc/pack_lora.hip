@@ -312,12 +312,6 @@ static int pack_down_ranges(int64_t M, int64_t K, int* per_out, int room) {
     return (KT + per - 1) / per;
 }
 
-static size_t pack_down_bytes(int64_t M, int splits) {     // partial planes, then the row sums of the K ranges
-    return (size_t)splits * (size_t)M * (kLoraRank + 2) * sizeof(float);
-}
-size_t pack_down_scratch_bytes(int64_t M, int64_t K) { return pack_down_bytes(M, pack_down_ranges(M, K, nullptr, kMaxRanges)); }
-size_t pack_down_scratch_min(int64_t M, int64_t K) { return pack_down_bytes(M, pack_down_ranges(M, K, nullptr, 16)); }
-
 // Few rows and a short contraction: the sweep with T beside it in the same launch (sparsify_down_kernel) ends before the fused
 // sweep and its reduction. Up to 1024 rows T's workgroups have a compute unit each; beyond, some units have two of them, and a unit
 // gets their operands no faster for it. Whole call [M, 2048, K] GROUP, that over the fused sweep, bf16 | FP8: [1024, 2048] 0.93 | 0.82,
@@ -327,6 +321,15 @@ size_t pack_down_scratch_min(int64_t M, int64_t K) { return pack_down_bytes(M, p
 static bool sweep_with_down(int64_t M, int64_t K, bool fp8) {
     return K <= (M <= 1024 ? 3072 : M <= 1280 ? (fp8 ? 2304 : 1792) : M <= 2048 ? 1536 : 0);
 }
+
+static size_t pack_down_bytes(int64_t M, int splits) {     // partial planes, then the row sums of the K ranges
+    return (size_t)splits * (size_t)M * (kLoraRank + 2) * sizeof(float);
+}
+static size_t pack_down_scratch(int64_t M, int64_t K, bool fp8, int room) {
+    return sweep_with_down(M, K, fp8) ? 0 : pack_down_bytes(M, pack_down_ranges(M, K, nullptr, room));
+}
+size_t pack_down_scratch_bytes(int64_t M, int64_t K, bool fp8) { return pack_down_scratch(M, K, fp8, kMaxRanges); }
+size_t pack_down_scratch_min(int64_t M, int64_t K, bool fp8) { return pack_down_scratch(M, K, fp8, 16); }
 
 hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps,
                             const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, float* scratch,

@@ -107,12 +107,14 @@ constexpr int kLoraRank = 64;
 
 // One pass over X for the LoRA branch (pack_lora.hip): the sweep writes the k-major compressed operand (as
 // launch_sparsify_pack does) and, per K range, an fp32 partial plane of T = X L_B^T and (ROW / TENSOR) the
-// row sums of squares, into `scratch` (scratch_bytes >= pack_down_scratch_min(M, K); the number of ranges is
-// the preferred one with pack_down_scratch_bytes(M, K)); a second small kernel adds the ranges up in a fixed
+// row sums of squares, into `scratch` (scratch_bytes >= pack_down_scratch_min(M, K, fp8); the number of ranges is
+// the preferred one with pack_down_scratch_bytes(M, K, fp8)); a second small kernel adds the ranges up in a fixed
 // order into the two bf16 planes of T ([2][M][64]: hi, lo), the ROW factors `scale` [M] or
-// the TENSOR row sums `rowsums` [M][2], from which launch_gemm forms the factor (GemmArgs::rowsums).
-size_t pack_down_scratch_bytes(int64_t M, int64_t K);
-size_t pack_down_scratch_min(int64_t M, int64_t K);
+// the TENSOR row sums `rowsums` [M][2], from which launch_gemm forms the factor (GemmArgs::rowsums). Few rows with a
+// short contraction take launch_sparsify_down instead, which needs no scratch: both sizes are 0 there.
+// x_scale set: FP8 form: kept values as E4M3 codes of (s x) / x_scale[0] in the FP8 k-major layout, K % 128 == 0.
+size_t pack_down_scratch_bytes(int64_t M, int64_t K, bool fp8);
+size_t pack_down_scratch_min(int64_t M, int64_t K, bool fp8);
 hipError_t prepare_pack_lora_kernels();
 hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps,
                             const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, float* scratch,
@@ -122,7 +124,6 @@ hipError_t launch_pack_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx
 hipError_t launch_sparsify_down(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, rtl_comp comp, float eps,
                                 const uint16_t* LB, int64_t ldlb, uint8_t* vals_km, uint8_t* meta_km, uint16_t* T,
                                 float* scale, float* rowsums, hipStream_t stream, const float* x_scale);
-// (x_scale set: FP8 form: kept values as E4M3 codes of (s x) / x_scale[0] in the FP8 k-major layout, K % 128 == 0.)
 // TENSOR scope: the single factor from the per-row sums [M][2] (fixed order, fp64), into scale[0]; `fused`
 // (nullable) receives scale[0] * mul[0].
 hipError_t launch_tensor_scale(const float* rowsums, int64_t M, float eps, float* scale, hipStream_t stream,

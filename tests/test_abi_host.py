@@ -256,6 +256,26 @@ def test_waves_of_a_row_make_no_extra_trips():
                     assert 8 % parts == 0
 
 
+@pytest.mark.parametrize("M,K,bf16_needs,fp8_needs", [(1, 128, False, False), (1024, 3072, False, False), (1025, 3072, True, True),
+                                                      (1024, 3200, True, True), (1280, 1792, False, False), (1280, 2304, True, False),
+                                                      (1281, 1792, True, True), (2048, 1536, False, False), (2049, 128, True, True)])
+def test_lora_calls_without_k_ranges_ask_for_no_room_for_them(M, K, bf16_needs, fp8_needs):
+    """Few rows with a short contraction have T = X L_B^T formed whole: operand and T are then all that a LoRA call needs."""
+    L, N = rtl.lib(), 1 << 20                            # (no contraction is split at that width)
+    t_bytes = (M * 64 * 4 + 255) // 256 * 256
+    for needs, plain, lora, call in (
+            (bf16_needs, L.rtl_sparse_linear_workspace, L.rtl_sparse_lora_linear_workspace,
+             lambda n: L.rtl_sparse_lora_linear(FAKE, FAKE, FAKE, FAKE, 0, FAKE, M, N, K, 64, K, K, 64, K, N, 3, 1e-8, FAKE, n, 0)),
+            (fp8_needs, L.rtl_sparse_linear_fp8_workspace, L.rtl_sparse_lora_linear_fp8_workspace,
+             lambda n: L.rtl_sparse_lora_linear_fp8(FAKE, FAKE, FAKE, FAKE, FAKE, 0, FAKE, M, N, K, 64, K, K, 64, K, N, 3, 1e-8,
+                                                    FAKE, n, 0))):
+        whole = plain(M, N, K, 3) + t_bytes
+        assert (lora(M, N, K, 64, 3) > whole) == needs
+        assert call(whole - 1) == 4
+        if needs:                                        # (an accepted call would launch where there is a device)
+            assert call(whole) == 4
+
+
 def test_kernels_need_no_scratch_memory(tmp_path):
     """No kernel of the library spills registers: scratch memory would cost every launch and is allocated by the runtime behind
     the caller's back. Read from the metadata notes of the code objects inside the built library."""

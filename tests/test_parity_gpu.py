@@ -512,10 +512,10 @@ def test_sparse_lora_linear_fp8_tiny_config(comp):
     assert torch.equal(Y0, rtl.sparse_linear_fp8(X, Wq, xs, bias=b, comp=comp))
 
 
-@pytest.mark.parametrize("shape", [(300, 200, 384), (129, 64, 128), (520, 64, 3072), "mlp_down"])
+@pytest.mark.parametrize("shape", [(300, 200, 384), (129, 64, 128), (520, 64, 3072), (2049, 64, 3072), (300, 200, 3456), "mlp_down"])
 def test_sparse_lora_linear_fp8_operand_and_sampled_rows(shape):
     """Ragged and full shapes: the FP8 compressed operand the one-pass sweep leaves must equal, bit for
-    bit, the one rtl_sparse_linear_fp8's sweep leaves (head of the workspace; at K = 3072 the K ranges are
+    bit, the one rtl_sparse_linear_fp8's sweep leaves (head of the workspace; at M = 2049 the K ranges are
     three 64-k stages long, so range boundaries fall inside 128-k blocks), and sampled rows of Y must meet
     the output bound."""
     if isinstance(shape, str):
@@ -668,12 +668,13 @@ def test_lora_down_projection_of_few_rows(M, K, comp):
 
 @pytest.mark.parametrize("comp", [rtl.COMP_NONE, rtl.COMP_GROUP])
 @pytest.mark.parametrize("shape", ["tiny", "mlp_down", "hr_out_proj", "hr_mlp_down", (300, 200, 192), (129, 64, 64),
-                                   (1000, 128, 1088)])
+                                   (1000, 128, 1088), (129, 200, 3264), (1000, 128, 3136), (2049, 128, 1088), (2049, 64, 64)])
 def test_one_pass_lora_sweep_writes_the_same_compressed_operand(shape, comp):
     """GROUP / NONE: the sweep that also forms X L_B^T must leave, bit for bit, the compressed operand
     (k-major values and metadata, head of the workspace) that the plain sweep of rtl_sparse_linear
-    leaves; rows past M of the padded layout are unspecified and not compared. K = 1088 = 17 blocks
-    leaves the last of its K ranges shorter than the others."""
+    leaves; rows past M of the padded layout are unspecified and not compared. The first three of the ragged
+    shapes form X L_B^T beside the plain sweep, the others in the fused one (3264, 3136 and 1088 are 51, 49 and
+    17 blocks, and leave the last of their K ranges shorter than the others)."""
     if isinstance(shape, str):
         X, W = synth.workload(shape, seed=0, device=DEV)
     else:
@@ -1297,11 +1298,12 @@ def test_pack_runs_of_whole_trips(M, K, comp):
     check_pack_fp8(X, comp, fp8_scale(X))
 
 
-@pytest.mark.parametrize("M,K", [(1, 64), (130, 4160), (513, 12288), (1029, 3072), (2049, 1088)])
+@pytest.mark.parametrize("M,K", [(1, 64), (130, 4160), (513, 12288), (1029, 3072), (2049, 1088), (2049, 64), (129, 3264)])
 @pytest.mark.parametrize("comp", [rtl.COMP_ROW, rtl.COMP_TENSOR])
 def test_lora_sweep_ranges_and_smaller_workspace(M, K, comp):
     """One to 64 K ranges (block counts that do not divide over them), sums over the ranges, and the smallest
-    workspace the call accepts: 16 ranges at most, same result up to the grouping of the fp32 sums over K."""
+    workspace the call accepts: 16 ranges at most, same result up to the grouping of the fp32 sums over K. ([1, 64] has its
+    X L_B^T formed whole, without ranges.)"""
     N = 40
     X = synth.activations("laplace_outlier", M, K, seed=M, device=DEV)
     W = synth.weights(N, K, seed=K, device=DEV)
