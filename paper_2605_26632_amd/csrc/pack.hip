@@ -505,10 +505,9 @@ hipError_t launch_sparsify_down(const uint16_t* X, int64_t M, int64_t K, int64_t
     int split[2];
     int64_t blocks;
     if (!x_scale && (comp == RTL_COMP_NONE || comp == RTL_COMP_GROUP)) {
-        const int KB = (int)(K / 64);
         split[0] = (int)((M + 31) / 32);
-        split[1] = KB >= 96 ? kBlockUnroll : 1;
-        blocks = split[0] * (int64_t)(((KB + split[1] - 1) / split[1] + kWavesPerBlock - 1) / kWavesPerBlock);
+        split[1] = 1;                                    // (short contractions only: one block per wave, see launch_pack_down)
+        blocks = split[0] * (int64_t)((K / 64 + kWavesPerBlock - 1) / kWavesPerBlock);
     } else {
         row_split((int)comp, M, K, split);
         blocks = (M * split[0] + kWavesPerBlock - 1) / kWavesPerBlock;
