@@ -1212,42 +1212,44 @@ struct SplitShape {
 };
 // Sparse 256 x 96 (eight waves of 32 rows, ring of four) stands between the 128 x 128 tile and the 256-row plan: with the plan's
 // 256 x 128 tiles an output of 130 to 192 tiles leaves compute units idle and each of the others pulls 34 KB a stage, here up to 256
-// pull 30. Its constants put the line where measurement has it; 58 of 170 drawn shapes of all sparse kinds that it can run
-// in one pass ([129..4608, 512..21504, 512..15360], inputs from HBM) took it with {4.4, 0.385}, 5.5 % faster in the mean: sparse [512, 9216,
-// 3072] 39.6 -> 36.6 us, [3738, 1184, 8448] 100.1 -> 90.0, FP8 [512, 12288, 3072] 28.2 -> 26.4, LoRA [512, 12288, 3072] 46.9 ->
-// 45.0; the five that lost (K <= 1920, 3 to 6 %) are what the larger fixed part leaves to the plan.
-// Dense 256 x 96 (ring of three) for the same reason where 256 x 128 tiles do not reach all units: 39 of 120 drawn shapes took it, 7 % faster
-// in the mean and none slower: [2028, 2560, 1792] 26.1 -> 21.7 us, [734, 7520, 13440] 174.6 -> 159.4, [370, 11648, 9216] 128 -> 118.
+// pull 30. Its constants put the line where measurement has it, which is at fewer stages in FP8 (kFixed96Fp8). Forced against the best
+// other form at 760 drawn shapes of all sparse kinds that it can run in one pass ([129..16896, 512..21504, 512..15360], inputs from HBM):
+// bf16 58 of 490 take it, FP8 75 of 270, 7.1 % and 4.7 % faster in the mean and none slower by 1 %: sparse [793, 4672, 8960] 98.5 -> 86.0 us, [4906,
+// 832, 11392] 128 -> 119, FP8 [737, 5825, 6400] 52.1 -> 48.7, FP8 + LoRA [434, 10432, 512] 13.9 -> 13.0; with a line at 20 stages bf16 lost up to 9 %
+// ([886, 5952, 1280], [3516, 1504, 1536] 22.7 -> 24.5).
+// Dense 256 x 96 (ring of three) for the same reason where 256 x 128 tiles do not reach all units: 108 of 2360 drawn shapes take it, 5.9 % faster
+// than the best other form in the mean, 9.7 % slower at worst.
 constexpr SplitShape kSparseShapes[] = {
     {32, 32, 1.2, 0.087}, {64, 32, 1.9, 0.108}, {64, 64, 2.4, 0.153}, {128, 64, 2.3, 0.19}, {128, 128, 2.8, 0.30},
-    {256, 96, 5.2, 0.37}};
+    {256, 96, 9.2, 0.325}};
+constexpr double kFixed96Fp8 = 3.4;
 constexpr SplitShape kDenseShapes[] = {
-    {32, 32, 1.2, 0.10}, {64, 32, 1.8, 0.135}, {64, 64, 1.0, 0.18}, {128, 64, 2.5, 0.262}, {128, 128, 3.8, 0.36},
-    {256, 128, 4.0, 0.48}, {256, 96, 3.9, 0.445}};
+    {32, 32, 1.45, 0.081}, {64, 32, 1.55, 0.135}, {64, 64, 1.25, 0.19}, {128, 64, 2.5, 0.285}, {128, 128, 3.4, 0.38},
+    {256, 128, 4.15, 0.525}, {256, 96, 3.95, 0.44}};
 
 // How the problem should run. Times are estimated from the measured constants: a small shape needs ceil(tiles / 256)
 // passes over the 256 compute units; with more than one, all units pull operands all the time and slow each other down
-// beyond the constants, which were taken one workgroup to a unit (factor 1.1; dense 128 x 128 1.15 with two passes, 1.3
+// beyond the constants, which were taken one workgroup to a unit (factor 1.1; dense 1.24, 128 x 128 1.12 with two passes, 1.3
 // with more). The 256-row plan is its simulated schedule times the time per KB of a stage, which grows from 10.7 ns (dense
-// 15.5: both operands row-major) while at most 96 units work to 17.2 (21) when all do and share the L2s and the power
-// budget. One table serves every operand kind: FP8 and LoRA calls rank the same way (LoRA's residual, 5 us a tile of the
-// 256-row plan, is left out), and LoRA without its residual then sums like the plain call.
-// Against every variant forced one by one on 3130 shapes ([1..6000, 512..21504, 512..15360], all six kinds of call, 1320 of
-// them drawn where several passes compete with the 256-row plan): 1.2 % slower than the best on average, more than 2 %
-// slower than the 256-row plan at 11. With the factors at 0.92 (sparse 64 x 64 and 128 x 128), 1.0 and 1.1 (dense) it was
-// 118, by up to 1.29x (128 x 128 tiles in several passes: sparse [1408, 14368, 11904] 303 -> 392 us, LoRA [639, 10400, 11776]
-// 137 -> 169); above 2048 rows, 128 x 128 tiles in several passes won more than 3 % at 2 of 220.
+// 14.6: both operands row-major) while at most 96 units work to 17.2 (20) when all do and share the L2s and the power
+// budget. One table serves every operand kind, but for the line of the sparse 256 x 96 tile: the others rank the same way in FP8 and LoRA
+// calls (LoRA's residual, 5 us a tile of the 256-row plan, is left out), and LoRA without its residual then sums like the plain call.
+// Against every form forced one by one on drawn shapes that played no part in the fit ([1..16896, 512..21504, 512..15360], inputs from
+// HBM): sparse of all kinds, 700 shapes: 1.1 % slower than the best on average, more than 2 % slower than the 256-row plan at 2; dense,
+// 700 shapes: 0.4 % and 5. (The constants of the dense loop before its 16 x 16 instructions: 2.1 % and 19 of 2360.)
+// With the factors at 0.92 (sparse 64 x 64 and 128 x 128) 128 x 128 tiles in several passes lost up to 1.29x to the plan: [1408, 14368,
+// 11904] 303 -> 392 us; above 2048 rows they won more than 3 % at 2 of 220.
 struct SplitChoice {
     int shape;       // index of the small shape, or -1 for the 256-row plan
     int k_splits;    // > 1: gemm_part_kernel on the 128 x 128 (part_256 false) or 256 x 128 tile
     bool part_256;
 };
 static int64_t part_pitch(int64_t N) { return (N + 7) / 8 * 8; }     // columns of a plane: whole eight-column chunks
-static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_t blocks, bool dense, size_t room) {
+static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_t blocks, bool dense, bool fp8, size_t room) {
     const double busy = (double)(plan.body_tiles + plan.tail_tiles < 256 ? plan.body_tiles + plan.tail_tiles : 256);
     const double load = busy > 96 ? (busy - 96) / 160 : 0.0;
-    const double per_kb = dense ? 0.0155 + 0.0055 * load : 0.0107 + 0.0065 * load;
-    double best = 3.4 + (double)blocks * plan.cost * per_kb;
+    const double per_kb = dense ? 0.0146 + 0.0053 * load : 0.0107 + 0.0065 * load;
+    double best = (dense ? 3.3 : 3.4) + (double)blocks * plan.cost * per_kb;
     SplitChoice pick{-1, 1, false};
     const SplitShape* shapes = dense ? kDenseShapes : kSparseShapes;
     const int count = dense ? (int)(sizeof(kDenseShapes) / sizeof(SplitShape)) : (int)(sizeof(kSparseShapes) / sizeof(SplitShape));
@@ -1257,33 +1259,33 @@ static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_
         if (tiles > 4096) continue;                        // far more than a few passes: never the better one
         double block = s.block;
         if (s.bm == 256) {                                 // one pass only, slower as the chip fills (its rivals are, in the sparse case)
-            if (tiles > 256 || (!dense && M > 4608)) continue;     // (sparse: not measured beyond)
-            if (dense && s.bn == 128 && tiles > 96) block += 0.0026 * (double)(tiles - 96);
-            if (dense && s.bn == 96 && tiles > 128) block += 0.0019 * (double)(tiles - 128);
+            if (tiles > 256) continue;
+            if (dense && s.bn == 128 && tiles > 96) block += 0.0029 * (double)(tiles - 96);
+            if (dense && s.bn == 96 && tiles > 128) block += 0.0021 * (double)(tiles - 128);
         }
+        if (dense && s.bm == 32) block += 0.0005 * (double)(M < 32 ? M : 32);      // (rows past M repeat the last one: less to pull)
         const int64_t passes = (tiles + 255) / 256;
         if (passes > 1 && s.bm >= 128 && s.bn >= 128 && M > 2048) continue;
         // (the dense 64 x 64 line was fitted at long K; with one or two blocks it takes what its neighbours do: [161, 6168, 128]
         // 8.2 us against 7.4 with the 256-row plan and 6.4 with 128 x 64, [1981, 1024, 128] 7.4 / 6.2 / 5.5)
-        const double fixed = dense && s.bm == 64 && s.bn == 64 && blocks <= 2 ? 2.4 : s.fixed;
-        const double several = !(dense && s.bm >= 128 && s.bn >= 128) ? 1.1 : (passes > 2 ? 1.3 : 1.15);
+        const double fixed = dense && s.bm == 64 && s.bn == 64 && blocks <= 2 ? 2.4 : fp8 && s.bm == 256 ? kFixed96Fp8 : s.fixed;
+        const double several = !dense ? 1.1 : s.bm >= 128 && s.bn >= 128 ? (passes > 2 ? 1.3 : 1.12) : 1.24;
         const double t = (double)passes * (fixed + (double)blocks * block) * (passes > 1 ? several : 1.0);
         if (t < best) {
             best = t;
             pick.shape = i;
         }
     }
-    // Contraction split over workgroups: at most one workgroup per compute unit (dense 224: the last ones slow all
-    // others down), at least 16 blocks each, up to six parts (dense eight). Second launch, writing and reading the planes: 8 us + 0.5 us per MB of
-    // planes (dense 4.5 + 0.8), fitted to 150 points at N = 1024 and 3072, K = 6144 and 12288; the estimate has to be
-    // 2 % better than the best unsplit one.
+    // Contraction split over workgroups: at most one workgroup per compute unit, at least 16 blocks each (dense 20), up to six parts
+    // (dense eight). Second launch, writing and reading the planes: 8 us + 0.5 us per MB of planes (dense 5.1 + 0.31); the
+    // estimate has to be 2 % better than the best unsplit one.
     for (int big = 0; big < 2; ++big) {
         const int64_t tiles = ((M + (big ? 255 : 127)) / (big ? 256 : 128)) * ((N + 127) / 128);
-        const double block = big ? (dense ? 0.53 : 0.35) : (dense ? 0.36 : 0.285);
-        for (int s = 2; s <= (dense ? kMaxKSplits : 6) && tiles * s <= (dense ? 224 : 256) && blocks / s >= 16; ++s) {
+        const double block = big ? (dense ? 0.535 : 0.35) : (dense ? 0.395 : 0.285);
+        for (int s = 2; s <= (dense ? kMaxKSplits : 6) && tiles * s <= 256 && blocks / s >= (dense ? 20 : 16); ++s) {
             const double planes = (double)s * (double)M * (double)part_pitch(N) * 4.0;
             if (planes > (double)room) break;
-            const double t = (double)((blocks + s - 1) / s) * block + (dense ? 4.5 + planes * 0.8e-6 : 8.0 + planes * 0.5e-6);
+            const double t = (double)((blocks + s - 1) / s) * block + (dense ? 5.1 + planes * 0.31e-6 : 8.0 + planes * 0.5e-6);
             if (t < best * (pick.k_splits > 1 ? 1.0 : 0.98)) {
                 best = t;
                 pick = SplitChoice{pick.shape, s, big != 0};
@@ -1298,12 +1300,12 @@ static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_
 size_t gemm_partial_bytes(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K, size_t room) {
     const int64_t blocks = K / (fp8 ? 128 : 64);
     if (blocks < 32 || ((M + 255) / 256) * ((N + 127) / 128) > 128) return 0;       // (the bound of the loop above at two splits)
-    const SplitChoice c = pick_split(plan_for(M, N, !sparse), M, N, blocks, !sparse, room);
+    const SplitChoice c = pick_split(plan_for(M, N, !sparse), M, N, blocks, !sparse, fp8, room);
     return c.k_splits > 1 ? (size_t)c.k_splits * (size_t)M * (size_t)part_pitch(N) * 4 : 0;
 }
 
 void gemm_choice(bool sparse, bool fp8, int64_t M, int64_t N, int64_t K, size_t room, int out[3]) {
-    const SplitChoice c = pick_split(plan_for(M, N, !sparse), M, N, K / (fp8 ? 128 : 64), !sparse, room);
+    const SplitChoice c = pick_split(plan_for(M, N, !sparse), M, N, K / (fp8 ? 128 : 64), !sparse, fp8, room);
     out[0] = c.k_splits > 1 ? -1 : c.shape;
     out[1] = c.k_splits;
     out[2] = c.part_256 ? 256 : 128;
@@ -1393,7 +1395,8 @@ hipError_t launch_gemm(bool sparse, const GemmArgs& a_in, hipStream_t stream) {
     // The TENSOR factor: formed by the small-tile kernels themselves while that is cheaper than a launch (each of their
     // workgroups reads all rows' sums: up to two passes of workgroups and 2048 rows), else by its own kernel. Whole call
     // [M, 3072, 3072], own kernel -> folded, us: M = 37 12.2 -> 11.1, 512 21.9 -> 20.4, 1024 28.6 -> 27.6; [2000, 512, 1024] 15.4 -> 13.8; 4000 rows lost 0.2.
-    const SplitChoice choice = pick_split(plan, a.M, a.N, a.K / (a.fp8 ? 128 : 64), !sparse, a.partials ? a.partial_bytes : 0);
+    const SplitChoice choice = pick_split(plan, a.M, a.N, a.K / (a.fp8 ? 128 : 64), !sparse, a.fp8,
+                                          a.partials ? a.partial_bytes : 0);
     if (a.rowsums) {
         bool fold = sparse && choice.k_splits == 1 && choice.shape >= 0 && a.M <= 2048;
         if (fold) {
