@@ -1212,17 +1212,18 @@ struct SplitShape {
 };
 // Sparse 256 x 96 (eight waves of 32 rows, ring of four) stands between the 128 x 128 tile and the 256-row plan: with the plan's
 // 256 x 128 tiles an output of 130 to 192 tiles leaves compute units idle and each of the others pulls 34 KB a stage, here up to 256
-// pull 30. Its constants put the line where measurement has it, which is at fewer stages in FP8 (kFixed96Fp8). Forced against the best
+// pull 30. Its constants put the line where measurement has it, which is at fewer stages (kFixed96Early) in FP8 and for widths not divisible by
+// 8, whose 2-byte stores take the plan's tiles longer ([1289, 3372, 512] 22.3 -> 19.8, [864, 5158, 2048] 41.1 -> 36.4). Forced against the best
 // other form at 760 drawn shapes of all sparse kinds that it can run in one pass ([129..16896, 512..21504, 512..15360], inputs from HBM):
-// bf16 58 of 490 take it, FP8 75 of 270, 7.1 % and 4.7 % faster in the mean and none slower by 1 %: sparse [793, 4672, 8960] 98.5 -> 86.0 us, [4906,
-// 832, 11392] 128 -> 119, FP8 [737, 5825, 6400] 52.1 -> 48.7, FP8 + LoRA [434, 10432, 512] 13.9 -> 13.0; with a line at 20 stages bf16 lost up to 9 %
-// ([886, 5952, 1280], [3516, 1504, 1536] 22.7 -> 24.5).
+// bf16 70 of 490 take it, FP8 75 of 270, 6.7 % and 4.7 % faster in the mean and none slower by 1 % (32 of 200 others: 6.1 %, none slower): sparse
+// [793, 4672, 8960] 98.5 -> 86.0 us, [4906, 832, 11392] 128 -> 119, FP8 [737, 5825, 6400] 52.1 -> 48.7, FP8 + LoRA [434, 10432, 512] 13.9 -> 13.0;
+// with a line at 20 stages bf16 lost up to 9 % ([886, 5952, 1280], [3516, 1504, 1536] 22.7 -> 24.5).
 // Dense 256 x 96 (ring of three) for the same reason where 256 x 128 tiles do not reach all units: 108 of 2360 drawn shapes take it, 5.9 % faster
 // than the best other form in the mean, 9.7 % slower at worst.
 constexpr SplitShape kSparseShapes[] = {
     {32, 32, 1.2, 0.087}, {64, 32, 1.9, 0.108}, {64, 64, 2.4, 0.153}, {128, 64, 2.3, 0.19}, {128, 128, 2.8, 0.30},
     {256, 96, 9.2, 0.325}};
-constexpr double kFixed96Fp8 = 3.4;
+constexpr double kFixed96Early = 3.4;
 constexpr SplitShape kDenseShapes[] = {
     {32, 32, 1.45, 0.081}, {64, 32, 1.55, 0.135}, {64, 64, 1.25, 0.19}, {128, 64, 2.5, 0.285}, {128, 128, 3.4, 0.38},
     {256, 128, 4.15, 0.525}, {256, 96, 3.95, 0.44}};
@@ -1235,8 +1236,8 @@ constexpr SplitShape kDenseShapes[] = {
 // budget. One table serves every operand kind, but for the line of the sparse 256 x 96 tile: the others rank the same way in FP8 and LoRA
 // calls (LoRA's residual, 5 us a tile of the 256-row plan, is left out), and LoRA without its residual then sums like the plain call.
 // Against every form forced one by one on drawn shapes that played no part in the fit ([1..16896, 512..21504, 512..15360], inputs from
-// HBM): sparse of all kinds, 700 shapes: 1.1 % slower than the best on average, more than 2 % slower than the 256-row plan at 2; dense,
-// 700 shapes: 0.4 % and 5. (The constants of the dense loop before its 16 x 16 instructions: 2.1 % and 19 of 2360.)
+// HBM): sparse of all kinds, 600 shapes: 1.0 % slower than the best on average, more than 2 % slower than the 256-row plan at 2; dense,
+// 600 shapes: 0.3 % and 5. (The constants of the dense loop before its 16 x 16 instructions: 2.1 % and 19 of 2360.)
 // With the factors at 0.92 (sparse 64 x 64 and 128 x 128) 128 x 128 tiles in several passes lost up to 1.29x to the plan: [1408, 14368,
 // 11904] 303 -> 392 us; above 2048 rows they won more than 3 % at 2 of 220.
 struct SplitChoice {
@@ -1268,7 +1269,7 @@ static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_
         if (passes > 1 && s.bm >= 128 && s.bn >= 128 && M > 2048) continue;
         // (the dense 64 x 64 line was fitted at long K; with one or two blocks it takes what its neighbours do: [161, 6168, 128]
         // 8.2 us against 7.4 with the 256-row plan and 6.4 with 128 x 64, [1981, 1024, 128] 7.4 / 6.2 / 5.5)
-        const double fixed = dense && s.bm == 64 && s.bn == 64 && blocks <= 2 ? 2.4 : fp8 && s.bm == 256 ? kFixed96Fp8 : s.fixed;
+        const double fixed = dense && s.bm == 64 && s.bn == 64 && blocks <= 2 ? 2.4 : !dense && s.bm == 256 && (fp8 || N % 8 != 0) ? kFixed96Early : s.fixed;
         const double several = !dense ? 1.1 : s.bm >= 128 && s.bn >= 128 ? (passes > 2 ? 1.3 : 1.12) : 1.24;
         const double t = (double)passes * (fixed + (double)blocks * block) * (passes > 1 ? several : 1.0);
         if (t < best) {
@@ -1276,13 +1277,15 @@ static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_
             pick.shape = i;
         }
     }
-    // Contraction split over workgroups: at most one workgroup per compute unit, at least 16 blocks each (dense 20), up to six parts
+    // Contraction split over workgroups: at most one workgroup per compute unit, at least 16 blocks each (dense 20, but 16 from 9 to 64
+    // rows, which 32 x 32 tiles would take in full), up to six parts
     // (dense eight). Second launch, writing and reading the planes: 8 us + 0.5 us per MB of planes (dense 5.1 + 0.31); the
     // estimate has to be 2 % better than the best unsplit one.
+    const int64_t min_blocks = dense && (M <= 8 || M > 64) ? 20 : 16;
     for (int big = 0; big < 2; ++big) {
         const int64_t tiles = ((M + (big ? 255 : 127)) / (big ? 256 : 128)) * ((N + 127) / 128);
         const double block = big ? (dense ? 0.535 : 0.35) : (dense ? 0.395 : 0.285);
-        for (int s = 2; s <= (dense ? kMaxKSplits : 6) && tiles * s <= 256 && blocks / s >= (dense ? 20 : 16); ++s) {
+        for (int s = 2; s <= (dense ? kMaxKSplits : 6) && tiles * s <= 256 && blocks / s >= min_blocks; ++s) {
             const double planes = (double)s * (double)M * (double)part_pitch(N) * 4.0;
             if (planes > (double)room) break;
             const double t = (double)((blocks + s - 1) / s) * block + (dense ? 5.1 + planes * 0.31e-6 : 8.0 + planes * 0.5e-6);
