@@ -1216,9 +1216,9 @@ struct SplitShape {
 // 8, whose 2-byte stores take the plan's tiles longer ([1289, 3372, 512] 22.3 -> 19.8, [864, 5158, 2048] 41.1 -> 36.4). Forced against the best
 // other form at 760 drawn shapes of all sparse kinds that it can run in one pass ([129..16896, 512..21504, 512..15360], inputs from HBM):
 // bf16 70 of 490 take it, FP8 75 of 270, 6.7 % and 4.7 % faster in the mean and none slower by 1 % (32 of 200 others: 6.1 %, none slower): sparse
-// [793, 4672, 8960] 98.5 -> 86.0 us, [4906, 832, 11392] 128 -> 119, FP8 [737, 5825, 6400] 52.1 -> 48.7, FP8 + LoRA [434, 10432, 512] 13.9 -> 13.0;
+// [793, 4672, 8960] 98.5 -> 86.0 us, [4906, 832, 11392] 137.8 -> 128.2, FP8 [737, 5825, 6400] 52.1 -> 48.7, FP8 + LoRA [434, 10432, 512] 13.9 -> 13.0;
 // with a line at 20 stages bf16 lost up to 9 % ([886, 5952, 1280], [3516, 1504, 1536] 22.7 -> 24.5).
-// Dense 256 x 96 (ring of three) for the same reason where 256 x 128 tiles do not reach all units: 108 of 2360 drawn shapes take it, 5.9 % faster
+// Dense 256 x 96 (ring of three) for the same reason where 256 x 128 tiles (which the plan's tails are) do not reach all units: 108 of 2360 drawn shapes take it, 5.9 % faster
 // than the best other form in the mean, 9.7 % slower at worst.
 constexpr SplitShape kSparseShapes[] = {
     {32, 32, 1.2, 0.087}, {64, 32, 1.9, 0.108}, {64, 64, 2.4, 0.153}, {128, 64, 2.3, 0.19}, {128, 128, 2.8, 0.30},
@@ -1226,7 +1226,7 @@ constexpr SplitShape kSparseShapes[] = {
 constexpr double kFixed96Early = 3.4;
 constexpr SplitShape kDenseShapes[] = {
     {32, 32, 1.45, 0.081}, {64, 32, 1.55, 0.135}, {64, 64, 1.25, 0.19}, {128, 64, 2.5, 0.285}, {128, 128, 3.4, 0.38},
-    {256, 128, 4.15, 0.525}, {256, 96, 3.95, 0.44}};
+    {256, 96, 3.95, 0.44}};
 
 // How the problem should run. Times are estimated from the measured constants: a small shape needs ceil(tiles / 256)
 // passes over the 256 compute units; with more than one, all units pull operands all the time and slow each other down
@@ -1261,8 +1261,7 @@ static SplitChoice pick_split(const TilePlan& plan, int64_t M, int64_t N, int64_
         double block = s.block;
         if (s.bm == 256) {                                 // one pass only, slower as the chip fills (its rivals are, in the sparse case)
             if (tiles > 256) continue;
-            if (dense && s.bn == 128 && tiles > 96) block += 0.0029 * (double)(tiles - 96);
-            if (dense && s.bn == 96 && tiles > 128) block += 0.0021 * (double)(tiles - 128);
+            if (dense && tiles > 128) block += 0.0021 * (double)(tiles - 128);
         }
         if (dense && s.bm == 32) block += 0.0005 * (double)(M < 32 ? M : 32);      // (rows past M repeat the last one: less to pull)
         const int64_t passes = (tiles + 255) / 256;
@@ -1341,7 +1340,6 @@ static hipError_t with_split(int i, Op op) {
             case 2: return op(Split<false, 64, 64, 1, 2, 2, 4>{});
             case 3: return op(Split<false, 128, 64, 2, 2, 2, 3>{});
             case 4: return op(Split<false, 128, 128, 2, 2, 1, 3>{});
-            case 5: return op(Split<false, 256, 128, 4, 2, 1, 3>{});
             default: return op(Split<false, 256, 96, 4, 2, 1, 3>{});
         }
     }
@@ -1375,8 +1373,8 @@ hipError_t prepare_gemm_kernels() {
         run(with_split<true, 1, false>(i, prep));
         run(with_split<true, 0, true>(i, prep));
         run(with_split<true, 1, true>(i, prep));
+        run(with_split<false, 0, false>(i, prep));
     }
-    for (int i = 0; i < 7; ++i) run(with_split<false, 0, false>(i, prep));
     for (int i = 0; i < 2; ++i) {
         run(with_part<false, 0, false>(i != 0, prep));
         run(with_part<true, 0, false>(i != 0, prep));

@@ -227,7 +227,7 @@ def test_every_entry_point_plans_the_same_contraction_split():
 ])
 def test_tile_choice_keeps_the_256_row_plan_where_small_tiles_are_slower(sparse, fp8, M, N, K):
     """(or takes 256 x 96 tiles, which run in one pass only)"""
-    assert gemm_choice(sparse, fp8, M, N, K)[:2] in ((-1, 1), (5, 1) if sparse else (6, 1))
+    assert gemm_choice(sparse, fp8, M, N, K)[:2] in ((-1, 1), (5, 1))
 
 
 def test_tile_choice_where_small_tiles_are_faster():
@@ -239,6 +239,15 @@ def test_tile_choice_where_small_tiles_are_faster():
     assert gemm_choice(False, False, 333, 3072, 12288)[1] > 1
     for s in ((161, 6168, 128), (1981, 1024, 128), (2686, 640, 128), (319, 6336, 128)):      # dense 64 x 64: slower than the 256-row plan
         assert gemm_choice(False, False, *s)[0] in (3, 4)
+
+
+def test_small_tile_shapes_of_the_gpu_tests_reach_every_tile():
+    """The lists the parity tests run: every shape of the small-tile tables, sparse, dense and FP8, and the several-pass forms."""
+    from test_parity_gpu import SMALL_TILE_SHAPES, SMALL_TILE_SHAPES_FP8
+    for sparse, fp8, shapes in ((True, False, SMALL_TILE_SHAPES), (False, False, SMALL_TILE_SHAPES), (True, True, SMALL_TILE_SHAPES_FP8)):
+        assert {gemm_choice(sparse, fp8, *s)[0] for s in shapes} >= set(range(6)), (sparse, fp8)
+    assert gemm_choice(True, False, 1, 16421, 6144)[:2] == (0, 1)           # 514 tiles
+    assert gemm_choice(False, False, 357, 21102, 1536)[:2] == (4, 1)        # 495 tiles
 
 
 def test_waves_of_a_row_make_no_extra_trips():

@@ -599,9 +599,9 @@ def test_sparse_lora_linear_zero_factor_equals_sparse_linear():
     assert torch.equal(Y0, rtl.sparse_linear(X, W, comp=rtl.COMP_GROUP))
 
 
-@pytest.mark.parametrize("M,N,K", [(257, 12283, 3136), (129, 21504, 7168), (2050, 2651, 4480)])
+@pytest.mark.parametrize("M,N,K", [(257, 12283, 3136), (129, 21504, 7168), (2050, 2651, 4480), (257, 12280, 3136), (2050, 2648, 4480)])
 def test_sparse_tiles_of_256_by_96(M, N, K):
-    """The 256 x 96 tile: one row in the last panel, partial last column tiles (also an odd width, 2-byte stores), an odd number of
+    """The 256 x 96 tile: one row in the last panel, partial last column tiles (wide stores and, for odd widths, 2-byte ones), an odd number of
     k blocks, and every kind of operand; TENSOR forms its factor in the kernel up to 2048 rows and before it beyond."""
     X = synth.activations("laplace_outlier", M, K, seed=71, device=DEV)
     W = synth.weights(N, K, seed=72, device=DEV)
@@ -626,17 +626,41 @@ def test_sparse_tiles_of_256_by_96(M, N, K):
         assert rel_max_err(Y[sel].float().cpu().numpy(), r["Y"]) <= Y_TOL
 
 
-@pytest.mark.parametrize("M,N,K", [(129, 18115, 576), (1281, 3331, 1856), (2050, 2564, 704)])
+@pytest.mark.parametrize("M,N,K", [(129, 21504, 7168), (2050, 2651, 4480), (129, 16808, 128), (140, 17448, 128), (2050, 2648, 4480)])
+def test_fp8_tiles_of_256_by_96(M, N, K):
+    """The same tile on FP8 operands, plain and LoRA: from one stage on, partial last column tiles with wide and with 2-byte stores."""
+    X = synth.activations("laplace_outlier", M, K, seed=81, device=DEV)
+    W = synth.weights(N, K, seed=82, device=DEV)
+    b = synth.bias(N, seed=83, device=DEV)
+    LA, LB = synth.lora(N, K, 64, seed=84, device=DEV, std_a=0.1, std_b=0.1)
+    assert gemm_choice(True, True, M, N, K)[:2] == (5, 1)
+    sel = torch.tensor([0, M - 2, M - 1], device=DEV)
+    xs, Wq = fp8_scale(X), rtl.quantize_fp8(W)
+    Xs, Wn, f, bb = synth.bits(X[sel]), Wq.cpu().numpy(), float(xs.item()), synth.bits(b)
+    Y, guard_ok = guarded((M, N), torch.bfloat16, 7.0)
+    rtl.sparse_linear_fp8(X, Wq, xs, bias=b, out=Y)
+    guard_ok()
+    r = oracle.sparse_linear_fp8_oracle(Xs, Wn, f, bias=bb, scope=oracle.GROUP)
+    check_y_fp8(Y[sel], r, Wn, f, bias=bb, max_rows=1)
+    r = oracle.sparse_lora_linear_fp8_oracle(Xs, Wn, f, synth.bits(LA), synth.bits(LB), bias=bb, scope=oracle.GROUP)
+    assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b)[sel]), r["Y"]) <= Y_TOL
+
+
+@pytest.mark.parametrize("M,N,K", [(129, 18115, 576), (1281, 3331, 1856), (2050, 2564, 704), (129, 18120, 576), (1281, 3336, 1856),
+                                   (2050, 2568, 704)])
 def test_dense_tiles_of_256_by_96(M, N, K):
-    """The dense 256 x 96 tile: few rows in the last panel, partial last column tiles (odd widths too), odd numbers of k blocks."""
+    """The dense 256 x 96 tile: few rows in the last panel, partial last column tiles (2-byte stores for odd widths, wide ones for the
+    others and, past a padded row stride, for odd ones too), odd numbers of k blocks."""
     X = synth.activations("gelu", M, K, seed=75, device=DEV)
     W = synth.weights(N, K, seed=76, device=DEV)
     b = synth.bias(N, seed=77, device=DEV)
-    assert gemm_choice(False, False, M, N, K)[:2] == (6, 1)
+    assert gemm_choice(False, False, M, N, K)[:2] == (5, 1)
     rows = np.array([0, M // 2, M - 2, M - 1])
     sel = torch.from_numpy(rows).to(DEV)
-    check_y(rtl.dense_linear(X, W, bias=b)[sel],
-            oracle.dense_linear_oracle(synth.bits(X[sel]), synth.bits(W), bias=synth.bits(b)))
+    Y = rtl.dense_linear(X, W, bias=b)
+    check_y(Y[sel], oracle.dense_linear_oracle(synth.bits(X[sel]), synth.bits(W), bias=synth.bits(b)))
+    padded = torch.full((M, (N + 15) // 8 * 8), 7.0, dtype=torch.bfloat16, device=DEV)
+    assert torch.equal(rtl.dense_linear(X, W, bias=b, out=padded[:, :N]), Y) and bool((padded[:, N:] == 7.0).all())
 
 
 @pytest.mark.parametrize("comp", COMPS)
@@ -1176,12 +1200,17 @@ def test_randomized_linear_cases():
         assert rel_max_err(y8l, r8l["Y"]) <= Y_TOL
 
 
-# One output per tile shape of the small-tile loop (32x32, 64x32, 64x64, 128x64, 128x128, dense 256x128 as the sizes
-# grow), ragged in M and N, with block counts that are short of, equal to and not a multiple of the K groups; the last two
-# take several passes over the compute units (sparse 32x32, dense 128x128).
-@pytest.mark.parametrize("M,N,K", [(1, 1, 64), (31, 33, 128), (33, 31, 192), (37, 1000, 4672), (65, 3071, 1088), (97, 3072, 3136),
-                                   (129, 1553, 832), (201, 3009, 1344), (393, 3041, 1600), (700, 3000, 704), (777, 3072, 3072),
-                                   (1301, 3065, 576), (1, 16421, 6144), (259, 16976, 2048)])
+# Outputs for every tile shape of the small-tile loop (32x32, 64x32, 64x64, 128x64, 128x128, 256x96 as the sizes grow; which
+# of them reaches which is asserted on the host), ragged in M and N, with block counts that are short of, equal to and not a
+# multiple of the K groups, and 32x32 and dense 128x128 tiles in several passes over the compute units.
+SMALL_TILE_SHAPES = [(1, 1, 64), (31, 33, 128), (33, 31, 192), (37, 1000, 4672), (65, 3071, 1088), (97, 3072, 3136),
+                     (129, 1553, 832), (201, 3009, 1344), (393, 3041, 1600), (700, 3000, 704), (777, 3072, 3072),
+                     (1301, 3065, 576), (1, 16421, 6144), (259, 16976, 2048), (357, 21102, 1536)]
+SMALL_TILE_SHAPES_FP8 = [(1, 1, 128), (33, 31, 384), (37, 1000, 4736), (97, 3072, 3200), (201, 3009, 1408), (393, 3041, 1664),
+                         (700, 3000, 640), (129, 16523, 128)]
+
+
+@pytest.mark.parametrize("M,N,K", SMALL_TILE_SHAPES)
 @pytest.mark.parametrize("comp", [rtl.COMP_GROUP, rtl.COMP_ROW])
 def test_small_tiles_sparse_dense_and_lora(M, N, K, comp):
     """Sampled rows against the oracle, guard bytes around Y, and every form that shares the tile loop: sparse,
@@ -1260,8 +1289,7 @@ def test_fp8_256_column_bodies_on_both_sides_of_the_pinning_rule(K):
     assert rel_max_err(y_to_np(rtl.sparse_lora_linear_fp8(X, Wq, xs, LA, LB, bias=b)[sel]), r["Y"]) <= Y_TOL
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 1, 128), (33, 31, 384), (37, 1000, 4736), (97, 3072, 3200), (201, 3009, 1408),
-                                   (393, 3041, 1664), (700, 3000, 640)])
+@pytest.mark.parametrize("M,N,K", SMALL_TILE_SHAPES_FP8)
 def test_small_tiles_fp8(M, N, K):
     X = synth.activations("laplace", M, K, seed=M + N, device=DEV)
     W = synth.weights(N, K, seed=K, device=DEV)
