@@ -21,8 +21,9 @@
 // 1730 against 1556 TFLOP/s (dense bf16), 1470 against 1395 (sparse bf16, executed) and 2865 against 2725 (sparse FP8):
 // twice the operand reads per multiply-add cost less than halving the accumulator traffic saves. On zeros all reach 2130
 // to 2230. In a tile loop a stalled wave has half the time to come back before the matrix core runs dry, and the small
-// instructions lose 3 % (dense) to 8 % (sparse) of the cycles. Dense gains from 16 (rtl_dense_linear on inputs that come from
-// HBM, 32 -> 16, us: [4608, 9216, 3072] 229.5 -> 217.3, [4096, 3072, 12288] 268.4 -> 261.3, [4608, 3072, 3072] 82.6 -> 80.4,
+// instructions lose 3 % (dense) to 8 % (sparse) of the cycles. Dense gains from 16 (this loop built in both sizes, before its
+// tails and its table were fitted to 16; the whole change from the loop before it was worth 3 % at [4608, 9216, 3072]. rtl_dense_linear on
+// inputs from HBM, 32 -> 16, us: [4608, 9216, 3072] 229.5 -> 217.3, [4096, 3072, 12288] 268.4 -> 261.3, [4608, 3072, 3072] 82.6 -> 80.4,
 // [800, 9216, 3072] 61.1 -> 59.1); sparse ties ([4096, 3072, 12288] 188.1 -> 186.6, [4608, 12288, 3072] 199.9 -> 200.5,
 // [16896, 12288, 3072] 724.8 -> 723.9, FP8 [4608, 3072, 12288] 131.4 -> 131.2) and loses with 128 x 128 tiles ([1500, 3072, 3072] 31.6
 // -> 33.1).
@@ -125,13 +126,13 @@ __device__ __forceinline__ void wait_vmcnt_lgkm0() {   // vmcnt <= N, all LDS re
     __builtin_amdgcn_s_waitcnt(0x0070 | (N & 0xF) | ((N >> 4) << 14));
 }
 
-// Per-stage LDS footprint. Rows of the A tile hold 64 bytes in the sparse kernels (the kept half) and 128 in
-// the dense one; rows of the B tile hold 128 bytes, so that every L2 request of a row-major operand is a
-// whole line. WAVES_K > 1: a stage holds one k block per K group (see gemm_tile), kGroup bytes each.
 // Size of the matrix instructions (see the top of the file).
 template <bool SPARSE>
 constexpr int kMmaSize = SPARSE ? 32 : 16;
 
+// Per-stage LDS footprint. Rows of the A tile hold 64 bytes in the sparse kernels (the kept half) and 128 in
+// the dense one; rows of the B tile hold 128 bytes, so that every L2 request of a row-major operand is a
+// whole line. WAVES_K > 1: a stage holds one k block per K group (see gemm_tile), kGroup bytes each.
 template <bool SPARSE, int BM, int BN, int STAGES, int WAVES_M, int WAVES_N, bool FP8, int WAVES_K = 1>
 struct Smem {
     static constexpr int kABytes = BM * (SPARSE ? 64 : 128);
